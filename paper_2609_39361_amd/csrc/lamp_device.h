@@ -37,6 +37,19 @@ __device__ __forceinline__ uint32_t pk_e4m3_sat(float a, float b, uint32_t old =
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, false);
 }
 
+// The same into bits [23:16] and [31:24], bits [15:0] kept.
+__device__ __forceinline__ uint32_t pk_e4m3_hi(float a, float b, uint32_t old)
+{
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, true);
+}
+
+__device__ __forceinline__ uint32_t pk_e4m3_sat_hi(float a, float b, uint32_t old)
+{
+    a = __builtin_amdgcn_fmed3f(a, -448.0f, 448.0f);
+    b = __builtin_amdgcn_fmed3f(b, -448.0f, 448.0f);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, true);
+}
+
 // Pointers into read-only memory that every lane of a wave reads at the same
 // address: the constant address space makes the compiler use scalar loads.
 typedef const float __attribute__((address_space(4))) *kptr32_t;
@@ -53,6 +66,19 @@ __device__ __forceinline__ float2 unpk_e4m3(uint32_t r)
 {
     auto v = __builtin_amdgcn_cvt_pk_f32_fp8((int)r, false);
     return make_float2(v[0], v[1]);
+}
+
+// Of four codes, one per byte, the two of bits [15:0] (half 0) or [31:16]
+// (half 1) decoded, or moved to the low bytes of 16-bit slots.
+__device__ __forceinline__ float2 unpk_e4m3x4(uint32_t w, int half)
+{
+    auto v = half ? __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
+    return make_float2(v[0], v[1]);
+}
+
+__device__ __forceinline__ uint32_t spread_codes(uint32_t w, int half)
+{
+    return __builtin_amdgcn_perm(0u, w, half ? 0x0C030C02u : 0x0C010C00u);
 }
 
 __device__ __forceinline__ float e4m3_value(uint32_t code)

@@ -118,7 +118,8 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
 
     // per-slot row, query index and visible key range [vlo, vhi]
     int row[QPL], vlo[QPL], vhi[QPL];
-    const float *qrow[QPL];
+    QRows<QPL> qr;
+    qr.off = (uint32_t)lane * D * 4u;
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         row[s] = s * 64 + lane;
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             vlo[s] = p.N;
             vhi[s] = -1;
         }
-        qrow[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + j) * D;   // zero-padded rows, in bounds
+        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + 64 * s) * D;   // zero-padded rows, in bounds
     }
     // visible key range of the whole block
     const int bv_lo = p.window > 0 ? (q0 - p.window + 1 > 0 ? q0 - p.window + 1 : 0) : 0;
@@ -198,10 +199,10 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                 uint32_t n = 0;
                 for (uint32_t m = atmax; m; m &= m - 1) {
                     const int bit = __builtin_ctz(m);
-                    const float *qr = qrow[0];
+                    const float *qrow = qr.row(0);
 #pragma unroll
-                    for (int s = 1; s < QPL; ++s) qr = bit / (2 * NWD) == s ? qrow[s] : qr;
-                    n += y16_saturates<D, RowLay<D>>(qr, kt32 + (size_t)(kc + bit % (2 * NWD)) * D) ? 1u : 0u;
+                    for (int s = 1; s < QPL; ++s) qrow = bit / (2 * NWD) == s ? qr.row(s) : qrow;
+                    n += y16_saturates<D, RowLay<D>>(qrow, kt32 + (size_t)(kc + bit % (2 * NWD)) * D) ? 1u : 0u;
                 }
                 if (n) atomicAdd(&stl[ST_SAT16], n);
             }
@@ -218,12 +219,12 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             for (int ch = 0; ch < KPW / 16; ++ch) {
                 const int kc = key0 + ch * 16;
                 uint32_t yc[QPL][8];
-                rec16_keys<D, QPL, 16>(qrow, kt32 + (size_t)(kc + (lane & 15)) * D, yc);
+                rec16_keys<D, QPL, 16>(qr, keys16<RowLay<D>>(kt32 + (size_t)kc * D), yc);
                 fn(kc, yc);
             }
         } else {
             uint32_t yc[QPL][KPW / 2];
-            rec16_keys<D, QPL, KPW>(qrow, kt32 + (size_t)(key0 + (lane & 15) % KPW) * D, yc);
+            rec16_keys<D, QPL, KPW>(qr, keys_at<RowLay<D>>(kt32 + (size_t)key0 * D, (uint32_t)((lane & 15) % KPW) * D), yc);
             fn(key0, yc);
         }
     };
@@ -271,14 +272,14 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                         const int c16 = th * CPS + ch;
                         const int ck0 = k0 + c16 * 16;
                         if (ck0 > bv_hi || ck0 + 15 < bv_lo) continue;   // nothing visible in the block
-                        uint32_t a8[QPL][8], sat[QPL];
+                        uint32_t a8[QPL][4], sat[QPL];
                         if constexpr (SR) {
                             int jq[QPL];
 #pragma unroll
                             for (int s = 0; s < QPL; ++s) jq[s] = q0 + row[s];
-                            sr8_chunk<D, QPL>(qrow, kt32 + (size_t)ck0 * D, p.seed, (uint64_t)bh, jq, ck0, a8, sat);
+                            sr8_chunk<D, QPL>(qr, kt32 + (size_t)ck0 * D, p.seed, (uint64_t)bh, jq, ck0, a8, sat);
                         } else {
-                            emu8_chunk<D, QPL>(qrow, kt32 + (size_t)ck0 * D, a8, sat);
+                            emu8_any<D, QPL, false>(qr, keys16<RowLay<D>>(kt32 + (size_t)ck0 * D), a8, sat);
                         }
                         auto vis16 = [&](int s) {
                             uint32_t m = 0;
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
 #pragma unroll
                                     for (int i = 0; i < 4; ++i) {
                                         const int key = 4 * q4 + i;
-                                        const uint32_t code = (a8[s][key >> 1] >> (8 * (key & 1))) & 0xFFu;
+                                        const uint32_t code = (a8[s][key >> 2] >> (8 * (key & 3))) & 0xFFu;
                                         x |= ((vm >> key & 1u) ? code : 0xFFu) << (8 * i);
                                     }
                                     wd[q4] = x;
@@ -323,14 +324,14 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                             uint32_t packed[8];
 #pragma unroll
                             for (int pp = 0; pp < 8; ++pp) {
-                                const float2 yv = unpk_e4m3(a8[s][pp]);
+                                const float2 yv = unpk_e4m3x4(a8[s][pp / 2], pp & 1);
                                 const int i0 = ck0 + 2 * pp;
                                 // invisible keys enter as -inf, by selection rather than branches
                                 const float x0 = (full || visible(s, i0)) ? yv.x : NEG_INF;
                                 const float x1 = (full || visible(s, i0 + 1)) ? yv.y : NEG_INF;
                                 mx[s] = x0 > mx[s] ? x0 : mx[s];
                                 mx[s] = x1 > mx[s] ? x1 : mx[s];
-                                packed[pp] = (a8[s][pp] & 0xFFu) | ((a8[s][pp] & 0xFF00u) << 8);
+                                packed[pp] = spread_codes(a8[s][pp / 2], pp & 1);
                             }
                             u32x4 *dst = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + c16 * 16);
                             dst[0] = u32x4{packed[0], packed[1], packed[2], packed[3]};
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                         const int ck0 = k0 + c16 * 16;
                         if (ck0 > bv_hi || ck0 + 15 < bv_lo) continue;
                         uint32_t yc[QPL][8];
-                        rec16_chunk<D, QPL>(qrow, kt32 + (size_t)ck0 * D, yc);
+                        rec16_keys<D, QPL, 16>(qr, keys16<RowLay<D>>(kt32 + (size_t)ck0 * D), yc);
                         obs16(ck0, yc);
 #pragma unroll
                         for (int s = 0; s < QPL; ++s) {

@@ -204,9 +204,9 @@ __device__ __forceinline__ int wave_max_i32(int v)
 // OBS: the instantiation that also writes the logit observables (p.dbg_y8,
 // p.dbg_y16); the same code otherwise, kept apart so that the stores do not
 // change the register allocation of the instantiations that do not.
-// CMP: the compact register layout (Sec. 3.3, "Register layout"): the fused
-// pass keeps the 8-bit codes four per register and computes the 16-bit logits
-// of at most one speculative sub-block; when two or more are flagged (a
+// CMP: the schedule of the compact register layout (Sec. 3.3, "Register
+// layout"): the fused pass computes the 16-bit logits of at most one
+// speculative sub-block; when two or more are flagged (a
 // "disruptive" tile) the others follow in a sequential 16-bit pass once the
 // 8-bit codes are stored.  A schedule only: the results are those of the safe
 // layout.
@@ -272,7 +272,8 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     const bool mu_trunc = (p.flags & LAMP_MU_TRUNC) != 0u;
 
     int row[QPL], vlo[QPL], vhi[QPL], jq[QPL];
-    const float *qrow[QPL];
+    QRows<QPL> qr;   // grouped layout: 64-row blocks stored [group][row][4] (zero-padded rows, in bounds)
+    qr.off = (uint32_t)lane * 16u;
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         row[s] = s * 64 + lane;
@@ -284,8 +285,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             vlo[s] = p.N;
             vhi[s] = -1;
         }
-        // grouped layout: 64-row blocks stored [group][row][4] (zero-padded rows, in bounds)
-        qrow[s] = p.qt + ((size_t)b * p.Hq + h) * p.Nq * D + (size_t)(j / 64) * 64 * D + (j % 64) * 4;
+        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + 64 * s) * D;
     }
     const int bv_lo = p.window > 0 ? (q0 - p.window + 1 > 0 ? q0 - p.window + 1 : 0) : 0;
     const int bv_hi = p.causal ? (q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1) : p.N - 1;
@@ -294,6 +294,13 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     const float *kt32 = p.kt32 + ((size_t)b * p.Hkv + hk) * (size_t)p.Nk * D;   // fp32 keys, grouped layout
     // row of key i in the grouped layout (16-key blocks stored [group][key][4])
     auto krow_of = [&](int i) { return kt32 + (size_t)(i / 16) * 16 * D + (i % 16) * 4; };
+    // this wave's 4 keys of each member of the set m of sub-blocks of the tile
+    // at k0, the g-th member's in lanes 4g .. 4g+3 of every 16-lane row
+    auto member_keys = [&](int k0, uint32_t m) {
+        const int kk = (lane & 15) % (4 * __builtin_popcount(m));
+        for (int g = 0; g < kk / 4; ++g) m &= m - 1;
+        return keys_at<GrpLay>(kt32 + (size_t)k0 * D, (uint32_t)(__builtin_ctz(m) * BK * D + (w * 4 + (kk & 3)) * 4));
+    };
     const uint16_t *vtbase = p.vt + ((size_t)b * p.Hkv + hk) * (size_t)D * p.Nk;    // V^T [D][Nk]
     uint8_t *mrow = p.mask + (((size_t)b * p.Hq + h) * nqb + qb) * (size_t)(p.Nk / BK);
 
@@ -351,7 +358,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     // 8-bit codes of this wave's sub-block of `tile` into its code buffer, the
     // column maxima over visible keys into m8s (NEG_INF for a sub-block that
     // was not emulated)
-    auto emit8 = [&](int tile, const uint32_t (&a8)[QPL][8], bool done, const uint32_t (&sat)[QPL]) {
+    auto emit8 = [&](int tile, const uint32_t (&a8)[QPL][Y8_WORDS<SIMP>], bool done, const uint32_t (&sat)[QPL]) {
         const int ck0 = tile * KPT + w * BK;
         uint16_t *yc = ycode_of(tile);
         float *m8s = m8s_of(tile);
@@ -388,7 +395,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int key = 4 * q4 + i;
-                            const uint32_t code = (a8[s][key >> 1] >> (8 * (key & 1))) & 0xFFu;
+                            const uint32_t code = (a8[s][key >> 2] >> (8 * (key & 3))) & 0xFFu;
                             x |= ((vm >> key & 1u) ? code : 0xFFu) << (8 * i);
                         }
                         wd[q4] = x;
@@ -410,14 +417,14 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     for (int pp = 0; pp < 8; ++pp) {
                         const float2 yv = SIMP ? make_float2(bf16_value(a8[s][pp] & 0xFFFFu),
                                                              bf16_value(a8[s][pp] >> 16))
-                                               : unpk_e4m3(a8[s][pp]);
+                                               : unpk_e4m3x4(a8[s][pp / 2], pp & 1);
                         const int i0 = ck0 + 2 * pp;
                         // invisible keys enter as -inf, by selection rather than branches
                         const float x0 = (FULL || visible(s, i0)) ? yv.x : NEG_INF;
                         const float x1 = (FULL || visible(s, i0 + 1)) ? yv.y : NEG_INF;
                         mx = x0 > mx ? x0 : mx;
                         mx = x1 > mx ? x1 : mx;
-                        packed[pp] = SIMP ? a8[s][pp] : (a8[s][pp] & 0xFFu) | ((a8[s][pp] & 0xFF00u) << 8);
+                        packed[pp] = SIMP ? a8[s][pp] : spread_codes(a8[s][pp / 2], pp & 1);
                     }
                     u32x4 *dst = reinterpret_cast<u32x4 *>(yc + row[s] * YP + w * BK);
                     dst[0] = u32x4{packed[0], packed[1], packed[2], packed[3]};
@@ -490,7 +497,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         const int key0 = k0 + th * BK + w * 4;
         if (key0 > bv_hi || key0 + 3 < bv_lo) return;   // nothing visible in the block
         uint32_t yc[QPL][WPM];
-        rec16_keys<D, QPL, 4, SIMP, GrpLay>(qrow, krow_of(key0 + (lane & 3)), yc);
+        rec16_keys<D, QPL, 4, SIMP, GrpLay>(qr, keys_at<GrpLay>(krow_of(key0), 4u * (lane & 3)), yc);
         fn(key0, yc);
     };
     // a 16-bit exponential from the table in global memory as bf16 high / low
@@ -541,10 +548,10 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     uint32_t n = 0;
                     for (uint32_t m = atmax; m; m &= m - 1) {
                         const int bit = __builtin_ctz(m);
-                        const float *qr = qrow[0];
+                        const float *qrow = qr.row(0);
 #pragma unroll
-                        for (int s = 1; s < QPL; ++s) qr = bit / 4 == s ? qrow[s] : qr;
-                        n += y16_saturates<D, GrpLay>(qr, krow_of(key0 + bit % 4)) ? 1u : 0u;
+                        for (int s = 1; s < QPL; ++s) qrow = bit / 4 == s ? qr.row(s) : qrow;
+                        n += y16_saturates<D, GrpLay>(qrow, krow_of(key0 + bit % 4)) ? 1u : 0u;
                     }
                     if (n) atomicAdd(&stl[ST_SAT16], n);
                 }
@@ -583,12 +590,12 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     uint32_t act = active_of(t);
     if (mode != MODE_ALL16) {
         const bool done = own_emulated(t, act);
-        uint32_t a8[QPL][8], sat[QPL];
+        uint32_t a8[QPL][Y8_WORDS<SIMP>], sat[QPL];
         if (done) {
             if constexpr (SR)
-                sr8_chunk_bc<D, QPL, GrpLay>(qrow, kt32 + (size_t)(t * KPT + w * BK) * D, jq, (uint32_t)(t * KPT + w * BK),
+                sr8_chunk_bc<D, QPL, GrpLay>(qr, kt32 + (size_t)(t * KPT + w * BK) * D, jq, (uint32_t)(t * KPT + w * BK),
                                              (uint32_t)(b * p.Hq + h), p.seed, a8, sat);
-            else emu8_any<D, QPL, SIMP, GrpLay>(qrow, kt32 + (size_t)(t * KPT + w * BK) * D, a8, sat);
+            else emu8_any<D, QPL, SIMP, GrpLay>(qr, keys16<GrpLay>(kt32 + (size_t)(t * KPT + w * BK) * D), a8, sat);
         }
         emit8(t, a8, done, sat);
     }
@@ -608,22 +615,16 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         {
             const int nf_all = __builtin_popcount(F0);
             const int nf = CMP ? (nf_all < 1 ? nf_all : 1) : nf_all;   // members in the fused pass
-            const int kk = nf ? (lane & 15) % (4 * nf) : 0;
-            int thg = 0;
-            if (nf) {
-                uint32_t m = F0;
-                for (int g = 0; g < kk / 4; ++g) m &= m - 1;
-                thg = __builtin_ctz(m);
-            }
-            const float *krowr = krow_of(k0 + thg * BK + w * 4 + (kk & 3));
+            // CMP: the lowest member alone
+            const KRows kr = nf ? member_keys(k0, CMP ? F0 & (0u - F0) : F0) : KRows{kt32, 0u};
             const bool emu = mode != MODE_ALL16 && has_next && own_emulated(t + 1, act_next);
             const float *k32e = kt32 + (size_t)(k0 + KPT + w * BK) * D;   // read only when emu (then below N)
-            uint32_t a8[QPL][8], sat8[QPL];
+            uint32_t a8[QPL][Y8_WORDS<SIMP>], sat8[QPL];
             auto run = [&](auto nkey_c, auto emu_c) {
                 constexpr int NKEY = decltype(nkey_c)::value;
                 constexpr bool EMU = decltype(emu_c)::value;
                 uint32_t c[QPL][y16_words<SIMP>(NKEY)];
-                fused_pass<D, QPL, NKEY, EMU, SIMP, GrpLay, CMP>(qrow, k32e, krowr, a8, c, sat8);
+                fused_pass<D, QPL, NKEY, EMU, SIMP, GrpLay>(qr, keys16<GrpLay>(k32e), kr, a8, c, sat8);
                 if constexpr (NKEY > 0)
 #pragma unroll
                     for (int s = 0; s < QPL; ++s)
@@ -652,7 +653,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             }
             if constexpr (SR)
                 if (emu)
-                    sr8_chunk_bc<D, QPL, GrpLay>(qrow, k32e, jq, (uint32_t)(k0 + KPT + w * BK), (uint32_t)(b * p.Hq + h),
+                    sr8_chunk_bc<D, QPL, GrpLay>(qr, k32e, jq, (uint32_t)(k0 + KPT + w * BK), (uint32_t)(b * p.Hq + h),
                                                  p.seed, a8, sat8);
             LAMP_PH(0);
             if (has_next && mode != MODE_ALL16) emit8(t + 1, a8, emu, sat8);
@@ -661,14 +662,11 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 // 16-bit pass (4 keys of each per wave, as in the fused pass)
                 if (nf_all >= 2) {
                     const int nr = nf_all - 1;
-                    const int kb = (lane & 15) % (4 * nr);
-                    uint32_t m = F0 & (F0 - 1u);   // without the member of the fused pass
-                    for (int g = 0; g < kb / 4; ++g) m &= m - 1;
-                    const float *krow = krow_of(k0 + __builtin_ctz(m) * BK + w * 4 + (kb & 3));
+                    const KRows krs = member_keys(k0, F0 & (F0 - 1u));   // without the member of the fused pass
                     auto seq = [&](auto nkey_c) {
                         constexpr int NKEY = decltype(nkey_c)::value;
                         uint32_t c[QPL][y16_words<SIMP>(NKEY)];
-                        rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qrow, krow, c);
+                        rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
 #pragma unroll
                         for (int s = 0; s < QPL; ++s)
 #pragma unroll
@@ -1181,14 +1179,11 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     uint32_t y16b[QPL][4 * WPM];
                     if (Rn) {
                         const int nr = __builtin_popcount(Rn);
-                        const int kb = (lane & 15) % (4 * nr);
-                        uint32_t m = Rn;
-                        for (int g = 0; g < kb / 4; ++g) m &= m - 1;
-                        const float *krow = krow_of(k0 + __builtin_ctz(m) * BK + w * 4 + (kb & 3));
+                        const KRows krs = member_keys(k0, Rn);
                         auto rec = [&](auto nkey_c) {
                             constexpr int NKEY = decltype(nkey_c)::value;
                             uint32_t c[QPL][y16_words<SIMP>(NKEY)];
-                            rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qrow, krow, c);
+                            rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
 #pragma unroll
                             for (int s = 0; s < QPL; ++s)
 #pragma unroll

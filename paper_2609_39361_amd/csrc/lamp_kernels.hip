@@ -209,7 +209,7 @@ __global__ void build_sim_tables_kernel(uint16_t *__restrict__ sim8, uint32_t *_
 // ------------------------------------------------------------------ logits entry kernels
 // One wave: 64 rows x (16*NC) keys.  grid.x = B*Hq*ceil(nrows/64), grid.y = N/(16*NC).
 template <int D, int NC, bool SR>
-__global__ __launch_bounds__(64) void logits8_kernel(LogitsParams p)
+__global__ __launch_bounds__(64, 2) void logits8_kernel(LogitsParams p)
 {
     const int lane = threadIdx.x;
     const int nrg = (p.nrows + 63) / 64;
@@ -220,33 +220,31 @@ __global__ __launch_bounds__(64) void logits8_kernel(LogitsParams p)
     const int r = rg * 64 + lane;
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
-    const float *qrow[1] = {p.qt + (((size_t)b * p.Hq + h) * p.N + j) * D};
+    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
     for (int g = 0; g < NC; ++g) {
         const int key0 = (blockIdx.y * NC + g) * 16;
         const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
-        uint32_t acc[1][8], sat[1];
+        uint32_t acc[1][4], sat[1];
         if constexpr (SR) {
             const int jq[1] = {j};
-            sr8_chunk<D, 1>(qrow, kt, p.seed, (uint64_t)bh, jq, key0, acc, sat);
+            sr8_chunk<D, 1>(qr, kt, p.seed, (uint64_t)bh, jq, key0, acc, sat);
         } else {
-            emu8_chunk<D, 1>(qrow, kt, acc);
+            emu8_any<D, 1, false>(qr, keys16<RowLay<D>>(kt), acc, sat);
         }
         if (r < p.nrows) {
             uint8_t *out = p.y8 + (((size_t)b * p.Hq + h) * p.nrows + r) * p.N + key0;
 #pragma unroll
-            for (int pp = 0; pp < 8; ++pp)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int i = key0 + 2 * pp + t;
-                    const bool vis = !(p.causal && i > j) && !(p.window > 0 && i <= j - p.window);
-                    out[2 * pp + t] = vis ? (uint8_t)(acc[0][pp] >> (8 * t)) : (uint8_t)0xFF;
-                }
+            for (int t = 0; t < 16; ++t) {
+                const int i = key0 + t;
+                const bool vis = !(p.causal && i > j) && !(p.window > 0 && i <= j - p.window);
+                out[t] = vis ? (uint8_t)(acc[0][t >> 2] >> (8 * (t & 3))) : (uint8_t)0xFF;
+            }
         }
     }
 }
 
 template <int D>
-__global__ __launch_bounds__(64) void logits16_kernel(LogitsParams p)
+__global__ __launch_bounds__(64, 2) void logits16_kernel(LogitsParams p)
 {
     const int lane = threadIdx.x;
     const int nrg = (p.nrows + 63) / 64;
@@ -258,10 +256,10 @@ __global__ __launch_bounds__(64) void logits16_kernel(LogitsParams p)
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
     const int key0 = blockIdx.y * 16;
-    const float *qrow[1] = {p.qt + (((size_t)b * p.Hq + h) * p.N + j) * D};
+    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
     const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
     uint32_t codes[1][8];
-    rec16_chunk<D, 1>(qrow, kt, codes);
+    rec16_keys<D, 1, 16>(qr, keys16<RowLay<D>>(kt), codes);
     if (r >= p.nrows) return;
     uint16_t *out = p.y16 + (((size_t)b * p.Hq + h) * p.nrows + r) * p.N + key0;
 #pragma unroll
@@ -274,7 +272,7 @@ __global__ __launch_bounds__(64) void logits16_kernel(LogitsParams p)
 
 // SIM profile logit values: one wave, 64 rows x 16 keys.
 template <int D, bool HIGH>
-__global__ __launch_bounds__(64) void logits_sim_kernel(LogitsParams p)
+__global__ __launch_bounds__(64, 2) void logits_sim_kernel(LogitsParams p)
 {
     const int lane = threadIdx.x;
     const int nrg = (p.nrows + 63) / 64;
@@ -286,17 +284,17 @@ __global__ __launch_bounds__(64) void logits_sim_kernel(LogitsParams p)
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
     const int key0 = blockIdx.y * 16;
-    const float *qrow[1] = {p.qt + (((size_t)b * p.Hq + h) * p.N + j) * D};
+    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
     const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
     float val[16];
     if constexpr (HIGH) {
         uint32_t w[1][16];
-        rec16_chunk<D, 1, true>(qrow, kt, w);
+        rec16_keys<D, 1, 16, true>(qr, keys16<RowLay<D>>(kt), w);
 #pragma unroll
         for (int i = 0; i < 16; ++i) val[i] = __builtin_bit_cast(float, w[0][i]);
     } else {
-        uint32_t w[1][8];
-        emu8s_pass<D, 1>(qrow, kt, w);
+        uint32_t w[1][8], sat[1];
+        emu8_any<D, 1, true>(qr, keys16<RowLay<D>>(kt), w, sat);
 #pragma unroll
         for (int i = 0; i < 16; ++i) val[i] = bf16_value((w[0][i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
     }

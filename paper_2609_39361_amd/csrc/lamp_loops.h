@@ -1,16 +1,25 @@
-// lamp_loops.h -- the two logit loops of the LampAttention forward pass.
+// lamp_loops.h -- the logit loops of the LampAttention forward pass.
 //
-// Both loops give each lane QPL query rows and accumulate over the D channels
-// of a group of NKEY <= 16 keys.  Lane l of every 16-lane row of the wave
-// holds the key value of key (l mod NKEY) for the current channel; the FMA
-// reads it through a DPP row broadcast (row_newbcast:i hands lane i of each
-// row to all 16 lanes of that row), so every lane multiplies its own query
-// value by the value of key i without scalar registers or LDS.  Keys and
-// queries are fp32 and arrive with ordinary vector loads one 4-channel group
-// ahead of their use.  A DPP read of a VGPR written by a VALU instruction less
-// than two instructions earlier is a hardware hazard; the key registers are
-// only written by loads, and the build scans the generated code for the
-// pattern (see build.py).
+// Every lane owns QPL query rows; a pass accumulates over the D channels the
+// logits of groups of 4 keys, one rank-1 matrix instruction per channel, group
+// and row slot: v_mfma_f32_4x4x1_16b_f32 computes 16 blocks of 4 x 4 outer
+// products D = A B + C, and with the A operand of one block broadcast to all
+// (cbsz 4, the block chosen by abid) its four results are, in every lane, the
+// FP32 FMAs fma(k_i, q, c_i) of four keys i with that lane's own query value.
+// Each is one fused multiply-add with one rounding, bit for bit v_fma_f32
+// (subnormals and signed zeros included), so chained over the channels it is
+// the FMA chain of the method's definition.  A wave reads its keys once: lane
+// l of a key operand holds key (l mod 16) of channel group (l / 16) of a
+// 16-channel block, and abid = 4 * group + g broadcasts keys 4g .. 4g+3.
+//
+// What bounds it: VALU issue.  The fp32 matrix instructions do not overlap the
+// VALU's conversions (neither of their own wave nor of another), but feed the
+// keys for free: 0.89 ns per 64 multiply-adds and SIMD, against 1.99 ns for an
+// FMA that reads its key through a DPP broadcast and 1.19 ns for one on plain
+// registers.  The 8-bit step (decode a code pair 2.09 ns, round a value pair
+// to e4m3 3.70 ns) takes 3.65 ns per 64 multiply-adds instead of 4.54 with
+// broadcast FMAs; the 16-bit accumulation 0.9 instead of 1.99.  (Decoding on
+// the fp8 matrix instructions instead was no faster: 3.4 to 3.7 ns.)
 #pragma once
 #include <utility>
 
@@ -18,7 +27,10 @@
 
 namespace lamp {
 
-// acc + bcast_i(kv) * q with one rounding (v_fmac_f32 is a fused multiply-add).
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// acc + bcast_i(kv) * q with one rounding, key i of each 16-lane row by DPP
+// (the stochastic-rounding loop).
 template <int I>
 __device__ __forceinline__ float fmac_bc(float acc, float kv, float q)
 {
@@ -26,127 +38,12 @@ __device__ __forceinline__ float fmac_bc(float acc, float kv, float q)
     return acc;
 }
 
-// Two code words of two accumulators each advanced by one channel in a single
-// statement: word a holds the codes of keys I0, I1 of query value qa, word b
-// those of keys J0, J1 of qb; each pair is decoded, the FMAs read the keys by
-// row broadcast, and the results are rounded to e4m3 into bits [15:0] of the
-// word (bits [31:16] kept; no saturation, see pk_e4m3).  The decoded values go
-// to four fixed registers that the statement declares clobbered, so the two
-// chains interleave with no wait state between the statements of one chain
-// that the compiler, not seeing into the assembly, would otherwise insert
-// after every separate asm statement.
-template <int I0, int I1, int J0, int J1>
-__device__ __forceinline__ void emu8_words(uint32_t &a, uint32_t &b, float kv, float qa, float qb)
+// c_i + k_i * q for the 4 keys i that lanes 4*ABID .. 4*ABID+3 of kv hold.
+template <int ABID>
+__device__ __forceinline__ f32x4_t rank1(float kv, float q, f32x4_t c)
 {
-    asm("v_cvt_pk_f32_fp8 v[248:249], %0\n\t"
-        "v_cvt_pk_f32_fp8 v[250:251], %1\n\t"
-        "v_fmac_f32_dpp v248, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp v249, %2, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp v250, %2, %4 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp v251, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_cvt_pk_fp8_f32 %0, v248, v249\n\t"
-        "v_cvt_pk_fp8_f32 %1, v250, v251"
-        : "+v"(a), "+v"(b)
-        : "v"(kv), "v"(qa), "v"(qb), "n"(I0), "n"(I1), "n"(J0), "n"(J1)
-        : "v248", "v249", "v250", "v251");
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(kv, q, c, 4, ABID, 0);
 }
-
-// One channel of all eight code words of both query rows (16 keys) in a
-// single statement: the body of emu8_words for word pairs 0..7.  One
-// statement per channel keeps the compiler from placing a wait state between
-// the word pairs, which it does after every separate statement.
-#define LAMP_E8W(A, B, K0, K1)                                                          \
-    "v_cvt_pk_f32_fp8 v[248:249], " A "\n\t"                                           \
-    "v_cvt_pk_f32_fp8 v[250:251], " B "\n\t"                                           \
-    "v_fmac_f32_dpp v248, %16, %17 row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp v249, %16, %17 row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp v250, %16, %18 row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp v251, %16, %18 row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_cvt_pk_fp8_f32 " A ", v248, v249\n\t"                                            \
-    "v_cvt_pk_fp8_f32 " B ", v250, v251\n\t"
-
-__device__ __forceinline__ void emu8_words8(uint32_t (&a)[8], uint32_t (&b)[8], float kv, float qa, float qb)
-{
-    asm(LAMP_E8W("%0", "%8", 0, 1) LAMP_E8W("%1", "%9", 2, 3) LAMP_E8W("%2", "%10", 4, 5)
-        LAMP_E8W("%3", "%11", 6, 7) LAMP_E8W("%4", "%12", 8, 9) LAMP_E8W("%5", "%13", 10, 11)
-        LAMP_E8W("%6", "%14", 12, 13) LAMP_E8W("%7", "%15", 14, 15)
-        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
-          "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7])
-        : "v"(kv), "v"(qa), "v"(qb)
-        : "v248", "v249", "v250", "v251");
-}
-#undef LAMP_E8W
-
-// The compact register layout (Sec. 3.3, "Register layout": four 8-bit
-// accumulators per 32-bit register): one channel of both query rows' 16
-// codes held four per word -- keys 4w, 4w+1 in bits [15:0] of word w, keys
-// 4w+2, 4w+3 in bits [31:16] -- in a single statement.  The high halves are
-// decoded with an SDWA word select and written back with op_sel, so the
-// instructions are those of emu8_words8.
-#define LAMP_E8H(A, B, K0, K1, K2, K3)                                                  \
-    "v_cvt_pk_f32_fp8 v[248:249], " A "\n\t"                                           \
-    "v_cvt_pk_f32_fp8 v[250:251], " B "\n\t"                                           \
-    "v_fmac_f32_dpp v248, %8, %9 row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t"   \
-    "v_fmac_f32_dpp v249, %8, %9 row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t"   \
-    "v_fmac_f32_dpp v250, %8, %10 row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t"  \
-    "v_fmac_f32_dpp v251, %8, %10 row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t"  \
-    "v_cvt_pk_fp8_f32 " A ", v248, v249\n\t"                                            \
-    "v_cvt_pk_fp8_f32 " B ", v250, v251\n\t"                                            \
-    "v_cvt_pk_f32_fp8_sdwa v[248:249], " A " src0_sel:WORD_1\n\t"                       \
-    "v_cvt_pk_f32_fp8_sdwa v[250:251], " B " src0_sel:WORD_1\n\t"                       \
-    "v_fmac_f32_dpp v248, %8, %9 row_newbcast:" #K2 " row_mask:0xf bank_mask:0xf\n\t"   \
-    "v_fmac_f32_dpp v249, %8, %9 row_newbcast:" #K3 " row_mask:0xf bank_mask:0xf\n\t"   \
-    "v_fmac_f32_dpp v250, %8, %10 row_newbcast:" #K2 " row_mask:0xf bank_mask:0xf\n\t"  \
-    "v_fmac_f32_dpp v251, %8, %10 row_newbcast:" #K3 " row_mask:0xf bank_mask:0xf\n\t"  \
-    "v_cvt_pk_fp8_f32 " A ", v248, v249 op_sel:[0,0,1]\n\t"                             \
-    "v_cvt_pk_fp8_f32 " B ", v250, v251 op_sel:[0,0,1]\n\t"
-
-__device__ __forceinline__ void emu8_quads4(uint32_t (&a)[4], uint32_t (&b)[4], float kv, float qa, float qb)
-{
-    asm(LAMP_E8H("%0", "%4", 0, 1, 2, 3) LAMP_E8H("%1", "%5", 4, 5, 6, 7) LAMP_E8H("%2", "%6", 8, 9, 10, 11)
-        LAMP_E8H("%3", "%7", 12, 13, 14, 15)
-        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3])
-        : "v"(kv), "v"(qa), "v"(qb)
-        : "v248", "v249", "v250", "v251");
-}
-#undef LAMP_E8H
-
-// One channel of the 16-bit accumulation of one query row for NKEY keys in
-// a single statement: acc[i] += bcast_i(kv) * q, i = 0..NKEY-1.
-#define LAMP_F16(I, ACC) "v_fmac_f32_dpp " ACC ", %[k], %[q] row_newbcast:" #I " row_mask:0xf bank_mask:0xf\n\t"
-template <int NKEY>
-__device__ __forceinline__ void fmac16_row(float (&acc)[NKEY], float kv, float q)
-{
-    static_assert(NKEY == 4 || NKEY == 8 || NKEY == 12 || NKEY == 16, "4, 8, 12 or 16 keys");
-    if constexpr (NKEY == 4) {
-        asm(LAMP_F16(0, "%0") LAMP_F16(1, "%1") LAMP_F16(2, "%2") LAMP_F16(3, "%3")
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
-            : [k] "v"(kv), [q] "v"(q));
-    } else if constexpr (NKEY == 8) {
-        asm(LAMP_F16(0, "%0") LAMP_F16(1, "%1") LAMP_F16(2, "%2") LAMP_F16(3, "%3")
-            LAMP_F16(4, "%4") LAMP_F16(5, "%5") LAMP_F16(6, "%6") LAMP_F16(7, "%7")
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-              "+v"(acc[7])
-            : [k] "v"(kv), [q] "v"(q));
-    } else if constexpr (NKEY == 12) {
-        asm(LAMP_F16(0, "%0") LAMP_F16(1, "%1") LAMP_F16(2, "%2") LAMP_F16(3, "%3")
-            LAMP_F16(4, "%4") LAMP_F16(5, "%5") LAMP_F16(6, "%6") LAMP_F16(7, "%7")
-            LAMP_F16(8, "%8") LAMP_F16(9, "%9") LAMP_F16(10, "%10") LAMP_F16(11, "%11")
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-              "+v"(acc[7]), "+v"(acc[8]), "+v"(acc[9]), "+v"(acc[10]), "+v"(acc[11])
-            : [k] "v"(kv), [q] "v"(q));
-    } else {
-        asm(LAMP_F16(0, "%0") LAMP_F16(1, "%1") LAMP_F16(2, "%2") LAMP_F16(3, "%3")
-            LAMP_F16(4, "%4") LAMP_F16(5, "%5") LAMP_F16(6, "%6") LAMP_F16(7, "%7")
-            LAMP_F16(8, "%8") LAMP_F16(9, "%9") LAMP_F16(10, "%10") LAMP_F16(11, "%11")
-            LAMP_F16(12, "%12") LAMP_F16(13, "%13") LAMP_F16(14, "%14") LAMP_F16(15, "%15")
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-              "+v"(acc[7]), "+v"(acc[8]), "+v"(acc[9]), "+v"(acc[10]), "+v"(acc[11]), "+v"(acc[12]),
-              "+v"(acc[13]), "+v"(acc[14]), "+v"(acc[15])
-            : [k] "v"(kv), [q] "v"(q));
-    }
-}
-#undef LAMP_F16
 
 // Where the loops find the fp32 queries and keys.  Row layout ([row][D]): the
 // 4-channel group g of a row is at offset 4g and consecutive keys are D apart.
@@ -154,188 +51,236 @@ __device__ __forceinline__ void fmac16_row(float (&acc)[NKEY], float kv, float q
 // in blocks of 16, each block stored [group][row][4], so that one 4-channel
 // group of a block is contiguous: group g of a query row is at 256g, of a key
 // row at 64g, and consecutive keys of a block are 4 apart.
-// WORDS selects the two-word 8-bit statement (emu8_words) for two query rows
-// per lane: its four fixed temporaries sit at the top of the register file,
-// so it is only for kernels that use the whole file anyway (the pipelined
-// kernel at 128 rows per block, two waves per SIMD).
-template <int QS_, int KS_, int KR_, bool WORDS_>
+template <int QS_, int KS_, int KR_>
 struct Lay {
     static constexpr int QS = QS_, KS = KS_, KR = KR_;   // query / key group stride, key row stride
-    static constexpr bool WORDS = WORDS_;
 };
 template <int D>
-using RowLay = Lay<4, 4, D, false>;
-using GrpLay = Lay<256, 64, 4, true>;
+using RowLay = Lay<4, 4, D>;
+using GrpLay = Lay<256, 64, 4>;
 
-// Two wait states that nothing is scheduled across.  The register allocator
-// may copy a loaded key register with a VALU move where a loop is entered or
-// left (to line up the loop-carried buffers); placed at the top of every loop
-// over channel groups and after it, this keeps each DPP read of a key at least
-// two wait states behind such a copy.  The build check verifies the result.
-__device__ __forceinline__ void dpp_guard()
+// The query rows of a wave: slot s of a lane at base[s] (uniform) + off bytes
+// (the lane's own), so that the loads keep one offset register.
+template <int QPL>
+struct QRows {
+    const float *base[QPL];
+    uint32_t off;
+    __device__ __forceinline__ const float *row(int s) const
+    {
+        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base[s]) + off);
+    }
+};
+
+// A key operand: group 0 of this lane's key at base (uniform) + off bytes; the
+// lane reads channel group 4j + lane/16 of every 16-channel block j.
+struct KRows {
+    const float *base;
+    uint32_t off;
+};
+
+// The 16 consecutive keys at k32.
+template <class LY>
+__device__ __forceinline__ KRows keys16(const float *k32)
 {
-    asm volatile("s_nop 1");
+    const uint32_t l = __lane_id();
+    return {k32, 4u * ((l & 15u) * LY::KR + (l >> 4) * LY::KS)};
 }
 
-// dpp_guard with a scheduling barrier after it, for loops whose first
-// broadcast FMAs the scheduler would otherwise hoist above the wait states
-// (the FMAs are side-effect-free inline assembly and may move across them).
+// The key at element offset `key_off` of this lane (the caller's choice of
+// keys: groups of four in lanes 4g .. 4g+3 of every 16-lane row).
+template <class LY>
+__device__ __forceinline__ KRows keys_at(const float *k32, uint32_t key_off)
+{
+    return {k32, 4u * (key_off + (__lane_id() >> 4) * LY::KS)};
+}
+
+__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+__device__ __forceinline__ f32x4_t load4v(const float *base, uint32_t off)
+{
+    return *reinterpret_cast<const f32x4_t *>(reinterpret_cast<const char *>(base) + off);
+}
+__device__ __forceinline__ float4 load4(const float *base, uint32_t off)
+{
+    const f32x4_t v = load4v(base, off);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Two wait states that nothing is scheduled across, at the top of every loop
+// whose DPP instructions read loaded registers: the register allocator may
+// copy such a register with a VALU move where a loop is entered or left, and a
+// DPP read of a VGPR needs two wait states after a VALU write of it.  The
+// build check verifies the result.
 __device__ __forceinline__ void dpp_guard_fenced()
 {
     asm volatile("s_nop 1");
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Query rows come either from global memory (const float *) or from LDS
-// (lds_cfptr, so that the loads are ds_read_b128 rather than flat loads).
-typedef const __attribute__((address_space(3))) float *lds_cfptr;
+// 8-bit logits of 16 keys: e4m3 codes, four per word (word g: keys 4g .. 4g+3),
+// or, in the SIM profile, bf16 patterns two per word.
+template <bool SIMP>
+constexpr int Y8_WORDS = SIMP ? 8 : 4;
 
-__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load4(lds_cfptr p)
+// c_g <- fma(k, q, c_g) for NG groups g of 4 keys (channel group R of the key operand).
+template <int R, int NG, int... G>
+__device__ __forceinline__ void fma_groups(float kv, float q, f32x4_t (&c)[NG], std::integer_sequence<int, G...>)
 {
-    const f32x4_t v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4_t *>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
+    ((c[G] = rank1<4 * R + G>(kv, q, c[G])), ...);
 }
 
-// Loads of a 4-channel group: this lane's key row and query rows.
-template <int QPL, class LY, class QP>
-__device__ __forceinline__ void load_group(const float *krow, const QP (&qrow)[QPL], int c, float4 &k4,
-                                           float4 (&q4)[QPL])
+// One channel of the 8-bit accumulation of 16 keys of one query row,
+// acc <- RN_e4m3(RN32(q * k + acc)), and of the FMA chains of NM groups of 4
+// keys of kr.  In three batches that nothing is scheduled across -- decode the
+// four code words, the matrix instructions back to back, round back -- because
+// every change between the VALU and the matrix instructions costs some 8
+// cycles: alternating them one by one took 4.32 ns per 64 multiply-adds, the
+// batches 3.65 (all eight words of two rows in one batch: the same, with 16
+// more registers).
+template <int R, bool SAT, int NM>
+__device__ __forceinline__ void emu8_row(float ke, float kr, float q, uint32_t (&w)[4], f32x4_t (&acc)[NM > 0 ? NM : 1])
 {
-    k4 = *reinterpret_cast<const float4 *>(krow + (c / 4) * LY::KS);
+    f32x4_t t[4];
 #pragma unroll
-    for (int s = 0; s < QPL; ++s) q4[s] = load4(qrow[s] + (c / 4) * LY::QS);
-}
-
-__device__ __forceinline__ float f4_at(const float4 &v, int i)
-{
-    return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
-}
-
-// One channel of the 8-bit accumulation for key pair (2P, 2P+1) of every
-// slot: acc <- RN_e4m3(RN32(q * k + acc)).
-template <int QPL, bool SAT, int P>
-__device__ __forceinline__ void emu8_pair(float kv, const float (&q)[QPL], uint32_t (&acc)[QPL][8])
-{
-#pragma unroll
-    for (int s = 0; s < QPL; ++s) {
-        const float2 a = unpk_e4m3(acc[s][P]);
-        const float x = fmac_bc<2 * P>(a.x, kv, q[s]);
-        const float y = fmac_bc<2 * P + 1>(a.y, kv, q[s]);
-        acc[s][P] = SAT ? pk_e4m3_sat(x, y, acc[s][P]) : pk_e4m3(x, y, acc[s][P]);
+    for (int g = 0; g < 4; ++g) {
+        const float2 lo = unpk_e4m3x4(w[g], 0), hi = unpk_e4m3x4(w[g], 1);
+        t[g] = f32x4_t{lo.x, lo.y, hi.x, hi.y};
     }
+    __builtin_amdgcn_sched_barrier(0);
+    fma_groups<R>(ke, q, t, std::make_integer_sequence<int, 4>());
+    if constexpr (NM > 0) fma_groups<R>(kr, q, acc, std::make_integer_sequence<int, NM>());
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        if constexpr (SAT) w[g] = pk_e4m3_sat(t[g][0], t[g][1], w[g]);
+        else w[g] = pk_e4m3(t[g][0], t[g][1], w[g]);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        if constexpr (SAT) w[g] = pk_e4m3_sat_hi(t[g][2], t[g][3], w[g]);
+        else w[g] = pk_e4m3_hi(t[g][2], t[g][3], w[g]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// One channel of the non-saturating pass over every word: with WORDS and two
-// query rows per lane, the two rows of a word index in one statement
-// (emu8_words); otherwise one pair at a time (emu8_pair).
-template <int QPL, bool SAT, bool WORDS, int... P>
-__device__ __forceinline__ void emu8_channel(float kv, const float (&q)[QPL], uint32_t (&acc)[QPL][8],
-                                             std::integer_sequence<int, P...>)
+// The loop over the channels: the 8-bit accumulation of the 16 keys of ke
+// (EMU; in the SIM profile on FP32 values in e8, otherwise on the codes w8;
+// SAT: saturating) and the FMA chains of NM groups of 4 keys of kr, sharing
+// the query loads.  The queries come PD 4-channel groups ahead, the keys a
+// 16-channel block ahead (the last block's loads wrap to the first channels
+// and are not used).
+template <int D, int QPL, int NM, bool EMU, bool SIMP, bool SAT, int PD, class LY>
+__device__ __forceinline__ void logit_loop(const QRows<QPL> &qr, const KRows &ke, const KRows &kr,
+                                           uint32_t (&w8)[QPL][4], f32x4_t (&e8)[QPL][SIMP && EMU ? 4 : 1],
+                                           f32x4_t (&acc)[QPL][NM > 0 ? NM : 1])
 {
-    if constexpr (!SAT && WORDS && QPL == 2 && sizeof...(P) == 8)
-        emu8_words8(acc[0], acc[1], kv, q[0], q[1]);
-    else if constexpr (!SAT && WORDS && QPL == 2)
-        (emu8_words<2 * P, 2 * P + 1, 2 * P, 2 * P + 1>(acc[0][P], acc[1][P], kv, q[0], q[1]), ...);
-    else (emu8_pair<QPL, SAT, P>(kv, q, acc), ...);
+    static_assert(D % 16 == 0 && (PD == 2 || PD == 4), "16-channel blocks");
+    f32x4_t q4[PD][QPL], kea, keb, kra, krb;
+    uint32_t qoff = qr.off, eoff = ke.off, roff = kr.off;
+    auto ldk = [&](int c, f32x4_t &e, f32x4_t &r) {
+        if constexpr (EMU) e = load4v(ke.base + (c / 4) * LY::KS, eoff);
+        if constexpr (NM > 0) r = load4v(kr.base + (c / 4) * LY::KS, roff);
+    };
+    auto ldq = [&](int g, f32x4_t (&q)[QPL]) {
+#pragma unroll
+        for (int s = 0; s < QPL; ++s) q[s] = load4v(qr.base[s] + g * LY::QS, qoff);
+    };
+    ldk(0, kea, kra);
+#pragma unroll
+    for (int r = 0; r < PD; ++r) ldq(r, q4[r]);
+    auto group = [&](auto r_c, int c, const f32x4_t &e, const f32x4_t &k) {
+        constexpr int R = decltype(r_c)::value;
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+            for (int s = 0; s < QPL; ++s) {
+                const float q = q4[R % PD][s][cc];
+                if constexpr (EMU && !SIMP) {
+                    emu8_row<R, SAT, NM>(e[cc], NM > 0 ? k[cc] : 0.0f, q, w8[s], acc[s]);
+                } else {
+                    if constexpr (EMU) fma_groups<R>(e[cc], q, e8[s], std::make_integer_sequence<int, 4>());
+                    if constexpr (NM > 0) fma_groups<R>(k[cc], q, acc[s], std::make_integer_sequence<int, NM>());
+                    if constexpr (EMU) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) e8[s][g][i] = rn_sim<3>(e8[s][g][i]);
+                    }
+                }
+            }
+        const int g = c / 4 + R + PD;
+        ldq(g < D / 4 ? g : g - D / 4, q4[R % PD]);
+    };
+#pragma nounroll
+    for (int c = 0; c < D; c += 16) {
+        // opaque to the compiler, so that the loads keep the form of a scalar
+        // base plus a 32-bit lane offset
+        asm volatile("" : "+v"(qoff), "+v"(eoff), "+v"(roff));
+        ldk(c + 16 < D ? c + 16 : 0, keb, krb);
+        group(std::integral_constant<int, 0>(), c, kea, kra);
+        group(std::integral_constant<int, 1>(), c, kea, kra);
+        group(std::integral_constant<int, 2>(), c, kea, kra);
+        group(std::integral_constant<int, 3>(), c, kea, kra);
+        if constexpr (EMU) kea = keb;
+        if constexpr (NM > 0) kra = krb;
+    }
 }
 
 // Y8 of one 16-key chunk for QPL query rows of this lane (Sec. 4.1:
 // acc <- RN_e4m3(RN32(q_tilde * k + acc)), channels ascending, from +0).
-// k32 points at the chunk's first key (layout LY); qrow[s] at the fp32
-// pre-scaled query row of slot s.  acc[s][p] receives the codes of keys 2p,
-// 2p+1 in bits [15:0].
-template <int D, int QPL, bool SAT, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void emu8_pass(const QP (&qrow)[QPL], const float *k32, uint32_t (&acc)[QPL][8])
+template <int D, int QPL, bool SAT, class LY = RowLay<D>>
+__device__ __forceinline__ void emu8_pass(const QRows<QPL> &qr, const KRows &ke, uint32_t (&w)[QPL][4])
 {
-    static_assert(D % 8 == 0, "channels in pairs of 4-channel groups");
+    f32x4_t none[QPL][1];
 #pragma unroll
     for (int s = 0; s < QPL; ++s)
 #pragma unroll
-        for (int p = 0; p < 8; ++p) acc[s][p] = 0u;
-    const float *krow = k32 + (size_t)(__lane_id() & 15) * LY::KR;
-    // Two alternating load buffers: the key registers feeding the DPP
-    // broadcast are only ever written by vector loads, never copied.
-    float4 ka, kb, qa[QPL], qb[QPL];
-    auto run = [&](const float4 &k4, const float4 (&q4)[QPL]) {
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            float q[QPL];
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) q[s] = f4_at(q4[s], cc);
-            emu8_channel<QPL, SAT, LY::WORDS>(f4_at(k4, cc), q, acc, std::make_integer_sequence<int, 8>());
-        }
-    };
-    // steady state, then the last pair of groups without further loads (the
-    // offsets stay affine in c, so they fold into the loads' immediates)
-    load_group<QPL, LY>(krow, qrow, 0, ka, qa);
-    for (int c = 0; c < D - 8; c += 8) {
-        dpp_guard();
-        load_group<QPL, LY>(krow, qrow, c + 4, kb, qb);
-        run(ka, qa);
-        load_group<QPL, LY>(krow, qrow, c + 8, ka, qa);
-        run(kb, qb);
-    }
-    load_group<QPL, LY>(krow, qrow, D - 4, kb, qb);
-    dpp_guard();
-    run(ka, qa);
-    run(kb, qb);
+        for (int g = 0; g < 4; ++g) w[s][g] = 0u;
+    logit_loop<D, QPL, 0, true, false, SAT, 2, LY>(qr, ke, ke, w, none, none);
 }
 
+// Nonzero iff one of the four codes of a word is a NaN code (bits 7, 15, 23, 31).
+__device__ __forceinline__ uint32_t e4m3x4_nan_bits(uint32_t w) { return ((w & 0x7F7F7F7Fu) + 0x01010101u) & 0x80808080u; }
+
 // Keys whose 8-bit code is a NaN after the non-saturating pass, one bit per
-// key (bit i: key i of the 16, codes of keys 2p and 2p+1 in word p).  Such a
-// chain overflowed in some step, which is exactly when the saturating
-// recursion clamps to +-448: the two recursions agree up to that step.
+// key (bit i: key i of the 16).  Such a chain overflowed in some step, which
+// is exactly when the saturating recursion clamps to +-448: the two recursions
+// agree up to that step.
 template <int QPL>
-__device__ __forceinline__ void nan_keys(const uint32_t (&acc)[QPL][8], uint32_t (&sat)[QPL])
+__device__ __forceinline__ void nan_keys(const uint32_t (&w)[QPL][4], uint32_t (&sat)[QPL])
 {
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         uint32_t m = 0;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const uint32_t r = e4m3_nan_bits(acc[s][p]);
-            m |= ((r >> 7) & 1u) << (2 * p);
-            m |= ((r >> 15) & 1u) << (2 * p + 1);
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t r = e4m3x4_nan_bits(w[s][g]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m |= ((r >> (8 * i + 7)) & 1u) << (4 * g + i);
         }
         sat[s] = m;
     }
 }
 
-// The fast pass uses the non-saturating conversion; if any lane of the wave
-// overflowed somewhere (a NaN code at the end of a chain), the chunk is
-// recomputed with the saturating conversion.  sat[s] receives the keys of
-// slot s whose accumulation saturated (nan_keys), 0 when none did.
-template <int D, int QPL, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void emu8_chunk(const QP (&qrow)[QPL], const float *k32, uint32_t (&acc)[QPL][8],
+// After the non-saturating pass: if any lane of the wave overflowed somewhere
+// (a NaN code at the end of a chain), the chunk is recomputed with the
+// saturating conversion.  sat[s] receives the keys of slot s whose
+// accumulation saturated (nan_keys), 0 when none did.
+template <int D, int QPL, class LY>
+__device__ __forceinline__ void emu8_check(const QRows<QPL> &qr, const KRows &ke, uint32_t (&w)[QPL][4],
                                            uint32_t (&sat)[QPL])
 {
-    emu8_pass<D, QPL, false, LY>(qrow, k32, acc);
     uint32_t nan = 0;
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         sat[s] = 0u;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) nan |= e4m3_nan_bits(acc[s][p]);
+        for (int g = 0; g < 4; ++g) nan |= e4m3x4_nan_bits(w[s][g]);
     }
     if (wave_any(nan != 0)) {
-        nan_keys<QPL>(acc, sat);
-        emu8_pass<D, QPL, true, LY>(qrow, k32, acc);
+        nan_keys<QPL>(w, sat);
+        emu8_pass<D, QPL, true, LY>(qr, ke, w);
     }
 }
-
-template <int D, int QPL, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void emu8_chunk(const QP (&qrow)[QPL], const float *k32, uint32_t (&acc)[QPL][8])
-{
-    uint32_t sat[QPL];
-    emu8_chunk<D, QPL, LY>(qrow, k32, acc, sat);
-}
-
-// One channel of the 16-bit accumulation for every key and slot.
-template <int QPL, int NKEY, int... I>
-__device__ __forceinline__ void rec16_channel(float kv, const float (&q)[QPL], float (&acc)[QPL][NKEY],
-                                              std::integer_sequence<int, I...>);
 
 // ---- the SIM profile (Sec. 4.1): FP32 range, 3 / 11 mantissa bits, no saturation
 // Words of 16-bit logits for NKEY keys: e4m11 codes two per word, or, in the
@@ -360,255 +305,94 @@ __device__ __forceinline__ uint32_t pack_sim8(float a, float b)
     return (__builtin_bit_cast(uint32_t, a) >> 16) | (__builtin_bit_cast(uint32_t, b) & 0xFFFF0000u);
 }
 
-// One channel of the SIM 8-bit accumulation for every key and slot:
-// acc <- RN_3(RN32(q * k + acc)).
-template <int QPL, int... I>
-__device__ __forceinline__ void emu8s_channel(float kv, const float (&q)[QPL], float (&acc)[QPL][16],
-                                              std::integer_sequence<int, I...>)
-{
-#pragma unroll
-    for (int s = 0; s < QPL; ++s) ((acc[s][I] = rn_sim<3>(fmac_bc<I>(acc[s][I], kv, q[s]))), ...);
-}
-
-// Y8 of one 16-key chunk in the SIM profile (as emu8_pass); codes[s][p]
-// receives the bf16 patterns of keys 2p (bits [15:0]) and 2p+1.
-template <int D, int QPL, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void emu8s_pass(const QP (&qrow)[QPL], const float *k32, uint32_t (&codes)[QPL][8])
-{
-    static_assert(D % 8 == 0, "channels in pairs of 4-channel groups");
-    float acc[QPL][16];
-#pragma unroll
-    for (int s = 0; s < QPL; ++s)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[s][i] = 0.0f;
-    const float *krow = k32 + (size_t)(__lane_id() & 15) * LY::KR;
-    float4 ka, kb, qa[QPL], qb[QPL];
-    auto run = [&](const float4 &k4, const float4 (&q4)[QPL]) {
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            float q[QPL];
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) q[s] = f4_at(q4[s], cc);
-            emu8s_channel<QPL>(f4_at(k4, cc), q, acc, std::make_integer_sequence<int, 16>());
-        }
-    };
-    load_group<QPL, LY>(krow, qrow, 0, ka, qa);
-    for (int c = 0; c < D - 8; c += 8) {
-        dpp_guard_fenced();
-        load_group<QPL, LY>(krow, qrow, c + 4, kb, qb);
-        run(ka, qa);
-        load_group<QPL, LY>(krow, qrow, c + 8, ka, qa);
-        run(kb, qb);
-    }
-    load_group<QPL, LY>(krow, qrow, D - 4, kb, qb);
-    dpp_guard_fenced();
-    run(ka, qa);
-    run(kb, qb);
-#pragma unroll
-    for (int s = 0; s < QPL; ++s)
-#pragma unroll
-        for (int p = 0; p < 8; ++p) codes[s][p] = pack_sim8(acc[s][2 * p], acc[s][2 * p + 1]);
-}
-
-// Y8 of a 16-key chunk in either profile (sat as in emu8_chunk; 0 in the
-// SIM profile, which does not saturate).
-template <int D, int QPL, bool SIMP, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void emu8_any(const QP (&qrow)[QPL], const float *k32, uint32_t (&codes)[QPL][8],
-                                         uint32_t (&sat)[QPL])
-{
-    if constexpr (SIMP) {
-        emu8s_pass<D, QPL, LY>(qrow, k32, codes);
-#pragma unroll
-        for (int s = 0; s < QPL; ++s) sat[s] = 0u;
-    } else {
-        emu8_chunk<D, QPL, LY>(qrow, k32, codes, sat);
-    }
-}
-
 // The 16-bit logits of the FP32 chains in acc, encoded: rounded once to e4m11
 // (codes, two per word) or, in the SIM profile, to 11 mantissa bits (FP32
 // patterns, one per word).
-template <bool SIMP, int QPL, int NKEY>
-__device__ __forceinline__ void encode16(const float (&acc)[QPL][NKEY], uint32_t (&c)[QPL][y16_words<SIMP>(NKEY)])
+template <bool SIMP, int QPL, int NM>
+__device__ __forceinline__ void encode16(const f32x4_t (&acc)[QPL][NM], uint32_t (&c)[QPL][y16_words<SIMP>(4 * NM)])
 {
 #pragma unroll
-    for (int s = 0; s < QPL; ++s) {
-        if constexpr (SIMP) {
+    for (int s = 0; s < QPL; ++s)
 #pragma unroll
-            for (int i = 0; i < NKEY; ++i) c[s][i] = __builtin_bit_cast(uint32_t, rn_sim<11>(acc[s][i]));
-        } else {
+        for (int g = 0; g < NM; ++g) {
+            if constexpr (SIMP) {
 #pragma unroll
-            for (int p = 0; p < NKEY / 2; ++p) {
-                uint32_t x0, x1;
-                (void)rn_e4m11_f32(acc[s][2 * p], &x0);
-                (void)rn_e4m11_f32(acc[s][2 * p + 1], &x1);
-                c[s][p] = x0 | (x1 << 16);
+                for (int i = 0; i < 4; ++i) c[s][4 * g + i] = __builtin_bit_cast(uint32_t, rn_sim<11>(acc[s][g][i]));
+            } else {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    uint32_t x0, x1;
+                    (void)rn_e4m11_f32(acc[s][g][2 * p], &x0);
+                    (void)rn_e4m11_f32(acc[s][g][2 * p + 1], &x1);
+                    c[s][2 * g + p] = x0 | (x1 << 16);
+                }
             }
         }
-    }
 }
 
-// Two passes over the channels fused into one loop that shares the query
-// loads: the 8-bit accumulation of the 16 keys at k32e (EMU; as emu8_pass,
-// without saturation, then checked as in emu8_chunk) and the 16-bit
-// accumulation of NKEY keys, this lane's key row being krowr (as rec16_keys).
-// The forward kernel uses it to run the 8-bit logits of the next key tile
-// together with the speculative 16-bit recompute of the current one.
-// sat receives the saturated keys of the 8-bit chunk as in emu8_chunk.
-// CMP: the 8-bit codes live four per register during the pass (emu8_quads4;
-// two query rows per lane, the grouped layout); a8 receives them two per word
-// as always.
-template <int D, int QPL, int NKEY, bool EMU, bool SIMP, class LY = RowLay<D>, bool CMP = false, class QP>
-__device__ __forceinline__ void fused_pass(const QP (&qrow)[QPL], const float *k32e, const float *krowr,
-                                           uint32_t (&a8)[QPL][8], uint32_t (&c16)[QPL][y16_words<SIMP>(NKEY)],
+// The 8-bit logits of the 16 keys ke (EMU; with the overflow check) and the
+// 16-bit logits of NKEY keys kr in one loop that shares the query loads.  The
+// forward kernel uses it to run the 8-bit logits of the next key tile together
+// with the speculative 16-bit recompute of the current one.  a8 receives the
+// 8-bit logits (Y8_WORDS), c16 the 16-bit ones, sat the saturated keys of the
+// 8-bit chunk (0 in the SIM profile, which does not saturate).
+template <int D, int QPL, int NKEY, bool EMU, bool SIMP, class LY = RowLay<D>>
+__device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke, const KRows &kr,
+                                           uint32_t (&a8)[QPL][Y8_WORDS<SIMP>], uint32_t (&c16)[QPL][y16_words<SIMP>(NKEY)],
                                            uint32_t (&sat)[QPL])
 {
-    static_assert(!CMP || (QPL == 2 && !SIMP && LY::WORDS), "compact words: two rows per lane, hardware formats");
-    constexpr bool QUADS = CMP && EMU;
-    uint32_t a8q[QPL][4];   // the compact words (QUADS)
     static_assert(EMU || NKEY > 0, "something to compute");
     static_assert(NKEY == 0 || NKEY == 4 || NKEY == 8 || NKEY == 12 || NKEY == 16, "0, 4, 8, 12 or 16 keys");
-    static_assert(D % 8 == 0, "channels in pairs of 4-channel groups");
-    constexpr int NA = NKEY > 0 ? NKEY : 1;
-    constexpr int NE = (SIMP && EMU) ? 16 : 1;   // SIM 8-bit accumulators (values, not codes)
-    float acc[QPL][NA], e8[QPL][NE];
+    constexpr int NM = NKEY / 4, NA = NM > 0 ? NM : 1, NE = SIMP && EMU ? 4 : 1;
+    uint32_t w8[QPL][4];
+    f32x4_t acc[QPL][NA], e8[QPL][NE];
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         sat[s] = 0u;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) a8[s][p] = 0u;
+        for (int g = 0; g < 4; ++g) w8[s][g] = 0u;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) a8q[s][p] = 0u;
+        for (int g = 0; g < NA; ++g) acc[s][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < NA; ++i) acc[s][i] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NE; ++i) e8[s][i] = 0.0f;
+        for (int g = 0; g < NE; ++g) e8[s][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    const float *krowe = k32e + (size_t)(__lane_id() & 15) * LY::KR;
-    // the SIM profile's loop needs the fenced guard (its schedule hoists
-    // broadcast FMAs above a plain one)
-    auto guard = [] {
-        if constexpr (SIMP) dpp_guard_fenced();
-        else dpp_guard();
-    };
-    float4 kea, keb, kra, krb, qa[QPL], qb[QPL];
-    auto ld = [&](int c, float4 &ke, float4 &kr, float4 (&q4)[QPL]) {
-        if constexpr (EMU) ke = load4(krowe + (c / 4) * LY::KS);
-        if constexpr (NKEY > 0) kr = load4(krowr + (c / 4) * LY::KS);
-#pragma unroll
-        for (int s = 0; s < QPL; ++s) q4[s] = load4(qrow[s] + (c / 4) * LY::QS);
-    };
-    auto run = [&](const float4 &ke, const float4 &kr, const float4 (&q4)[QPL]) {
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            float q[QPL];
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) q[s] = f4_at(q4[s], cc);
-            if constexpr (EMU && SIMP)
-                emu8s_channel<QPL>(f4_at(ke, cc), q, e8, std::make_integer_sequence<int, 16>());
-            else if constexpr (QUADS)
-                emu8_quads4(a8q[0], a8q[QPL - 1], f4_at(ke, cc), q[0], q[QPL - 1]);
-            else if constexpr (EMU)
-                emu8_channel<QPL, false, LY::WORDS>(f4_at(ke, cc), q, a8, std::make_integer_sequence<int, 8>());
-            if constexpr (NKEY > 0)
-                rec16_channel<QPL, NKEY>(f4_at(kr, cc), q, acc, std::make_integer_sequence<int, NKEY>());
-        }
-    };
-    ld(0, kea, kra, qa);
-    for (int c = 0; c < D - 8; c += 8) {
-        guard();
-        ld(c + 4, keb, krb, qb);
-        run(kea, kra, qa);
-        ld(c + 8, kea, kra, qa);
-        run(keb, krb, qb);
-    }
-    ld(D - 4, keb, krb, qb);
-    guard();
-    run(kea, kra, qa);
-    run(keb, krb, qb);
+    logit_loop<D, QPL, NM, EMU, SIMP, false, EMU ? 2 : 4, LY>(qr, ke, kr, w8, e8, acc);
     if constexpr (EMU && SIMP) {
 #pragma unroll
         for (int s = 0; s < QPL; ++s)
 #pragma unroll
-            for (int p = 0; p < 8; ++p) a8[s][p] = pack_sim8(e8[s][2 * p], e8[s][2 * p + 1]);
+            for (int p = 0; p < 8; ++p) a8[s][p] = pack_sim8(e8[s][p / 2][2 * (p & 1)], e8[s][p / 2][2 * (p & 1) + 1]);
     } else if constexpr (EMU) {
-        if constexpr (QUADS) {   // back to two codes per word
-#pragma unroll
-            for (int s = 0; s < QPL; ++s)
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    a8[s][2 * p] = a8q[s][p] & 0xFFFFu;
-                    a8[s][2 * p + 1] = a8q[s][p] >> 16;
-                }
-        }
-        uint32_t nan = 0;
+        emu8_check<D, QPL, LY>(qr, ke, w8, sat);
 #pragma unroll
         for (int s = 0; s < QPL; ++s)
 #pragma unroll
-            for (int p = 0; p < 8; ++p) nan |= e4m3_nan_bits(a8[s][p]);
-        if (wave_any(nan != 0)) {
-            nan_keys<QPL>(a8, sat);
-            emu8_pass<D, QPL, true, LY>(qrow, k32e, a8);
-        }
+            for (int g = 0; g < 4; ++g) a8[s][g] = w8[s][g];
     }
-    if constexpr (NKEY > 0) encode16<SIMP>(acc, c16);
+    if constexpr (NM > 0) encode16<SIMP>(acc, c16);
 }
 
-// One channel of the 16-bit accumulation for every key and slot.
-template <int QPL, int NKEY, int... I>
-__device__ __forceinline__ void rec16_channel(float kv, const float (&q)[QPL], float (&acc)[QPL][NKEY],
-                                              std::integer_sequence<int, I...>)
+// Y8 of a 16-key chunk in either profile (sat as in emu8_check).
+template <int D, int QPL, bool SIMP, class LY = RowLay<D>>
+__device__ __forceinline__ void emu8_any(const QRows<QPL> &qr, const KRows &ke, uint32_t (&a8)[QPL][Y8_WORDS<SIMP>],
+                                         uint32_t (&sat)[QPL])
 {
-#pragma unroll
-    for (int s = 0; s < QPL; ++s) fmac16_row<NKEY>(acc[s], kv, q[s]);
+    uint32_t none[QPL][1];
+    fused_pass<D, QPL, 0, true, SIMP, LY>(qr, ke, ke, a8, none, sat);
 }
 
 // Y16 of NKEY keys (NKEY in {4, 8, 12, 16}) for QPL query rows: the FP32 FMA
 // chain over the channels in ascending order from +0, rounded once to e4m11
-// (saturating).  krow is this lane's key row (layout LY): lane l of every
-// 16-lane row supplies key (l mod 16) and must hold key (l mod NKEY) (lanes
-// past NKEY duplicate the first keys and are not read).  codes[s][p] receives
-// the e4m11 codes of keys 2p (bits [15:0]) and 2p+1 (SIM profile: rounded to
-// 11 mantissa bits, codes[s][i] the FP32 pattern of key i).  With few keys per
-// channel the loop is latency-bound, so the loads run PD 4-channel groups
-// ahead in a ring of buffers written only by loads.
-template <int D, int QPL, int NKEY, bool SIMP = false, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void rec16_keys(const QP (&qrow)[QPL], const float *krow,
+// (saturating).  Lane l of every 16-lane row of kr supplies key (l mod 16) and
+// must hold key (l mod NKEY) (lanes past NKEY are not read).  codes[s][p]
+// receives the e4m11 codes of keys 2p (bits [15:0]) and 2p+1 (SIM profile:
+// rounded to 11 mantissa bits, codes[s][i] the FP32 pattern of key i).
+template <int D, int QPL, int NKEY, bool SIMP = false, class LY = RowLay<D>>
+__device__ __forceinline__ void rec16_keys(const QRows<QPL> &qr, const KRows &kr,
                                            uint32_t (&codes)[QPL][y16_words<SIMP>(NKEY)])
 {
-    static_assert(NKEY == 4 || NKEY == 8 || NKEY == 12 || NKEY == 16, "4, 8, 12 or 16 keys");
-    constexpr int PD0 = NKEY <= 8 ? 4 : 2;
-    constexpr int PD = (D / 4) % PD0 == 0 ? PD0 : 2;
-    static_assert((D / 4) % PD == 0, "whole rings of 4-channel groups");
-    float acc[QPL][NKEY];
-#pragma unroll
-    for (int s = 0; s < QPL; ++s)
-#pragma unroll
-        for (int i = 0; i < NKEY; ++i) acc[s][i] = 0.0f;
-    float4 kb[PD], qb[PD][QPL];
-    auto run = [&](int r) {
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            float q[QPL];
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) q[s] = f4_at(qb[r][s], cc);
-            rec16_channel<QPL, NKEY>(f4_at(kb[r], cc), q, acc, std::make_integer_sequence<int, NKEY>());
-        }
-    };
-#pragma unroll
-    for (int r = 0; r < PD; ++r) load_group<QPL, LY>(krow, qrow, 4 * r, kb[r], qb[r]);
-    for (int c = 0; c < D - 4 * PD; c += 4 * PD) {
-        dpp_guard();
-#pragma unroll
-        for (int r = 0; r < PD; ++r) {
-            run(r);
-            load_group<QPL, LY>(krow, qrow, c + 4 * (r + PD), kb[r], qb[r]);
-        }
-    }
-    dpp_guard();
-#pragma unroll
-    for (int r = 0; r < PD; ++r) run(r);   // the last ring, no further loads
-    encode16<SIMP>(acc, codes);
+    uint32_t none[QPL][Y8_WORDS<SIMP>], sat[QPL];
+    fused_pass<D, QPL, NKEY, false, SIMP, LY>(qr, kr, kr, none, codes, sat);
 }
 
 // Whether the 16-bit logit of one (query row, key) saturates: its FP32 FMA
@@ -622,14 +406,6 @@ __device__ __forceinline__ bool y16_saturates(const float *qrow, const float *kr
 #pragma unroll 4
     for (int c = 0; c < D; ++c) a = __builtin_fmaf(qrow[(c / 4) * LY::QS + c % 4], krow[(c / 4) * LY::KS + c % 4], a);
     return __builtin_fabsf(a) >= 511.9375f;
-}
-
-// Y16 of the 16 keys starting at k32 ([key][D] fp32).
-template <int D, int QPL, bool SIMP = false, class LY = RowLay<D>, class QP>
-__device__ __forceinline__ void rec16_chunk(const QP (&qrow)[QPL], const float *k32,
-                                            uint32_t (&codes)[QPL][y16_words<SIMP>(16)])
-{
-    rec16_keys<D, QPL, 16, SIMP, LY>(qrow, k32 + (size_t)(__lane_id() & 15) * LY::KR, codes);
 }
 
 } // namespace lamp

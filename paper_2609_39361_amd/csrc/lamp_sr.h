@@ -116,20 +116,22 @@ __device__ __forceinline__ void sr8_group(const float *const (&qrow)[QPL], const
 // 8-bit logits with stochastic rounding for 16 keys and QPL query rows per
 // lane: the key rows k32 + kk*D (fp32, kk = 0..15, the same for every lane),
 // the query rows qrow[s] (fp32, pre-scaled) of query index j[s]; key index
-// i0 + kk; bh = b*Hq + h.  Codes out as in emu8_chunk: acc[s][p] holds the
-// e4m3 codes of keys 2p (bits 7:0) and 2p+1 (bits 15:8); sat[s] bit kk is
+// i0 + kk; bh = b*Hq + h.  Codes out: acc[s][p] holds the
+// e4m3 codes of keys 4p .. 4p+3, one per byte; sat[s] bit kk is
 // set when a step of key kk's chain was clamped (|t| > 448).
 template <int D, int QPL>
-__device__ __forceinline__ void sr8_chunk(const float *const (&qrow)[QPL], const float *k32, uint64_t seed,
-                                          uint64_t bh, const int (&j)[QPL], int i0, uint32_t (&acc)[QPL][8],
+__device__ __forceinline__ void sr8_chunk(const QRows<QPL> &qr, const float *k32, uint64_t seed,
+                                          uint64_t bh, const int (&j)[QPL], int i0, uint32_t (&acc)[QPL][4],
                                           uint32_t (&sat)[QPL])
 {
     static_assert(D % 8 == 0, "channel groups of 8");
+    const float *qrow[QPL];
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
+        qrow[s] = qr.row(s);
         sat[s] = 0u;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) acc[s][p] = 0u;
+        for (int p = 0; p < 4; ++p) acc[s][p] = 0u;
     }
     for (int kk = 0; kk < 16; ++kk) {
         const float *krow = k32 + (size_t)kk * D;
@@ -147,7 +149,7 @@ __device__ __forceinline__ void sr8_chunk(const float *const (&qrow)[QPL], const
         for (int s = 0; s < QPL; ++s) {
             const uint32_t code = pk_e4m3_sat(y[s], 0.0f) & 0xFFu;
 #pragma unroll
-            for (int p = 0; p < 8; ++p) acc[s][p] |= (p == (kk >> 1)) ? code << (8 * (kk & 1)) : 0u;
+            for (int p = 0; p < 4; ++p) acc[s][p] |= (p == (kk >> 2)) ? code << (8 * (kk & 3)) : 0u;
             sat[s] |= (amax[s] > 0x43E00000u ? 1u : 0u) << kk;
         }
     }
@@ -199,8 +201,8 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
 }
 
 // Y8 with stochastic rounding of one 16-key chunk for QPL query rows of this
-// lane, keys read by row broadcast as in emu8_pass (k32 at the chunk's first
-// key, layout LY; qrow[s] at the pre-scaled query row of query index j[s];
+// lane, keys read by DPP row broadcast (k32 at the chunk's first
+// key, layout LY; slot s of qr the pre-scaled query row of query index j[s];
 // key index key0 + i; bh = b*Hq + h).  The loop runs 8 channels of every
 // chain at a time, so that each Philox call feeds its 8 steps at once, one key
 // pair after the other (a loop, not unrolled, over a switch on the pair: the
@@ -208,8 +210,8 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
 // registers of the surrounding kernel free); the loads run 8 channels ahead in
 // two buffers written only by loads.  acc[s][p] receives the codes of keys
 // 2p (bits 7:0) and 2p+1 (bits 15:8).
-template <int D, int QPL, bool CLAMP, class LY, class QP>
-__device__ __forceinline__ void sr8_pass(const QP (&qrow)[QPL], const float *k32, const int (&j)[QPL], uint32_t key0,
+template <int D, int QPL, bool CLAMP, class LY>
+__device__ __forceinline__ void sr8_pass(const QRows<QPL> &qr, const float *k32, const int (&j)[QPL], uint32_t key0,
                                          uint32_t bh, uint64_t seed, uint32_t (&acc)[QPL][8])
 {
     static_assert(D % 16 == 0, "pairs of 8-channel blocks");
@@ -225,8 +227,8 @@ __device__ __forceinline__ void sr8_pass(const QP (&qrow)[QPL], const float *k32
         k1 = load4(krow + (c / 4 + 1) * LY::KS);
 #pragma unroll
         for (int s = 0; s < QPL; ++s) {
-            q0[s] = load4(qrow[s] + (c / 4) * LY::QS);
-            q1[s] = load4(qrow[s] + (c / 4 + 1) * LY::QS);
+            q0[s] = load4(qr.base[s] + (c / 4) * LY::QS, qr.off);
+            q1[s] = load4(qr.base[s] + (c / 4 + 1) * LY::QS, qr.off);
         }
     };
     auto run = [&](int c, const float4 &k0, const float4 &k1, const float4 (&q0)[QPL], const float4 (&q1)[QPL]) {
@@ -260,24 +262,34 @@ __device__ __forceinline__ void sr8_pass(const QP (&qrow)[QPL], const float *k32
 }
 
 // sr8_pass without saturation first; if any lane of the wave overflowed (a
-// NaN code at the end of a chain), the chunk again with the clamp.  sat[s]
-// receives the keys of slot s whose accumulation saturated (as emu8_chunk).
-template <int D, int QPL, class LY, class QP>
-__device__ __forceinline__ void sr8_chunk_bc(const QP (&qrow)[QPL], const float *k32, const int (&j)[QPL],
-                                             uint32_t key0, uint32_t bh, uint64_t seed, uint32_t (&acc)[QPL][8],
+// NaN code at the end of a chain), the chunk again with the clamp.  w[s][p]
+// receives the codes of keys 4p .. 4p+3, one per byte, sat[s] the keys of slot
+// s whose accumulation saturated (as emu8_check).
+template <int D, int QPL, class LY>
+__device__ __forceinline__ void sr8_chunk_bc(const QRows<QPL> &qr, const float *k32, const int (&j)[QPL],
+                                             uint32_t key0, uint32_t bh, uint64_t seed, uint32_t (&w)[QPL][4],
                                              uint32_t (&sat)[QPL])
 {
-    sr8_pass<D, QPL, false, LY>(qrow, k32, j, key0, bh, seed, acc);
+    uint32_t acc[QPL][8];
+    auto pack = [&] {
+#pragma unroll
+        for (int s = 0; s < QPL; ++s)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) w[s][p] = (acc[s][2 * p] & 0xFFFFu) | (acc[s][2 * p + 1] << 16);
+    };
+    sr8_pass<D, QPL, false, LY>(qr, k32, j, key0, bh, seed, acc);
+    pack();
     uint32_t nan = 0;
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
         sat[s] = 0u;
 #pragma unroll
-        for (int p = 0; p < 8; ++p) nan |= e4m3_nan_bits(acc[s][p]);
+        for (int p = 0; p < 4; ++p) nan |= e4m3x4_nan_bits(w[s][p]);
     }
     if (wave_any(nan != 0)) {
-        nan_keys<QPL>(acc, sat);
-        sr8_pass<D, QPL, true, LY>(qrow, k32, j, key0, bh, seed, acc);
+        nan_keys<QPL>(w, sat);
+        sr8_pass<D, QPL, true, LY>(qr, k32, j, key0, bh, seed, acc);
+        pack();
     }
 }
 
