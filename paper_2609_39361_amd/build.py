@@ -30,6 +30,9 @@ ARCH = "gfx950"
 
 SOURCES = ["lamp_kernels.hip", "lamp_fwd.hip", "lamp_fwd16.hip", "lamp_fwd16_sr.hip", "lamp_decode.hip", "lamp_rates.hip",
            "lamp_noalloc.hip", "lamp_host.cpp"]
+# parts of lamp_fwd16.hip that this build compiles as units of their own, side
+# by side (-DLAMP_SPLIT_UNITS; without it lamp_fwd16.hip includes them)
+SPLIT_UNITS = ["lamp_fwd16_d256.hip", "lamp_fwd16_sim.hip"]
 
 DPP_VGPR_WAITS = 2
 DPP_EXEC_WAITS = 5
@@ -162,13 +165,14 @@ def build(verbose=False, extra=(), out=LIB):
     from concurrent.futures import ThreadPoolExecutor
     tmp = out + ".tmp%d" % os.getpid()
     flags = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
-             "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-DLAMP_SPLIT_UNITS",
              "-I", os.path.join(ROOT, "include"), "-I", CSRC,
              "-Wno-unused-command-line-argument", "-save-temps"] + list(extra)
-    jobs = max(1, min(len(SOURCES), int(os.environ.get("MAX_JOBS", "0")) or (os.cpu_count() or 1)))
+    units = SOURCES + SPLIT_UNITS
+    jobs = max(1, min(len(units), int(os.environ.get("MAX_JOBS", "0")) or (os.cpu_count() or 1)))
     with tempfile.TemporaryDirectory(prefix="lamp_build_") as work:
         with ThreadPoolExecutor(max_workers=jobs) as ex:
-            res = list(ex.map(lambda s: _compile(os.path.join(CSRC, s), work, flags, verbose), SOURCES))
+            res = list(ex.map(lambda s: _compile(os.path.join(CSRC, s), work, flags, verbose), units))
         failed = [out for rc, _, out in res if rc != 0]
         if failed:
             raise RuntimeError("hipcc failed:\n" + "\n".join(failed))
@@ -185,7 +189,7 @@ def build(verbose=False, extra=(), out=LIB):
             raise RuntimeError("link failed:\n" + r.stdout)
         asm_files = sorted(glob.glob(os.path.join(work, "*", "*-hip-amdgcn-amd-amdhsa-" + ARCH + ".s")))
         names = {os.path.basename(f).split("-hip-")[0] for f in asm_files}
-        if not {"lamp_fwd", "lamp_fwd16", "lamp_decode", "lamp_kernels"} <= names:
+        if not {os.path.splitext(u)[0] for u in units if u.endswith(".hip")} <= names:
             os.remove(tmp)
             raise RuntimeError("device assembly of the kernel sources missing: %r" % asm_files)
         bad = []

@@ -315,9 +315,7 @@ __device__ __forceinline__ void dec_logits_role(const DecParams &p, LogitsLds<D>
         if (key < p.N) {
             if (MODE != MODE_ALL16) p.y8[at] = (uint8_t)(acc[i >> 1] >> (8 * (i & 1)));
             if (MODE != MODE_PURE8) {
-                uint32_t code;
-                (void)rn_e4m11((double)acc16[i], &code);
-                p.y16[at] = (uint16_t)code;
+                p.y16[at] = (uint16_t)e4m11_code(rn_e4m11(acc16[i]));
             }
         }
         p.mask[at] = key >= vlo && key <= vhi ? (MODE == MODE_ALL16 ? 1 : 0) : 3;

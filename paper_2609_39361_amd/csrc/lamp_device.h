@@ -87,53 +87,32 @@ __device__ __forceinline__ float e4m3_value(uint32_t code)
 }
 
 // --- e4m11 -----------------------------------------------------------------
-// Round an fp64 value to e4m11 (RNE, subnormal quantum 2^-17, saturating at
-// 511.875).  Returns the value (exact in fp32) and its code in *code.
-__device__ __forceinline__ float rn_e4m11(double y, uint32_t *code)
+// Round an fp32 value to e4m11 (RNE, subnormal quantum 2^-17, saturating at
+// 511.875; a NaN or an infinity gives the largest magnitude): with P the power
+// of two at or below max(|x|, 2^-6), P * 2^12 + |x| stays in the binade of
+// P * 2^12, whose ulp is the quantum of x, so the addition rounds to it.
+__device__ __forceinline__ float rn_e4m11(float x)
 {
-    double ay = __builtin_fabs(y);
-    int e = __builtin_amdgcn_frexp_exp(ay) - 1;          // ay in [2^e, 2^(e+1))
-    int qe = (e > -6 ? e : -6) - 11;                     // exponent of the quantum
-    double c = __builtin_amdgcn_ldexp(1.5, 52 + qe);     // ulp(c) = 2^qe
-    double r = (ay + c) - c;                             // RNE to a multiple of 2^qe
-    r = r < 511.875 ? r : 511.875;
-    uint32_t sign = __builtin_signbit(y) ? 0x8000u : 0u;
-    uint32_t mag;
-    if (r < 0x1p-6) {
-        mag = (uint32_t)(r * 0x1p17);
-    } else {
-        uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, r) >> 32);
-        uint32_t ex = (hi >> 20) - 1023u + 7u;
-        mag = (ex << 11) | ((hi >> 9) & 0x7FFu);
-    }
-    *code = sign | mag;
-    float v = (float)r;
-    return sign ? -v : v;
+    const float ax = __builtin_fabsf(x);
+    const float b = __builtin_fmaxf(ax, 0x1p-6f);
+    const float P = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, b) & 0x7F800000u);
+    const float s = __builtin_fmaf(P, 4096.0f, ax);
+    const float r = __builtin_fminf(__builtin_fmaf(P, -4096.0f, s), 511.875f);
+    return __builtin_copysignf(r, x);
 }
 
-// Value of an e4m11 code, exact in fp32, without branches: the significand
-// (with its implicit bit for a normal code) scaled by 2^(max(ex, 1) - 18).
-// The same rounding of a finite fp32 value, on its bit pattern (identical to
-// rn_e4m11((double)x)): from 2^-6 on, round to nearest even at bit 12 of the
-// fp32 pattern (a carry moves into the exponent); below, add and subtract
-// 1.5 * 2^6, whose ulp is the subnormal quantum 2^-17; then saturate.
-__device__ __forceinline__ float rn_e4m11_f32(float x, uint32_t *code)
+// Code of an e4m11 value and value of a code, both exact: scaled by 2^-120 the
+// exponents of e4m11 (bias 7) are FP32's lowest, subnormals included, so the
+// code is the FP32 pattern without its 12 low bits.
+__device__ __forceinline__ uint32_t e4m11_code(float y)
 {
-    const uint32_t b = __builtin_bit_cast(uint32_t, x), sign = b & 0x80000000u, ab = b & 0x7FFFFFFFu;
-    const float ax = __builtin_bit_cast(float, ab);
-    const uint32_t rn = (ab + 0x7FFu + ((ab >> 12) & 1u)) & 0xFFFFF000u;
-    const float as = (ax + 96.0f) - 96.0f;
-    uint32_t r = ab < 0x3C800000u ? __builtin_bit_cast(uint32_t, as) : rn;   // 0x3C800000 = 2^-6
-    r = r < 0x43FFF000u ? r : 0x43FFF000u;                                     // 0x43FFF000 = 511.875
-    *code = (sign >> 16) | (r >= 0x3C800000u ? (r >> 12) - 0x3C000u : (uint32_t)(as * 131072.0f));
-    return __builtin_bit_cast(float, r | sign);
+    const uint32_t b = __builtin_bit_cast(uint32_t, y * 0x1p-120f);
+    return (b >> 12 & 0x7FFFu) | (b >> 16 & 0x8000u);
 }
 
 __device__ __forceinline__ float e4m11_value(uint32_t code)
 {
-    const uint32_t ex = (code >> 11) & 0xFu, m = code & 0x7FFu;
-    const float v = __builtin_amdgcn_ldexpf((float)(ex ? m | 0x800u : m), (int)(ex ? ex : 1u) - 18);
-    return (code & 0x8000u) ? -v : v;
+    return __builtin_bit_cast(float, (code & 0x8000u) << 16 | (code & 0x7FFFu) << 12) * 0x1p120f;
 }
 
 // An e4m11 (or e4m3) value truncated toward zero to e4m3, saturating at 448;
@@ -156,11 +135,7 @@ __device__ __forceinline__ float trunc_e4m3(float x)
 // Shifts below 2^-14 give the exponential 1.0 in both formats, so they are
 // lifted to 2^-14, the smallest normal shift, which keeps the code arithmetic
 // free of the subnormal case.
-__device__ __forceinline__ float shift_of(float mu_hat, float y)
-{
-    float x = mu_hat - y;
-    return x > 0x1p-14f ? x : 0x1p-14f;
-}
+__device__ __forceinline__ float shift_of(float mu_hat, float y) { return __builtin_fmaxf(mu_hat - y, 0x1p-14f); }
 
 // ue5m3 (bias 15) code of a normal shift: RNE on the fp32 bits.  Shifts are
 // at most 1024 (code 200); the clamp keeps the table index in range whatever
@@ -319,6 +294,12 @@ __device__ __forceinline__ double wave_max_f64(double v)
         v = o > v ? o : v;
     }
     return v;
+}
+
+// Maximum into an LDS word shared by the workgroup.
+__device__ __forceinline__ void lds_fmax(float *p, float v)
+{
+    (void)__hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ bool wave_any(bool p)

@@ -1,10 +1,14 @@
 // lamp_fwd16.hip -- the LampAttention forward kernel for 16-key sub-blocks
 // (b_k = 16, N_k = 4, d in {128, 256}), software-pipelined across key tiles.
 //
-// Work split as in the general kernel: one workgroup of 4 waves per (batch,
-// query head, query block of BQ rows); every lane holds QPL = BQ/64 query rows
-// and every wave the running state of all BQ rows; wave w owns sub-block w of
-// every 64-key tile and the output channel slice [w*D/4, (w+1)*D/4).
+// Work split: one workgroup per (batch, query head, query block of BQ rows),
+// of 4 BQ/WR waves.  Wave w = 4 hf + wk holds the WR rows of row part hf, WR/64
+// per lane, with their running state, and owns sub-block wk of every 64-key
+// tile and the output channel slice [wk*D/4, (wk+1)*D/4) of those rows.  The
+// decisions concern all BQ rows: the running maxima of every row are small and
+// kept by every wave, so that each derives stage 1 from the same shared data;
+// the sums stay with their row part, and the stage-2 test is put together from
+// the parts' votes in LDS.
 //
 // Pipelining.  The 8-bit logits of tile t+1 do not depend on any decision
 // taken in tile t.  Stage 1 of tile t needs the 16-bit logits of the
@@ -16,8 +20,7 @@
 // registers) together with the 8-bit logits of this wave's sub-block of tile
 // t+1 (codes to the other half of a double-buffered LDS array).  Per tile:
 //   A. fused pass: 16-bit logits of F0(t), 8-bit logits of tile t+1;
-//      16-bit column maxima merged with LDS atomic max (exact fixed point:
-//      e4m11 values are multiples of 2^-17 below 2^9);
+//      16-bit column maxima merged with LDS float maxima;
 //   B. barrier;
 //   C. stage 1 of tile t (Sec. 3.1, Eq. (7)) on the column maxima;
 //   D. exponentials of tile t (8-bit LUT in LDS, 16-bit table of exact bf16
@@ -36,10 +39,6 @@
 #include "lamp_sr.h"
 #include "lamp_stats.h"
 
-#ifndef LAMP_MIN_WAVES
-#define LAMP_MIN_WAVES 2
-#endif
-
 namespace lamp {
 
 // Phase timer (a build with -DLAMP_PHASE_TIMER, for measurement only): every
@@ -48,24 +47,24 @@ namespace lamp {
 // cleared by lamp_phase_read.  Phases: 0 fused pass, 1 code and maxima
 // emission, 2 barrier B, 3 stage 1, 4 exponentials, 5 barrier E, 6 rescale
 // and stage 2, 7 P.V and the next speculative set, 8 barrier I, 9 prologue
-// and epilogue.  (Not in the stochastic-rounding instantiations, which are
-// compiled in a unit of their own, lamp_fwd16_sr.hip.)
-#if defined(LAMP_PHASE_TIMER) && !defined(LAMP_FWD16_NO_LAUNCHERS)
+// and epilogue.  (Only in the instantiations of this unit, d = 128 with the
+// formats of Sec. 3.3; not in those of lamp_fwd16_*.hip.)
+#if defined(LAMP_PHASE_TIMER) && !defined(LAMP_FWD16_PART)
 __device__ unsigned long long phase_cycles[PHASE_N + 1];
 #define LAMP_PH_INIT                                                              \
-    __shared__ uint32_t ph_lds[4 * PHASE_N];                                      \
-    if (lane < PHASE_N) ph_lds[w * PHASE_N + lane] = 0u;                          \
+    __shared__ uint32_t ph_lds[8 * PHASE_N];                                      \
+    if (lane < PHASE_N) ph_lds[wv * PHASE_N + lane] = 0u;                          \
     uint32_t ph_t = (uint32_t)__builtin_readcyclecounter();
 #define LAMP_PH(i)                                                                \
     do {                                                                          \
         const uint32_t ph_n = (uint32_t)__builtin_readcyclecounter();             \
-        if (lane == 0) ph_lds[w * PHASE_N + (i)] += ph_n - ph_t;                  \
+        if (lane == 0) ph_lds[wv * PHASE_N + (i)] += ph_n - ph_t;                  \
         ph_t = ph_n;                                                              \
     } while (0)
 #define LAMP_PH_FLUSH                                                             \
     do {                                                                          \
         LAMP_PH(9);                                                               \
-        if (lane < PHASE_N) atomicAdd(&phase_cycles[lane], (unsigned long long)ph_lds[w * PHASE_N + lane]); \
+        if (lane < PHASE_N) atomicAdd(&phase_cycles[lane], (unsigned long long)ph_lds[wv * PHASE_N + lane]); \
         if (lane == PHASE_N) atomicAdd(&phase_cycles[PHASE_N], 1ull);             \
     } while (0)
 #else
@@ -74,7 +73,7 @@ __device__ unsigned long long phase_cycles[PHASE_N + 1];
 #define LAMP_PH_FLUSH ((void)0)
 #endif
 
-#ifndef LAMP_FWD16_NO_LAUNCHERS
+#ifndef LAMP_FWD16_PART
 hipError_t phase_read(unsigned long long *host, bool reset)
 {
 #ifdef LAMP_PHASE_TIMER
@@ -101,62 +100,38 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 enum { PREC_LOW = 0, PREC_S1 = 1, PREC_S2 = 2, PREC_INACTIVE = 3 };
 
 
-template <int D, int BQ>
+template <int D, int BQ, int WR>
 struct Cfg16 {
     static constexpr int NK = 4, BK = 16, KPT = 64, NW = 4;
-    static constexpr int QPL = BQ / 64;       // query rows per lane
+    static constexpr int H = BQ / WR;         // row parts
+    static constexpr int QPL = WR / 64;       // query rows per lane
+    static constexpr int NT = 64 * NW * H;    // threads
     static constexpr int CPW = D / NW;        // output channels per wave
     static constexpr int CT = CPW / 32;       // 32-channel MFMA tiles per wave
-    static constexpr int QG = BQ / 32;        // 32-row MFMA groups
+    static constexpr int QG = WR / 32;        // 32-row MFMA groups of a row part
     static constexpr int YP = KPT + 8;        // LDS pitch (u16) of the code rows
     static constexpr size_t YB = (size_t)BQ * YP * 2;
     static constexpr size_t OFF_Y = 0;                                  // u16 [2][BQ][YP]
     static constexpr size_t OFF_YL = OFF_Y + 2 * YB;                    // u16 [BQ][YP]
     static constexpr size_t OFF_LUT = OFF_YL + YB;                      // u16 [256]
     static constexpr size_t OFF_M8 = OFF_LUT + 512;                     // f32 [2][NK][BQ]
-    static constexpr size_t OFF_CMI = OFF_M8 + (size_t)2 * NK * BQ * 4;  // i32 [2][NK][BQ]
+    static constexpr size_t OFF_CM = OFF_M8 + (size_t)2 * NK * BQ * 4;  // f32 [2][NK][BQ]
     static constexpr size_t CMF = (size_t)2 * NW * BQ * 4 > (size_t)NK * BQ * 8 ? (size_t)2 * NW * BQ * 4
                                                                                   : (size_t)NK * BQ * 8;
-    static constexpr size_t OFF_CMF = OFF_CMI + (size_t)2 * NK * BQ * 4;  // f32 [2][NW][BQ] | f64 [NK][BQ]
+    static constexpr size_t OFF_CMF = OFF_CM + (size_t)2 * NK * BQ * 4;  // f32 [2][NW][BQ] | f64 [NK][BQ]
     static constexpr size_t OFF_SP = OFF_CMF + CMF;                     // f64 [2][NW][BQ]
     static constexpr size_t OFF_ED = OFF_SP + (size_t)2 * NW * BQ * 8;  // f64 [EXPDOC_NK]
-    static constexpr size_t OFF_TS = OFF_ED + (size_t)EXPDOC_NK * 8;    // i32 [2][NK] sub-block threats
-    static constexpr size_t OFF_ST = OFF_TS + (size_t)2 * NK * 4;       // u32 [ST_N] statistics
-    static constexpr size_t OFF_PD = OFF_ST + (size_t)ST_N * 4;         // f64 [NW][BQ] pending rescale factors
+    static constexpr size_t OFF_TS = OFF_ED + (size_t)EXPDOC_NK * 8;    // i32 [2][H][NK] sub-block threats
+    static constexpr size_t OFF_VT = OFF_TS + (size_t)2 * H * NK * 4;   // u32 [2][H] votes of the row parts
+    static constexpr size_t OFF_ST = OFF_VT + (size_t)2 * H * 4;        // u32 [ST_N] statistics
+    static constexpr size_t OFF_PD = (OFF_ST + (size_t)ST_N * 4 + 7) / 8 * 8;   // f64 [NW][BQ] pending rescale factors
     static constexpr size_t LDS = OFF_PD + (size_t)NW * BQ * 8;
-    static_assert(BQ == 64 || BQ == 128, "64 or 128 query rows per block");
+    static_assert((BQ == 64 || BQ == 128) && (WR == 64 || WR == BQ), "64 or 128 query rows per block");
     static_assert(CPW % 32 == 0, "whole 32-channel tiles per wave");
 };
 
-// e4m11 / e4m3 values as exact fixed point in units of 2^-17 (|y| < 2^9).
+// An e4m11 / e4m3 value as exact fixed point in units of 2^-17 (|y| < 2^9).
 __device__ __forceinline__ int fx_of(float y) { return (int)(y * 131072.0f); }
-__device__ __forceinline__ float fx_value(int f) { return (float)f * (1.0f / 131072.0f); }
-
-// Keys of the 16-bit column maxima merged by integer atomic max: exact fixed
-// point for e4m11, the order-preserving map of the FP32 pattern in the SIM
-// profile (whose values span FP32's range).
-template <bool SIMP>
-__device__ __forceinline__ int cm_key(float y)
-{
-    if constexpr (SIMP) return ord_of(y);
-    else return fx_of(y);
-}
-
-// fx_of of an e4m11 code, from the code: the significand (with its implicit
-// bit when normal) shifted by max(ex, 1) - 1.
-__device__ __forceinline__ int e4m11_fx(uint32_t code)
-{
-    const uint32_t ex = (code >> 11) & 0xFu, m = code & 0x7FFu;
-    const int mag = ex ? (int)((m | 0x800u) << (ex - 1u)) : (int)m;
-    return (code & 0x8000u) ? -mag : mag;
-}
-
-template <bool SIMP>
-__device__ __forceinline__ float cm_value(int f)
-{
-    if constexpr (SIMP) return ord_value(f);
-    else return fx_value(f);
-}
 
 // SIM 16-bit logits in LDS: the high and low 16 bits of the FP32 patterns of
 // two keys, in the code row and the low row.
@@ -213,31 +188,37 @@ __device__ __forceinline__ int wave_max_i32(int v)
 // SR: the 8-bit logits rounded stochastically (lamp_sr.h, sr8_chunk_bc) with
 // the generator keyed by p.seed; they run after the fused pass, which then
 // carries the speculative 16-bit logits alone.
-template <int D, int BQ, int MODE, bool SIMP, bool OBS, bool CMP, bool SR = false>
-__global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdParams p)
+// WR: query rows of a wave, 64 or BQ (fwd16_wide chooses).  Two waves per SIMD
+// either way: four (64 rows and 128 registers) run at 12.4 ms on the 8K
+// prefill, 11.6 ms with 128 rows and two, and the medium prompts lose as well.
+template <int D, int BQ, int WR, int MODE, bool SIMP, bool OBS, bool CMP, bool SR = false>
+__global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(FwdParams p)
 {
-    using C = Cfg16<D, BQ>;
-    constexpr int NK = C::NK, BK = C::BK, KPT = C::KPT, NW = C::NW, QPL = C::QPL, CPW = C::CPW;
-    constexpr int CT = C::CT, QG = C::QG, YP = C::YP;
-    constexpr int WPM = SIMP ? 4 : 2;   // words of 16-bit logits per 4 keys (SIM: FP32 patterns)
+    using C = Cfg16<D, BQ, WR>;
+    constexpr int NK = C::NK, BK = C::BK, KPT = C::KPT, NW = C::NW, CPW = C::CPW;
+    constexpr int CT = C::CT, QG = C::QG, YP = C::YP, H = C::H, NT = C::NT;
+    constexpr int QPL = C::QPL;
+    constexpr int HS = MODE == MODE_LAMP ? BQ / 64 : QPL;   // rows per lane whose running maximum a wave keeps
 
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *ycode2 = reinterpret_cast<uint16_t *>(smem + C::OFF_Y);   // [2][BQ][YP] logit codes, then E
     uint16_t *ylo = reinterpret_cast<uint16_t *>(smem + C::OFF_YL);     // [BQ][YP] low bf16 part of E16
     uint16_t *lut = reinterpret_cast<uint16_t *>(smem + C::OFF_LUT);    // [256] 8-bit exp (bf16 bits; SIM table)
     float *m8s2 = reinterpret_cast<float *>(smem + C::OFF_M8);          // [2][NK][BQ] 8-bit column maxima
-    int *cmi2 = reinterpret_cast<int *>(smem + C::OFF_CMI);             // [2][NK][BQ] 16-bit column maxima
+    float *cm2 = reinterpret_cast<float *>(smem + C::OFF_CM);           // [2][NK][BQ] 16-bit column maxima
     float *cmf = reinterpret_cast<float *>(smem + C::OFF_CMF);          // [2][NW][BQ] one-at-a-time maxima
     double *cst_lds = reinterpret_cast<double *>(smem + C::OFF_CMF);    // [NK][BQ] stage-2 costs (same space)
     double *sps = reinterpret_cast<double *>(smem + C::OFF_SP);         // [NW][BQ] partial row sums of E
     double *spf = sps + NW * BQ;                                        // [NW][BQ] over 8-bit sub-blocks
     double *edk = reinterpret_cast<double *>(smem + C::OFF_ED);         // exp_doc constants
-    int *tsl = reinterpret_cast<int *>(smem + C::OFF_TS);               // [2][NK] threats of a tile
+    int *tsl = reinterpret_cast<int *>(smem + C::OFF_TS);               // [2][H][NK] threats of a tile
+    uint32_t *votes = reinterpret_cast<uint32_t *>(smem + C::OFF_VT);   // [2][H] stage 2: needed, feasible sets
     uint32_t *stl = reinterpret_cast<uint32_t *>(smem + C::OFF_ST);    // [ST_N] statistics (p.stats)
     double *pend = reinterpret_cast<double *>(smem + C::OFF_PD);        // [NW][BQ] pending factors (G below)
 
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // w is wave-uniform
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // wave-uniform
+    const int w = wv & (NW - 1), hf = wv / NW;   // sub-block and channel slice, row part
     LAMP_PH_INIT
     const int nqb = p.Nq / BQ;   // query blocks per head (the last may be partial)
     // Block order.  Workgroups are handed to the 8 XCDs round-robin (block i to
@@ -276,7 +257,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     qr.off = (uint32_t)lane * 16u;
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
-        row[s] = s * 64 + lane;
+        row[s] = hf * WR + s * 64 + lane;
         const int j = q0 + row[s];
         jq[s] = j;
         vlo[s] = p.window > 0 ? (j - p.window + 1 > 0 ? j - p.window + 1 : 0) : 0;
@@ -285,7 +266,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             vlo[s] = p.N;
             vhi[s] = -1;
         }
-        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + 64 * s) * D;
+        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + WR * hf + 64 * s) * D;
     }
     const int bv_lo = p.window > 0 ? (q0 - p.window + 1 > 0 ? q0 - p.window + 1 : 0) : 0;
     const int bv_hi = p.causal ? (q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1) : p.N - 1;
@@ -304,11 +285,11 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
     const uint16_t *vtbase = p.vt + ((size_t)b * p.Hkv + hk) * (size_t)D * p.Nk;    // V^T [D][Nk]
     uint8_t *mrow = p.mask + (((size_t)b * p.Hq + h) * nqb + qb) * (size_t)(p.Nk / BK);
 
-    for (int i = tid; i < 256; i += 256) lut[i] = SIMP ? p.sim8[i] : p.lut8e[i];
+    for (int i = tid; i < 256; i += NT) lut[i] = SIMP ? p.sim8[i] : p.lut8e[i];
     if (tid < EXPDOC_NK) edk[tid] = EXPDOC_K[tid];
-    for (int i = tid; i < 2 * NK * BQ; i += 256) cmi2[i] = INT_MIN;
+    for (int i = tid; i < 2 * NK * BQ; i += NT) cm2[i] = -__builtin_inff();
     if (tid < ST_N) stl[tid] = 0u;
-    for (int i = tid; i < NW * BQ; i += 256) pend[i] = 1.0;
+    for (int i = tid; i < NW * BQ; i += NT) pend[i] = 1.0;
     // logit observables (tests): this query block is observed (uniform)
     const bool dbg_blk = qb >= p.dbg_qb0 && qb < p.dbg_qb0 + p.dbg_nqb;
     const bool dbg8 = OBS && !SIMP && p.dbg_y8 != nullptr && dbg_blk;
@@ -317,6 +298,16 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         return ((((size_t)b * p.Hq + h) * p.dbg_nqb + (qb - p.dbg_qb0)) * BQ + row[s]) * (size_t)p.Nk;
     };
 
+    // the rows whose running maxima this wave keeps (every row in the
+    // threshold mode, else its own), and its own among them
+    int rowS[HS];
+    float muS[HS];
+#pragma unroll
+    for (int g = 0; g < HS; ++g) {
+        rowS[g] = (HS == QPL ? hf * WR : 0) + g * 64 + lane;
+        muS[g] = NEG_INF;
+    }
+    auto own = [&](const float (&x)[HS], int s) { return HS == QPL || hf == 0 ? x[s] : x[HS - QPL + s]; };
     float mu[QPL];
     double om[QPL];
 #pragma unroll
@@ -333,20 +324,25 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             for (int r = 0; r < 16; ++r) acc[g][t][r] = 0.0f;
 
     auto visible = [&](int s, int key) { return key >= vlo[s] && key <= vhi[s]; };
+    // every key of [key0, key0 + n) visible to every row of this wave (uniform)
+    const int all_lo = p.window > 0 ? q0 + hf * WR + WR - p.window : 0;
+    const int all_hi = q0 + hf * WR + WR > p.N ? -1 : p.causal ? q0 + hf * WR : p.N - 1;
+    auto all_visible = [&](int key0, int n) { return key0 >= all_lo && key0 + n - 1 <= all_hi; };
     auto ycode_of = [&](int tile) { return ycode2 + (size_t)(tile & 1) * BQ * YP; };
     auto m8s_of = [&](int tile) { return m8s2 + (size_t)(tile & 1) * NK * BQ; };
-    auto cmi_of = [&](int tile) { return cmi2 + (size_t)(tile & 1) * NK * BQ; };
+    auto cm_of = [&](int tile) { return cm2 + (size_t)(tile & 1) * NK * BQ; };
 
-    // active sub-blocks of a tile (a visible pair anywhere in the block), uniform
+    // active sub-blocks of a tile (a visible pair anywhere in the block): some
+    // row j of the block with k <= j <= z + window - 1, or, not causal, any key
+    const int q_last = q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1;
     auto active_of = [&](int tile) {
         uint32_t a = 0;
 #pragma unroll
         for (int th = 0; th < NK; ++th) {
             const int k = tile * KPT + th * BK, z = k + BK - 1;
-            bool any = false;
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) any |= (k <= vhi[s] && z >= vlo[s]);
-            if (wave_any(any)) a |= 1u << th;
+            const int j0 = p.causal && k > q0 ? k : q0;
+            const int j1 = p.window > 0 && z + p.window - 1 < q_last ? z + p.window - 1 : q_last;
+            if (k < p.N && j0 <= j1) a |= 1u << th;
         }
         return a;
     };
@@ -362,9 +358,6 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         const int ck0 = tile * KPT + w * BK;
         uint16_t *yc = ycode_of(tile);
         float *m8s = m8s_of(tile);
-        bool full = true;
-#pragma unroll
-        for (int s = 0; s < QPL; ++s) full &= ck0 >= vlo[s] && ck0 + 15 <= vhi[s];
         if constexpr (!SIMP) {
             // visible keys of the 16 in each slot (for the observables)
             auto vis16 = [&](int s) {
@@ -422,8 +415,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                         // invisible keys enter as -inf, by selection rather than branches
                         const float x0 = (FULL || visible(s, i0)) ? yv.x : NEG_INF;
                         const float x1 = (FULL || visible(s, i0 + 1)) ? yv.y : NEG_INF;
-                        mx = x0 > mx ? x0 : mx;
-                        mx = x1 > mx ? x1 : mx;
+                        mx = __builtin_fmaxf(__builtin_fmaxf(x0, x1), mx);
                         packed[pp] = SIMP ? a8[s][pp] : spread_codes(a8[s][pp / 2], pp & 1);
                     }
                     u32x4 *dst = reinterpret_cast<u32x4 *>(yc + row[s] * YP + w * BK);
@@ -433,33 +425,35 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 m8s[w * BQ + row[s]] = mx;
             }
         };
-        if (!wave_any(!full)) run(std::true_type());
+        if (all_visible(ck0, 16)) run(std::true_type());
         else run(std::false_type());
     };
     // the margin test of every sub-block of `tile` against mu_hat (Eq. (7)):
     // mu_hat_j > fma(|mu_hat_j|, delta, m8); columns without a visible entry
     // are not tested; mu_hat = -inf fails.  m8 from LDS, identical in every wave.
-    auto fails_of = [&](const float (&m8)[NK][QPL], const float (&mh)[QPL]) {
+    auto fails = [&](float m8v, float mhv) {
+        // mu_hat = -inf as a finite number below every logit: a visible logit
+        // then fails and a column without one (m8 = -inf) passes, as required
+        const double m = (double)__builtin_fmaxf(mhv, -0x1p100f);
+        return !(m > __builtin_fma(__builtin_fabs(m), p.delta, (double)m8v));
+    };
+    auto fails_of = [&](const float (&m8)[NK][HS], const float (&mh)[HS]) {
         uint32_t f = 0;
 #pragma unroll
         for (int th = 0; th < NK; ++th) {
             bool bad = false;
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
-                if (m8[th][s] > NEG_INF) {
-                    const double m = (double)mh[s];
-                    bad |= !(m > __builtin_fma(__builtin_fabs(m), p.delta, (double)m8[th][s]));
-                }
+            for (int s = 0; s < HS; ++s) bad |= fails(m8[th][s], mh[s]);
             if (wave_any(bad)) f |= 1u << th;
         }
         return f;
     };
-    auto load_m8 = [&](int tile, float (&m8)[NK][QPL]) {
+    auto load_m8 = [&](int tile, float (&m8)[NK][HS]) {
         const float *m8s = m8s_of(tile);
 #pragma unroll
         for (int th = 0; th < NK; ++th)
 #pragma unroll
-            for (int s = 0; s < QPL; ++s) m8[th][s] = m8s[th * BQ + row[s]];
+            for (int s = 0; s < HS; ++s) m8[th][s] = m8s[th * BQ + rowS[s]];
     };
     // Threat of this wave's sub-block of `tile` against the running maximum mu
     // (the stage-1 ordering of Eq. (7)): T = max over rows with a visible 8-bit
@@ -480,24 +474,24 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 tv = (vis && d > tv) ? d : tv;
             }
             const int T = wave_max_i32(tv);
-            if (lane == 0) tsl[(tile & 1) * NK + w] = T;
+            if (lane == 0) tsl[((tile & 1) * H + hf) * NK + w] = T;
         }
     };
     // the set of sub-blocks whose 16-bit logits the next fused pass computes
     auto f0_of = [&](int tile, uint32_t act) -> uint32_t {
         if (mode == MODE_ALL16) return act;
         if (mode == MODE_PURE8 || stage1_off) return 0u;
-        float m8[NK][QPL];
+        float m8[NK][HS];
         load_m8(tile, m8);
-        return fails_of(m8, mu);
+        return fails_of(m8, muS);
     };
     // one-at-a-time 16-bit recompute of sub-block th of the tile at k0 shared
     // by all waves (4 keys each); fn(key0, codes[QPL][2]) receives the codes
     auto shared16 = [&](int k0, int th, auto fn) {
         const int key0 = k0 + th * BK + w * 4;
         if (key0 > bv_hi || key0 + 3 < bv_lo) return;   // nothing visible in the block
-        uint32_t yc[QPL][WPM];
-        rec16_keys<D, QPL, 4, SIMP, GrpLay>(qr, keys_at<GrpLay>(krow_of(key0), 4u * (lane & 3)), yc);
+        float yc[QPL][4];
+        rec16_values<D, QPL, 4, SIMP, GrpLay>(qr, keys_at<GrpLay>(krow_of(key0), 4u * (lane & 3)), yc);
         fn(key0, yc);
     };
     // a 16-bit exponential from the table in global memory as bf16 high / low
@@ -516,11 +510,10 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             return bf16_value(eh) + bf16_value(el);   // exact
         }
     };
-    // Observables of the 16-bit logits of 4 keys from key0 of every slot
-    // (codes two per word, as the recomputes leave them): their codes for the
-    // tests, and the saturated ones among the visible keys whose code is the
-    // largest e4m11 magnitude (the FP32 chain rerun for those alone).
-    auto obs16 = [&](int key0, const uint32_t (&yc)[QPL][WPM]) {
+    // Observables of the 16-bit logits of 4 keys from key0 of every slot: their
+    // codes for the tests, and the saturated ones among the visible keys whose
+    // value is the largest e4m11 magnitude (the FP32 chain rerun for those alone).
+    auto obs16 = [&](int key0, const float (&yc)[QPL][4]) {
         if constexpr (!SIMP) {
             if (dbg16) {
 #pragma unroll
@@ -528,8 +521,8 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     uint32_t wd[2];
 #pragma unroll
                     for (int x = 0; x < 2; ++x) {
-                        const uint32_t lo = visible(s, key0 + 2 * x) ? (yc[s][x] & 0xFFFFu) : 0xFFFFu;
-                        const uint32_t hi = visible(s, key0 + 2 * x + 1) ? (yc[s][x] >> 16) : 0xFFFFu;
+                        const uint32_t lo = visible(s, key0 + 2 * x) ? e4m11_code(yc[s][2 * x]) : 0xFFFFu;
+                        const uint32_t hi = visible(s, key0 + 2 * x + 1) ? e4m11_code(yc[s][2 * x + 1]) : 0xFFFFu;
                         wd[x] = lo | (hi << 16);
                     }
                     *reinterpret_cast<uint2 *>(p.dbg_y16 + dbg_off(s) + key0) = make_uint2(wd[0], wd[1]);
@@ -540,10 +533,8 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
 #pragma unroll
                 for (int s = 0; s < QPL; ++s)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t code = (yc[s][i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-                        atmax |= ((code & 0x7FFFu) == 0x7FFFu && visible(s, key0 + i) ? 1u : 0u) << (4 * s + i);
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        atmax |= (__builtin_fabsf(yc[s][i]) == 511.875f && visible(s, key0 + i) ? 1u : 0u) << (4 * s + i);
                 if (wave_any(atmax != 0u)) {
                     uint32_t n = 0;
                     for (uint32_t m = atmax; m; m &= m - 1) {
@@ -611,7 +602,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
 
         // ---- A. fused pass: 16-bit logits of F0 (4 keys of each member per
         // wave), 8-bit logits of this wave's sub-block of the next tile
-        uint32_t y16r[QPL][4 * WPM];   // 16-bit logits of keys th*16 + w*4 + {0..3} of the g-th member of F0
+        float y16r[QPL][4 * NK];   // 16-bit logits of keys th*16 + w*4 + {0..3} of the g-th member of F0
         {
             const int nf_all = __builtin_popcount(F0);
             const int nf = CMP ? (nf_all < 1 ? nf_all : 1) : nf_all;   // members in the fused pass
@@ -623,13 +614,12 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             auto run = [&](auto nkey_c, auto emu_c) {
                 constexpr int NKEY = decltype(nkey_c)::value;
                 constexpr bool EMU = decltype(emu_c)::value;
-                uint32_t c[QPL][y16_words<SIMP>(NKEY)];
+                float c[QPL][NKEY > 0 ? NKEY : 1];
                 fused_pass<D, QPL, NKEY, EMU, SIMP, GrpLay>(qr, keys16<GrpLay>(k32e), kr, a8, c, sat8);
-                if constexpr (NKEY > 0)
 #pragma unroll
-                    for (int s = 0; s < QPL; ++s)
+                for (int s = 0; s < QPL; ++s)
 #pragma unroll
-                        for (int pp = 0; pp < y16_words<SIMP>(NKEY); ++pp) y16r[s][pp] = c[s][pp];
+                    for (int i = 0; i < NKEY; ++i) y16r[s][i] = c[s][i];
             };
             using T_ = std::true_type;
             using F_ = std::false_type;
@@ -665,12 +655,12 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     const KRows krs = member_keys(k0, F0 & (F0 - 1u));   // without the member of the fused pass
                     auto seq = [&](auto nkey_c) {
                         constexpr int NKEY = decltype(nkey_c)::value;
-                        uint32_t c[QPL][y16_words<SIMP>(NKEY)];
-                        rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
+                        float c[QPL][NKEY];
+                        rec16_values<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
 #pragma unroll
                         for (int s = 0; s < QPL; ++s)
 #pragma unroll
-                            for (int pp = 0; pp < y16_words<SIMP>(NKEY); ++pp) y16r[s][WPM + pp] = c[s][pp];
+                            for (int i = 0; i < NKEY; ++i) y16r[s][4 + i] = c[s][i];
                     };
                     switch (nr) {
                     case 1: seq(std::integral_constant<int, 4>()); break;
@@ -680,7 +670,8 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 }
             }
             // 16-bit column maxima over this wave's 4 keys of every member of F0
-            int *cmi = cmi_of(t);
+            // (LDS float maxima: -inf, the identity, was set in the tile before)
+            float *cm = cm_of(t);
             uint32_t m = F0;
 #pragma unroll
             for (int g = 0; g < NK; ++g) {
@@ -688,17 +679,18 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 const int th = __builtin_ctz(m);
                 m &= m - 1;
                 const int key0 = k0 + th * BK + w * 4;
+                const bool full = all_visible(key0, 4);
 #pragma unroll
                 for (int s = 0; s < QPL; ++s) {
-                    int cm = INT_MIN;
+                    float x[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        int f;
-                        if constexpr (SIMP) f = cm_key<SIMP>(y16_value<SIMP>(&y16r[s][g * WPM], i));
-                        else f = e4m11_fx((y16r[s][g * WPM + (i >> 1)] >> (16 * (i & 1))) & 0xFFFFu);
-                        cm = (visible(s, key0 + i) && f > cm) ? f : cm;
+                    for (int i = 0; i < 4; ++i) x[i] = y16r[s][g * 4 + i];
+                    if (!full) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) x[i] = visible(s, key0 + i) ? x[i] : NEG_INF;
                     }
-                    if (cm != INT_MIN) atomicMax(&cmi[th * BQ + row[s]], cm);
+                    const float mx = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(x[0], x[1]), x[2]), x[3]);
+                    lds_fmax(&cm[th * BQ + row[s]], mx);
                 }
             }
         }
@@ -707,39 +699,36 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         LAMP_PH(2);
 
         // ---- C. running maximum mu_hat and stage 1 of tile t
-        float muh[QPL];
+        float muhS[HS];
 #pragma unroll
-        for (int s = 0; s < QPL; ++s) muh[s] = mu[s];
+        for (int s = 0; s < HS; ++s) muhS[s] = muS[s];
         uint32_t prec16 = 0;   // stage-1 (or threshold-0) sub-blocks
-        float cm16[NK][QPL];   // 16-bit column maxima of the members of F0
+        float cm16[NK][HS];    // 16-bit column maxima of the members of F0 (-inf elsewhere)
         {
-            const int *cmi = cmi_of(t);
+            const float *cm = cm_of(t);
 #pragma unroll
             for (int th = 0; th < NK; ++th)
 #pragma unroll
-                for (int s = 0; s < QPL; ++s) {
-                    const int f = (F0 >> th & 1u) ? cmi[th * BQ + row[s]] : INT_MIN;
-                    cm16[th][s] = f == INT_MIN ? NEG_INF : cm_value<SIMP>(f);
-                }
+                for (int s = 0; s < HS; ++s) cm16[th][s] = F0 ? cm[th * BQ + rowS[s]] : NEG_INF;
         }
         if (mode == MODE_PURE8 || stage1_off) {   // running maximum over the 8-bit logits
-            float m8[NK][QPL];
+            float m8[NK][HS];
             load_m8(t, m8);
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
+            for (int s = 0; s < HS; ++s)
 #pragma unroll
-                for (int th = 0; th < NK; ++th) muh[s] = m8[th][s] > muh[s] ? m8[th][s] : muh[s];
+                for (int th = 0; th < NK; ++th) muhS[s] = m8[th][s] > muhS[s] ? m8[th][s] : muhS[s];
         } else if (mode == MODE_ALL16) {
             prec16 = act;
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
+            for (int s = 0; s < HS; ++s)
 #pragma unroll
-                for (int th = 0; th < NK; ++th) muh[s] = cm16[th][s] > muh[s] ? cm16[th][s] : muh[s];
+                for (int th = 0; th < NK; ++th) muhS[s] = cm16[th][s] > muhS[s] ? cm16[th][s] : muhS[s];
         } else {
-            float m8[NK][QPL];
+            float m8[NK][HS];
             load_m8(t, m8);
             // threats T_theta = max_j (m8 - mu_j) (+inf when mu_j = -inf): exact
-            // ints from the four waves (own_threat), or, in the SIM profile,
+            // ints from the waves (own_threat), or, in the SIM profile,
             // exact in fp64
             using TT = std::conditional_t<SIMP, double, int>;
             TT T[NK];
@@ -748,16 +737,23 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 for (int th = 0; th < NK; ++th) {
                     double tv = -__builtin_inf();
 #pragma unroll
-                    for (int s = 0; s < QPL; ++s)
+                    for (int s = 0; s < HS; ++s)
                         if (m8[th][s] > NEG_INF) {
-                            const double d = (double)m8[th][s] - (double)mu[s];
+                            const double d = (double)m8[th][s] - (double)muS[s];
                             tv = d > tv ? d : tv;
                         }
                     T[th] = wave_max_f64(tv);
                 }
             } else {
 #pragma unroll
-                for (int th = 0; th < NK; ++th) T[th] = tsl[(t & 1) * NK + th];
+                for (int th = 0; th < NK; ++th) {
+                    T[th] = __builtin_amdgcn_readfirstlane(tsl[(t & 1) * H * NK + th]);
+#pragma unroll
+                    for (int g = 1; g < H; ++g) {
+                        const int o = __builtin_amdgcn_readfirstlane(tsl[((t & 1) * H + g) * NK + th]);
+                        T[th] = o > T[th] ? o : T[th];
+                    }
+                }
             }
             // descending threat, ties by index; order packed 4 bits per rank
             uint32_t order = 0, taken = 0;
@@ -780,22 +776,36 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     taken |= 1u << best;
                 }
             }
-            uint32_t fail = F0;   // the test against mu_hat = mu
-            int pos = 0, par = 0;
-            while (true) {
-                while (pos < na && !(fail >> ((order >> (4 * pos)) & 15u) & 1u)) ++pos;
-                if (pos >= na) break;
+            // The sub-blocks in that order, each tested against the mu_hat that
+            // the recomputes before it left (until the first one, mu, whose
+            // tests F0 holds).
+            bool raised = false;
+            int par = 0;
+            for (int pos = 0; pos < na; ++pos) {
                 const int th = (int)((order >> (4 * pos)) & 15u);
-                ++pos;
+                if (raised) {
+                    bool bad = false;
+#pragma unroll
+                    for (int s = 0; s < HS; ++s) {
+                        float c8 = m8[0][s];
+#pragma unroll
+                        for (int t2 = 1; t2 < NK; ++t2) c8 = t2 == th ? m8[t2][s] : c8;
+                        bad |= fails(c8, muhS[s]);
+                    }
+                    if (!wave_any(bad)) continue;
+                } else if (!(F0 >> th & 1u)) {
+                    continue;
+                }
+                raised = true;
                 prec16 |= 1u << th;
                 if (F0 >> th & 1u) {
 #pragma unroll
-                    for (int s = 0; s < QPL; ++s) {
-                        float c = muh[s];
+                    for (int s = 0; s < HS; ++s) {
+                        float c = muhS[s];
 #pragma unroll
                         for (int t2 = 0; t2 < NK; ++t2)
                             if (t2 == th) c = cm16[t2][s] > c ? cm16[t2][s] : c;
-                        muh[s] = c;
+                        muhS[s] = c;
                     }
                 } else {
                     // outside F0 (not expected, see above): all waves recompute
@@ -803,22 +813,26 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     float cm[QPL];
 #pragma unroll
                     for (int s = 0; s < QPL; ++s) cm[s] = NEG_INF;
-                    shared16(k0, th, [&](int kc, const uint32_t (&yc)[QPL][WPM]) {
+                    shared16(k0, th, [&](int kc, const float (&yc)[QPL][4]) {
                         obs16(kc, yc);
 #pragma unroll
                         for (int s = 0; s < QPL; ++s) {
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
-                                const float yv = y16_value<SIMP>(yc[s], i);
+                                const float yv = yc[s][i];
                                 if (visible(s, kc + i)) cm[s] = yv > cm[s] ? yv : cm[s];
                             }
                             uint2 *dst = reinterpret_cast<uint2 *>(ycode + row[s] * YP + (kc - k0));
                             if constexpr (SIMP) {
-                                *dst = make_uint2(pack_hi16(yc[s][0], yc[s][1]), pack_hi16(yc[s][2], yc[s][3]));
+                                uint32_t b[4];
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) b[i] = __builtin_bit_cast(uint32_t, yc[s][i]);
+                                *dst = make_uint2(pack_hi16(b[0], b[1]), pack_hi16(b[2], b[3]));
                                 *reinterpret_cast<uint2 *>(ylo + row[s] * YP + (kc - k0)) =
-                                    make_uint2(pack_lo16(yc[s][0], yc[s][1]), pack_lo16(yc[s][2], yc[s][3]));
+                                    make_uint2(pack_lo16(b[0], b[1]), pack_lo16(b[2], b[3]));
                             } else {
-                                *dst = make_uint2(yc[s][0], yc[s][1]);
+                                *dst = make_uint2(e4m11_code(yc[s][0]) | e4m11_code(yc[s][1]) << 16,
+                                                  e4m11_code(yc[s][2]) | e4m11_code(yc[s][3]) << 16);
                             }
                         }
                     });
@@ -826,25 +840,27 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     for (int s = 0; s < QPL; ++s) cmf[(par * NW + w) * BQ + row[s]] = cm[s];
                     __syncthreads();
 #pragma unroll
-                    for (int s = 0; s < QPL; ++s)
+                    for (int s = 0; s < HS; ++s)
 #pragma unroll
                         for (int ww = 0; ww < NW; ++ww) {
-                            const float c = cmf[(par * NW + ww) * BQ + row[s]];
-                            muh[s] = c > muh[s] ? c : muh[s];
+                            const float c = cmf[(par * NW + ww) * BQ + rowS[s]];
+                            muhS[s] = c > muhS[s] ? c : muhS[s];
                         }
                     par ^= 1;   // the next write goes to the other half: readers of this one may lag
                 }
-                if (pos < na) fail = fails_of(m8, muh);
             }
         }
 
+        float muh[QPL];
+#pragma unroll
+        for (int s = 0; s < QPL; ++s) muh[s] = own(muhS, s);
 
         LAMP_PH(3);
         // ---- D. exponentials of tile t against mu_hat
         {
             // the 16-bit maxima buffer of tile t+1 was last read in tile t-1
-            int *cmn = cmi_of(t + 1);
-            for (int i = tid; i < NK * BQ; i += 256) cmn[i] = INT_MIN;
+            float *cmn = cm_of(t + 1);
+            for (int i = tid; i < NK * BQ; i += NT) cmn[i] = NEG_INF;
 
             double sp[QPL], spF[QPL];   // all exponentials / those of 8-bit sub-blocks
             float mu8[QPL];             // the running maximum the 8-bit shifts use
@@ -869,9 +885,6 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 // used; invisible keys get E = 0 by selection.  The row sums are
                 // exact in fp64 in any order (multiples of 2^-41 below 2^7), so
                 // they run as four independent chains.
-                bool full = true;
-#pragma unroll
-                for (int s = 0; s < QPL; ++s) full &= ck0 >= vlo[s] && ck0 + 15 <= vhi[s];
                 auto run8 = [&](auto full_c) {
                     constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
@@ -908,7 +921,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                                       eb[14] | eb[15] << 16};
                     }
                 };
-                if (!wave_any(!full)) run8(std::true_type());
+                if (all_visible(ck0, 16)) run8(std::true_type());
                 else run8(std::false_type());
             } else if (!(F0 >> th & 1u)) {
                 // a stage-1 sub-block outside F0: its one-at-a-time 16-bit codes
@@ -979,54 +992,54 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
 #pragma unroll
                 for (int g = 0; g < NK; ++g) {
                     if (!use[g]) continue;
-                    // the 8 table reads of this member issued before the first is used
+                    const int key0 = k0 + tg[g] * BK + w * 4;
+                    if constexpr (!SIMP) {
+                        if (dbg16 || p.stats) {
+                            float yc[QPL][4];
+#pragma unroll
+                            for (int s = 0; s < QPL; ++s)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) yc[s][i] = y16r[s][g * 4 + i];
+                            obs16(key0, yc);
+                        }
+                    }
+                    // the table reads of this member issued before the first is used
                     uint32_t hl[QPL][4];
 #pragma unroll
                     for (int s = 0; s < QPL; ++s)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float y = y16_value<SIMP>(&y16r[s][g * WPM], i);
+                            const float y = y16r[s][g * 4 + i];
                             if constexpr (SIMP) hl[s][i] = p.sim16[sim_shift_index<11, SIM16_EMIN, SIM16_EMAX>(muh[s], y)];
                             else hl[s][i] = p.exp16hl[ue5m11_code(shift_of(muh[s], y))];
                         }
-                    const int key0 = k0 + tg[g] * BK + w * 4;
-                    if constexpr (!SIMP) {
-                        if (dbg16 || p.stats) {
-                            uint32_t yc[QPL][WPM];
+                    if (!all_visible(key0, 4)) {   // no mass from invisible keys
 #pragma unroll
-                            for (int s = 0; s < QPL; ++s)
+                        for (int s = 0; s < QPL; ++s)
 #pragma unroll
-                                for (int x = 0; x < WPM; ++x) yc[s][x] = y16r[s][g * WPM + x];
-                            obs16(key0, yc);
-                        }
+                            for (int i = 0; i < 4; ++i) hl[s][i] = visible(s, key0 + i) ? hl[s][i] : 0u;
                     }
 #pragma unroll
                     for (int s = 0; s < QPL; ++s) {
-                        uint32_t eh[4], el[4];
                         double ev[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const uint32_t x = hl[s][i];
                             float v;
-                            if constexpr (SIMP) {
-                                eh[i] = x >> 16;
-                                el[i] = x & 0xFFFFu;
-                                v = __builtin_bit_cast(float, x);
-                            } else {
-                                eh[i] = x & 0xFFFFu;
-                                el[i] = x >> 16;
-                                v = bf16_value(eh[i]) + bf16_value(el[i]);   // exact
-                            }
-                            const bool vis = visible(s, key0 + i);
-                            eh[i] = vis ? eh[i] : 0u;
-                            el[i] = vis ? el[i] : 0u;
-                            ev[i] = vis ? (double)v : 0.0;
+                            if constexpr (SIMP) v = __builtin_bit_cast(float, x);
+                            else v = bf16_value(x) + __builtin_bit_cast(float, x & 0xFFFF0000u);   // high + low, exact
+                            ev[i] = (double)v;
                         }
                         sp[s] += (ev[0] + ev[1]) + (ev[2] + ev[3]);
+                        // the high parts of the four (SIM: high halves) and the low ones
+                        constexpr uint32_t SEL_L = 0x05040100u, SEL_H = 0x07060302u;
+                        constexpr uint32_t SEL_HI = SIMP ? SEL_H : SEL_L, SEL_LO = SIMP ? SEL_L : SEL_H;
                         *reinterpret_cast<uint2 *>(ycode + row[s] * YP + (key0 - k0)) =
-                            make_uint2(eh[0] | eh[1] << 16, eh[2] | eh[3] << 16);
+                            make_uint2(__builtin_amdgcn_perm(hl[s][1], hl[s][0], SEL_HI),
+                                       __builtin_amdgcn_perm(hl[s][3], hl[s][2], SEL_HI));
                         *reinterpret_cast<uint2 *>(ylo + row[s] * YP + (key0 - k0)) =
-                            make_uint2(el[0] | el[1] << 16, el[2] | el[3] << 16);
+                            make_uint2(__builtin_amdgcn_perm(hl[s][1], hl[s][0], SEL_LO),
+                                       __builtin_amdgcn_perm(hl[s][3], hl[s][2], SEL_LO));
                     }
                 }
             }
@@ -1081,6 +1094,11 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     need |= !(sf <= (p.tau * omh[s]) * (1.0 - 0x1p-38));
                 }
                 need = wave_any(need);
+                if constexpr (H > 1) {   // of any row part
+                    if (tid % (64 * NW) == 0) votes[hf] = need ? 1u : 0u;
+                    __syncthreads();
+                    need = __builtin_amdgcn_readfirstlane(votes[0] | votes[1]) != 0u;
+                }
             }
             if (need) {
                 // costs c_theta,j = sum_{i in theta, ascending} E (omega_hat - E), own sub-block
@@ -1124,6 +1142,11 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     }
                     if (!wave_any(bad)) feas |= 1u << R;
                 }
+                if constexpr (H > 1) {   // feasible for every row part
+                    if (tid % (64 * NW) == 0) votes[H + hf] = feas;
+                    __syncthreads();
+                    feas = __builtin_amdgcn_readfirstlane(votes[H] & votes[H + 1]);
+                }
                 // smallest recompute set first, then ascending bitmask
                 int chosen = (int)F;
                 bool found = false;
@@ -1142,7 +1165,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     double ds[QPL];
 #pragma unroll
                     for (int s = 0; s < QPL; ++s) ds[s] = 0.0;
-                    auto s2fn = [&](int kc, const uint32_t (&yc)[QPL][WPM]) {
+                    auto s2fn = [&](int kc, const float (&yc)[QPL][4]) {
                         obs16(kc, yc);
 #pragma unroll
                         for (int s = 0; s < QPL; ++s) {
@@ -1157,7 +1180,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                                     uint32_t eh = 0, el = 0;
                                     if (visible(s, key)) {
                                         const float old = bf16_value(src[2 * pp + t2]);
-                                        const float ev = e16_of(muh[s], y16_value<SIMP>(yc[s], 2 * pp + t2), eh, el);
+                                        const float ev = e16_of(muh[s], yc[s][2 * pp + t2], eh, el);
                                         if constexpr (!SIMP) {
                                             ds[s] = ds[s] - (double)old;
                                             ds[s] = ds[s] + (double)ev;
@@ -1176,18 +1199,18 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                     // sub-blocks of R without codes from the fused pass: one batched
                     // recompute, 4 keys of each per wave (as for F0)
                     const uint32_t Rn = prec2 & ~F0;
-                    uint32_t y16b[QPL][4 * WPM];
+                    float y16b[QPL][4 * NK];
                     if (Rn) {
                         const int nr = __builtin_popcount(Rn);
                         const KRows krs = member_keys(k0, Rn);
                         auto rec = [&](auto nkey_c) {
                             constexpr int NKEY = decltype(nkey_c)::value;
-                            uint32_t c[QPL][y16_words<SIMP>(NKEY)];
-                            rec16_keys<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
+                            float c[QPL][NKEY];
+                            rec16_values<D, QPL, NKEY, SIMP, GrpLay>(qr, krs, c);
 #pragma unroll
                             for (int s = 0; s < QPL; ++s)
 #pragma unroll
-                                for (int pp = 0; pp < y16_words<SIMP>(NKEY); ++pp) y16b[s][pp] = c[s][pp];
+                                for (int i = 0; i < NKEY; ++i) y16b[s][i] = c[s][i];
                         };
                         switch (nr) {
                         case 1: rec(std::integral_constant<int, 4>()); break;
@@ -1202,17 +1225,17 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                         // (member of F0) or from the batch above
                         const bool inF0 = F0 >> th & 1u;
                         const int gi = __builtin_popcount((inF0 ? F0 : Rn) & ((1u << th) - 1u));
-                        uint32_t yc[QPL][WPM];
+                        float yc[QPL][4];
 #pragma unroll
                         for (int s = 0; s < QPL; ++s) {
 #pragma unroll
-                            for (int x = 0; x < WPM; ++x) yc[s][x] = inF0 ? y16r[s][x] : y16b[s][x];
+                            for (int x = 0; x < 4; ++x) yc[s][x] = inF0 ? y16r[s][x] : y16b[s][x];
 #pragma unroll
                             for (int g = 1; g < NK; ++g)
                                 if (g == gi)
 #pragma unroll
-                                    for (int x = 0; x < WPM; ++x)
-                                        yc[s][x] = inF0 ? y16r[s][g * WPM + x] : y16b[s][g * WPM + x];
+                                    for (int x = 0; x < 4; ++x)
+                                        yc[s][x] = inF0 ? y16r[s][g * 4 + x] : y16b[s][g * 4 + x];
                         }
                         s2fn(k0 + th * BK + w * 4, yc);
                     }
@@ -1243,6 +1266,8 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             om[s] = __builtin_fma(lam[s], om[s], S[s]);
             mu[s] = muh[s];
         }
+#pragma unroll
+        for (int s = 0; s < HS; ++s) muS[s] = muhS[s];
         if (tid == 0) {
 #pragma unroll
             for (int th = 0; th < NK; ++th)
@@ -1276,7 +1301,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             const bool hi16 = p16 >> c16 & 1u;
 #pragma unroll
             for (int g = 0; g < QG; ++g) {
-                const int off = (g * 32 + l32) * YP + c16 * 16 + half * 8;
+                const int off = (hf * WR + g * 32 + l32) * YP + c16 * 16 + half * 8;
                 const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ycode + off));
 #pragma unroll
                 for (int tt = 0; tt < CT; ++tt)
@@ -1296,7 +1321,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         u32x4 va[CT], vb[CT];
         load_v(0, va);
         {
-            // lambda_hat of row 32g + l32 lives in lane (32g + l32) % 64, slot (32g + l32) / 64
+            // lambda_hat of row 32g + l32 of the part lives in lane (32g + l32) % 64, slot g / 2
             // A row to which the tile added no mass (S = 0: every exponential
             // underflowed against a maximum that overshoots) keeps O and omega
             // in the same ratio, but lambda_hat can lie below fp32's range
@@ -1322,7 +1347,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
             if (wave_any(scale)) {
 #pragma unroll
                 for (int g = 0; g < QG; ++g) {
-                    const float lg = __shfl(lamf[g / 2 < QPL ? g / 2 : 0], ((g & 1) << 5) + l32, 64);
+                    const float lg = __shfl(lamf[g / 2], ((g & 1) << 5) + l32, 64);
 #pragma unroll
                     for (int tt = 0; tt < CT; ++tt)
 #pragma unroll
@@ -1351,10 +1376,10 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
         const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
         for (int g = 0; g < QG; ++g) {
-            const double og = __shfl(om[g / 2 < QPL ? g / 2 : 0], ((g & 1) << 5) + l32, 64);
-            const double pg = pend[w * BQ + g * 32 + l32];
+            const double og = __shfl(om[g / 2], ((g & 1) << 5) + l32, 64);
+            const double pg = pend[w * BQ + hf * WR + g * 32 + l32];
             const float inv = (float)(pg / og);   // pg = 1 unless the last tiles added no mass
-            const int jq = q0 + g * 32 + l32;
+            const int jq = q0 + hf * WR + g * 32 + l32;
             if (jq >= p.N) continue;   // beyond N in a partial last block
             float *orow = p.o + (((size_t)b * p.Hq + h) * p.N + jq) * D + w * CPW;
 #pragma unroll
@@ -1373,7 +1398,7 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
                 if (q0 + row[s] < p.N)
                     p.lse[((size_t)b * p.Hq + h) * p.N + q0 + row[s]] = (float)((double)mu[s] + ::log(om[s]));
         const int ntiles = p.Nk / KPT;
-        for (int tt = tid; tt < ntiles; tt += 256)
+        for (int tt = tid; tt < ntiles; tt += NT)
             if (tt < t_begin || tt > t_end)
                 for (int th = 0; th < NK; ++th) mrow[tt * NK + th] = PREC_INACTIVE;
     }
@@ -1382,60 +1407,84 @@ __global__ __launch_bounds__(256, LAMP_MIN_WAVES) void lamp_fwd16_kernel(FwdPara
 }
 
 // ------------------------------------------------------------------ launcher
-#ifndef LAMP_FWD16_NO_LAUNCHERS
-template <int D, int BQ, int MODE, bool SIMP, bool OBS, bool CMP = false>
-static hipError_t launch_fwd16_obs(const FwdParams &p, hipStream_t s)
+// Whether a call takes 64 query rows per wave (8 waves of a 128-row block, one
+// block per compute unit) rather than 128 (4 waves, two blocks).  A block alone
+// on its compute unit goes through a key tile in about 31 us with 64 rows and
+// 34 with 128 (the second wave of each SIMD fills the waits of the decisions);
+// two side by side need 48 us for a tile of each, so that a loaded device is
+// 1.2x faster with 128 rows, whose blocks are out of step with each other.
+// The line is where the blocks' key tiles, counted in blocks as long as the
+// longest, fill the compute units once: a causal pass of 512 blocks (half as
+// long on average as the longest) takes 1.05 against 1.20 ms, of 640 blocks
+// 1.64 against 1.56; blocks of equal length 0.93 against 1.01 ms at 256 and
+// 1.82 against 1.67 at 512 (d = 128; the same side at d = 256, in the
+// simulation profile and with stochastic rounding).
+inline bool fwd16_wide(const FwdParams &p, int BQ)
 {
-    using C = Cfg16<D, BQ>;
-    auto kern = lamp_fwd16_kernel<D, BQ, MODE, SIMP, OBS, CMP>;
+    const int64_t blocks = (int64_t)p.B * p.Hq * (p.Nq / BQ);
+    const int64_t reach = !p.causal ? 0 : p.window > 0 && p.window < p.N ? p.window : p.N;   // 0: equal lengths
+    return blocks * (2 * (int64_t)p.N - reach) <= 2 * (int64_t)p.N * p.cus;
+}
+
+template <int D, int BQ, int WR, int MODE, bool SIMP, bool OBS, bool CMP = false, bool SR = false>
+static hipError_t launch_fwd16_wr(const FwdParams &p, hipStream_t s)
+{
+    using C = Cfg16<D, BQ, WR>;
+    auto kern = lamp_fwd16_kernel<D, BQ, WR, MODE, SIMP, OBS, CMP, SR>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)(p.B * p.Hq * (p.Nq / BQ)));
-    hipLaunchKernelGGL(kern, grid, dim3(256), C::LDS, s, p);
+    hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS, s, p);
     return hipGetLastError();
 }
 
-template <int D, int BQ, int MODE, bool SIMP>
+template <int D, int BQ, int MODE, bool SIMP, bool SR = false>
 static hipError_t launch_fwd16_mode(const FwdParams &p, hipStream_t s)
 {
-    const bool obs = p.dbg_y8 || p.dbg_y16;
-    // the compact layout: threshold mode, hardware formats, 128-row blocks
-    if constexpr (MODE == MODE_LAMP && !SIMP && BQ == 128)
-        if (p.flags & LAMP_COMPACT)
-            return obs ? launch_fwd16_obs<D, BQ, MODE, SIMP, true, true>(p, s)
-                       : launch_fwd16_obs<D, BQ, MODE, SIMP, false, true>(p, s);
     if constexpr (!SIMP)
-        if (obs) return launch_fwd16_obs<D, BQ, MODE, SIMP, true>(p, s);
-    return launch_fwd16_obs<D, BQ, MODE, SIMP, false>(p, s);
+        if (p.dbg_y8 || p.dbg_y16) {
+            if constexpr (MODE == MODE_LAMP && !SR && BQ == 128)
+                if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, false, true, true>(p, s);
+            return launch_fwd16_wr<D, BQ, 64, MODE, false, true, false, SR>(p, s);
+        }
+    if constexpr (BQ == 128) {
+        // the compact schedule: threshold mode, hardware formats, 128-row blocks
+        if constexpr (MODE == MODE_LAMP && !SIMP && !SR)
+            if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, false, true>(p, s);
+        if (!fwd16_wide(p, BQ)) return launch_fwd16_wr<D, BQ, 128, MODE, SIMP, false, false, SR>(p, s);
+    }
+    return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, false, false, SR>(p, s);
 }
 
 template <int D, int BQ, bool SIMP>
-static hipError_t launch_fwd16_prof(const FwdParams &p, hipStream_t s)
+static hipError_t launch_fwd16(const FwdParams &p, hipStream_t s)
 {
     if (p.mode == MODE_PURE8) return launch_fwd16_mode<D, BQ, MODE_PURE8, SIMP>(p, s);
     if (p.mode == MODE_ALL16) return launch_fwd16_mode<D, BQ, MODE_ALL16, SIMP>(p, s);
     return launch_fwd16_mode<D, BQ, MODE_LAMP, SIMP>(p, s);
 }
 
-template <int D, int BQ>
-static hipError_t launch_fwd16(const FwdParams &p, hipStream_t s)
-{
-    if (p.flags & LAMP_SIM_PROFILE) return launch_fwd16_prof<D, BQ, true>(p, s);
-    return launch_fwd16_prof<D, BQ, false>(p, s);
-}
-
+#ifndef LAMP_FWD16_PART
+// d = 128 with the formats of Sec. 3.3 here; d = 256 and the SIM profile in
+// lamp_fwd16_d256.hip and lamp_fwd16_sim.hip, which the library's build compiles
+// as units of their own (LAMP_SPLIT_UNITS), side by side.
 hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found)
 {
+    if (p.flags & LAMP_SIM_PROFILE) return dispatch_fwd16_sim(D, BQ, p, s, found);
+    if (D == 256) return dispatch_fwd16_d256(BQ, p, s, found);
     *found = true;
-    if (D == 128 && BQ == 64) return launch_fwd16<128, 64>(p, s);
-    if (D == 128 && BQ == 128) return launch_fwd16<128, 128>(p, s);
-    if (D == 256 && BQ == 64) return launch_fwd16<256, 64>(p, s);
-    if (D == 256 && BQ == 128) return launch_fwd16<256, 128>(p, s);
+    if (D == 128 && BQ == 64) return launch_fwd16<128, 64, false>(p, s);
+    if (D == 128 && BQ == 128) return launch_fwd16<128, 128, false>(p, s);
     *found = false;
     return hipSuccess;
 }
-
-#endif // LAMP_FWD16_NO_LAUNCHERS
+#endif
 
 } // namespace lamp
+
+#if !defined(LAMP_FWD16_PART) && !defined(LAMP_SPLIT_UNITS)
+#define LAMP_FWD16_ONE_UNIT
+#include "lamp_fwd16_d256.hip"
+#include "lamp_fwd16_sim.hip"
+#endif

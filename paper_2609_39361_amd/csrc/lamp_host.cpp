@@ -43,6 +43,7 @@ struct DeviceState {
     void *ws = nullptr;          // the library's workspace of this device (grow-only)
     size_t ws_bytes = 0;
     std::vector<void *> retired; // outgrown workspaces, freed by lamp_reserve / lamp_shutdown
+    int cus = 0;                 // compute units
     void *scratch = nullptr;     // device address of this device's fixed scratch (lamp_attn_fwd_noalloc)
 };
 
@@ -70,6 +71,7 @@ int init_locked(int dev)
 {
     DeviceState *st = state_of(dev);
     if (st->ready) return LAMP_OK;
+    HIP_TRY(hipDeviceGetAttribute(&st->cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(hipMalloc(&st->lut8, 256));
     HIP_TRY(hipMalloc(&st->lut8e, 256 * sizeof(uint16_t)));
     HIP_TRY(hipMalloc(&st->exp16, 65536 * sizeof(uint16_t)));
@@ -350,6 +352,7 @@ static int fwd_impl(const uint16_t *q, const uint16_t *k, const uint16_t *v, int
         p.lut8e = st->lut8e;
         p.sim8 = st->sim8;
         p.sim16 = st->sim16;
+        p.cus = st->cus;
     }
     const WsLayout lay = ws_layout(B, Hq, Hkv, Nq, Nk, d, true);
     void *base = nullptr;

@@ -36,6 +36,7 @@ struct FwdParams {
     uint8_t *dbg_y8;          // [B][Hq][dbg_nqb*BQ][Nk] 8-bit codes of the observed query blocks, or null
     uint16_t *dbg_y16;        // the same for the 16-bit codes of recomputed sub-blocks, or null
     int dbg_qb0, dbg_nqb;     // observed query blocks of every (b, h)
+    int cus;                  // compute units of the device
 };
 
 struct LogitsParams {
@@ -60,6 +61,8 @@ hipError_t phase_read(unsigned long long *host, bool reset);
 hipError_t launch_prescale_q(const uint16_t *q, float *qt, int BH, int rows, int D, float scale, hipStream_t s);
 bool fwd_supported(int D, int BQ, int BK, int NK);
 hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
+hipError_t dispatch_fwd16_d256(int BQ, const FwdParams &p, hipStream_t s, bool *found);
+hipError_t dispatch_fwd16_sim(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
 // the general kernel with stochastically rounded 8-bit logits (row layout)

@@ -288,10 +288,10 @@ __global__ __launch_bounds__(64, 2) void logits_sim_kernel(LogitsParams p)
     const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
     float val[16];
     if constexpr (HIGH) {
-        uint32_t w[1][16];
-        rec16_keys<D, 1, 16, true>(qr, keys16<RowLay<D>>(kt), w);
+        float y[1][16];
+        rec16_values<D, 1, 16, true>(qr, keys16<RowLay<D>>(kt), y);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) val[i] = __builtin_bit_cast(float, w[0][i]);
+        for (int i = 0; i < 16; ++i) val[i] = y[0][i];
     } else {
         uint32_t w[1][8], sat[1];
         emu8_any<D, 1, true>(qr, keys16<RowLay<D>>(kt), w, sat);

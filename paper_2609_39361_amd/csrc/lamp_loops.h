@@ -283,62 +283,33 @@ __device__ __forceinline__ void emu8_check(const QRows<QPL> &qr, const KRows &ke
 }
 
 // ---- the SIM profile (Sec. 4.1): FP32 range, 3 / 11 mantissa bits, no saturation
-// Words of 16-bit logits for NKEY keys: e4m11 codes two per word, or, in the
-// SIM profile, FP32 patterns one per word.
-template <bool SIMP>
-constexpr int y16_words(int nkey)
-{
-    return nkey == 0 ? 1 : (SIMP ? nkey : nkey / 2);
-}
-
-// Value of the i-th 16-bit logit of a word array.
-template <bool SIMP>
-__device__ __forceinline__ float y16_value(const uint32_t *w, int i)
-{
-    if constexpr (SIMP) return __builtin_bit_cast(float, w[i]);
-    else return e4m11_value((w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-}
-
 // Two SIM 8-bit logits as their bf16 patterns (exact: 3 mantissa bits).
 __device__ __forceinline__ uint32_t pack_sim8(float a, float b)
 {
     return (__builtin_bit_cast(uint32_t, a) >> 16) | (__builtin_bit_cast(uint32_t, b) & 0xFFFF0000u);
 }
 
-// The 16-bit logits of the FP32 chains in acc, encoded: rounded once to e4m11
-// (codes, two per word) or, in the SIM profile, to 11 mantissa bits (FP32
-// patterns, one per word).
+// The 16-bit logits of the FP32 chains in acc, rounded once to e4m11 (SIM
+// profile: to 11 mantissa bits), as FP32 values.
 template <bool SIMP, int QPL, int NM>
-__device__ __forceinline__ void encode16(const f32x4_t (&acc)[QPL][NM], uint32_t (&c)[QPL][y16_words<SIMP>(4 * NM)])
+__device__ __forceinline__ void round16(const f32x4_t (&acc)[QPL][NM], float (&y)[QPL][4 * NM])
 {
 #pragma unroll
     for (int s = 0; s < QPL; ++s)
 #pragma unroll
-        for (int g = 0; g < NM; ++g) {
-            if constexpr (SIMP) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c[s][4 * g + i] = __builtin_bit_cast(uint32_t, rn_sim<11>(acc[s][g][i]));
-            } else {
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    uint32_t x0, x1;
-                    (void)rn_e4m11_f32(acc[s][g][2 * p], &x0);
-                    (void)rn_e4m11_f32(acc[s][g][2 * p + 1], &x1);
-                    c[s][2 * g + p] = x0 | (x1 << 16);
-                }
-            }
-        }
+        for (int i = 0; i < 4 * NM; ++i)
+            y[s][i] = SIMP ? rn_sim<11>(acc[s][i / 4][i % 4]) : rn_e4m11(acc[s][i / 4][i % 4]);
 }
 
 // The 8-bit logits of the 16 keys ke (EMU; with the overflow check) and the
 // 16-bit logits of NKEY keys kr in one loop that shares the query loads.  The
 // forward kernel uses it to run the 8-bit logits of the next key tile together
 // with the speculative 16-bit recompute of the current one.  a8 receives the
-// 8-bit logits (Y8_WORDS), c16 the 16-bit ones, sat the saturated keys of the
+// 8-bit logits (Y8_WORDS), y16 the 16-bit ones as FP32 values, sat the saturated keys of the
 // 8-bit chunk (0 in the SIM profile, which does not saturate).
 template <int D, int QPL, int NKEY, bool EMU, bool SIMP, class LY = RowLay<D>>
 __device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke, const KRows &kr,
-                                           uint32_t (&a8)[QPL][Y8_WORDS<SIMP>], uint32_t (&c16)[QPL][y16_words<SIMP>(NKEY)],
+                                           uint32_t (&a8)[QPL][Y8_WORDS<SIMP>], float (&y16)[QPL][NKEY > 0 ? NKEY : 1],
                                            uint32_t (&sat)[QPL])
 {
     static_assert(EMU || NKEY > 0, "something to compute");
@@ -369,7 +340,7 @@ __device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke
 #pragma unroll
             for (int g = 0; g < 4; ++g) a8[s][g] = w8[s][g];
     }
-    if constexpr (NM > 0) encode16<SIMP>(acc, c16);
+    if constexpr (NM > 0) round16<SIMP>(acc, y16);
 }
 
 // Y8 of a 16-key chunk in either profile (sat as in emu8_check).
@@ -377,22 +348,31 @@ template <int D, int QPL, bool SIMP, class LY = RowLay<D>>
 __device__ __forceinline__ void emu8_any(const QRows<QPL> &qr, const KRows &ke, uint32_t (&a8)[QPL][Y8_WORDS<SIMP>],
                                          uint32_t (&sat)[QPL])
 {
-    uint32_t none[QPL][1];
+    float none[QPL][1];
     fused_pass<D, QPL, 0, true, SIMP, LY>(qr, ke, ke, a8, none, sat);
 }
 
 // Y16 of NKEY keys (NKEY in {4, 8, 12, 16}) for QPL query rows: the FP32 FMA
 // chain over the channels in ascending order from +0, rounded once to e4m11
-// (saturating).  Lane l of every 16-lane row of kr supplies key (l mod 16) and
-// must hold key (l mod NKEY) (lanes past NKEY are not read).  codes[s][p]
-// receives the e4m11 codes of keys 2p (bits [15:0]) and 2p+1 (SIM profile:
-// rounded to 11 mantissa bits, codes[s][i] the FP32 pattern of key i).
+// (saturating), as FP32 values.  Lane l of every 16-lane row of kr supplies key
+// (l mod 16) and must hold key (l mod NKEY) (lanes past NKEY are not read).
 template <int D, int QPL, int NKEY, bool SIMP = false, class LY = RowLay<D>>
-__device__ __forceinline__ void rec16_keys(const QRows<QPL> &qr, const KRows &kr,
-                                           uint32_t (&codes)[QPL][y16_words<SIMP>(NKEY)])
+__device__ __forceinline__ void rec16_values(const QRows<QPL> &qr, const KRows &kr, float (&y)[QPL][NKEY])
 {
     uint32_t none[QPL][Y8_WORDS<SIMP>], sat[QPL];
-    fused_pass<D, QPL, NKEY, false, SIMP, LY>(qr, kr, kr, none, codes, sat);
+    fused_pass<D, QPL, NKEY, false, SIMP, LY>(qr, kr, kr, none, y, sat);
+}
+
+// The same as e4m11 codes: codes[s][p] holds keys 2p (bits [15:0]) and 2p+1.
+template <int D, int QPL, int NKEY, class LY = RowLay<D>>
+__device__ __forceinline__ void rec16_keys(const QRows<QPL> &qr, const KRows &kr, uint32_t (&codes)[QPL][NKEY / 2])
+{
+    float y[QPL][NKEY];
+    rec16_values<D, QPL, NKEY, false, LY>(qr, kr, y);
+#pragma unroll
+    for (int s = 0; s < QPL; ++s)
+#pragma unroll
+        for (int p = 0; p < NKEY / 2; ++p) codes[s][p] = e4m11_code(y[s][2 * p]) | e4m11_code(y[s][2 * p + 1]) << 16;
 }
 
 // Whether the 16-bit logit of one (query row, key) saturates: its FP32 FMA
