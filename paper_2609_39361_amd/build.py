@@ -32,7 +32,7 @@ SOURCES = ["lamp_kernels.hip", "lamp_fwd.hip", "lamp_fwd16.hip", "lamp_fwd16_sr.
            "lamp_noalloc.hip", "lamp_host.cpp"]
 # parts of lamp_fwd16.hip that this build compiles as units of their own, side
 # by side (-DLAMP_SPLIT_UNITS; without it lamp_fwd16.hip includes them)
-SPLIT_UNITS = ["lamp_fwd16_d256.hip", "lamp_fwd16_sim.hip"]
+SPLIT_UNITS = ["lamp_fwd16_d64.hip", "lamp_fwd16_d256.hip", "lamp_fwd16_sim.hip"]
 
 DPP_VGPR_WAITS = 2
 DPP_EXEC_WAITS = 5

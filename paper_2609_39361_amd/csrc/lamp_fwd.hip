@@ -1,6 +1,6 @@
 // lamp_fwd.hip -- the LampAttention forward kernel for gfx950 (paper Alg. 1),
-// general form: d = 64, or 64-key sub-blocks.  (16-key sub-blocks with d >=
-// 128 take the tile-pipelined kernel of lamp_fwd16.hip.)
+// 64-key sub-blocks.  (16-key sub-blocks take the tile-pipelined kernel of
+// lamp_fwd16.hip.)
 //
 // One workgroup handles one (batch, query head, query block of BQ rows) and
 // walks its key tiles (KPT = BK*NK keys) in order.  Work split:
@@ -917,16 +917,15 @@ bool fwd_supported(int D, int BQ, int BK, int NK)
 bool fwd_grouped(int D, int BQ, int BK, int NK)
 {
     (void)BQ;
-    return BK == 16 && NK == 4 && D >= 128;
+    (void)D;
+    return BK == 16 && NK == 4;
 }
 
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found)
 {
-    // 16-key sub-blocks with d >= 128: the kernel pipelined across key tiles
+    // 16-key sub-blocks: the kernel pipelined across key tiles
     if (fwd_grouped(D, BQ, BK, NK)) return dispatch_fwd16(D, BQ, p, s, found);
     *found = true;
-    LAMP_FWD_CASE(64, 64, 16, 4)
-    LAMP_FWD_CASE(64, 128, 16, 4)
 #define LAMP_FWD_D(D_) LAMP_FWD_CASE(D_, 64, 64, 4) LAMP_FWD_CASE(D_, 128, 64, 4)
     LAMP_FWD_D(64)
     LAMP_FWD_D(128)
@@ -938,12 +937,12 @@ hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipSt
 
 hipError_t dispatch_fwd_sr(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found)
 {
-    // 16-key sub-blocks with d >= 128: the pipelined kernel's SR instantiations
+    // 16-key sub-blocks: the pipelined kernel's SR instantiations
     if (fwd_grouped(D, BQ, BK, NK)) return dispatch_fwd16_sr(D, BQ, p, s, found);
     *found = true;
 #define LAMP_FWD_SR(D_, BQ_, BK_)                                            \
     if (D == D_ && BQ == BQ_ && BK == BK_ && NK == 4) return launch_fwd<D_, BQ_, BK_, 4, true>(p, s);
-#define LAMP_FWD_SR_D(D_) LAMP_FWD_SR(D_, 64, 16) LAMP_FWD_SR(D_, 128, 16) LAMP_FWD_SR(D_, 64, 64) LAMP_FWD_SR(D_, 128, 64)
+#define LAMP_FWD_SR_D(D_) LAMP_FWD_SR(D_, 64, 64) LAMP_FWD_SR(D_, 128, 64)
     LAMP_FWD_SR_D(64)
     LAMP_FWD_SR_D(128)
     LAMP_FWD_SR_D(256)

@@ -1,10 +1,12 @@
 // lamp_fwd16.hip -- the LampAttention forward kernel for 16-key sub-blocks
-// (b_k = 16, N_k = 4, d in {128, 256}), software-pipelined across key tiles.
+// (b_k = 16, N_k = 4), software-pipelined across key tiles.
 //
 // Work split: one workgroup per (batch, query head, query block of BQ rows),
 // of 4 BQ/WR waves.  Wave w = 4 hf + wk holds the WR rows of row part hf, WR/64
 // per lane, with their running state, and owns sub-block wk of every 64-key
-// tile and the output channel slice [wk*D/4, (wk+1)*D/4) of those rows.  The
+// tile and an output slice of those rows: the D/4 channels of index wk, or, at
+// d = 64, 32 channels of half the rows (the matrix instructions of P.V take 32
+// channels).  The
 // decisions concern all BQ rows: the running maxima of every row are small and
 // kept by every wave, so that each derives stage 1 from the same shared data;
 // the sums stay with their row part, and the stage-2 test is put together from
@@ -106,9 +108,11 @@ struct Cfg16 {
     static constexpr int H = BQ / WR;         // row parts
     static constexpr int QPL = WR / 64;       // query rows per lane
     static constexpr int NT = 64 * NW * H;    // threads
-    static constexpr int CPW = D / NW;        // output channels per wave
+    static constexpr int CPW = D / NW >= 32 ? D / NW : 32;   // output channels per wave
+    static constexpr int NCW = D / CPW;       // channel slices
+    static constexpr int RPV = WR * NCW / NW; // rows of a wave's output slice
     static constexpr int CT = CPW / 32;       // 32-channel MFMA tiles per wave
-    static constexpr int QG = WR / 32;        // 32-row MFMA groups of a row part
+    static constexpr int QG = RPV / 32;       // 32-row MFMA groups of the slice
     static constexpr int YP = KPT + 8;        // LDS pitch (u16) of the code rows
     static constexpr size_t YB = (size_t)BQ * YP * 2;
     static constexpr size_t OFF_Y = 0;                                  // u16 [2][BQ][YP]
@@ -127,7 +131,7 @@ struct Cfg16 {
     static constexpr size_t OFF_PD = (OFF_ST + (size_t)ST_N * 4 + 7) / 8 * 8;   // f64 [NW][BQ] pending rescale factors
     static constexpr size_t LDS = OFF_PD + (size_t)NW * BQ * 8;
     static_assert((BQ == 64 || BQ == 128) && (WR == 64 || WR == BQ), "64 or 128 query rows per block");
-    static_assert(CPW % 32 == 0, "whole 32-channel tiles per wave");
+    static_assert(CPW % 32 == 0 && RPV % 32 == 0, "whole 32-channel tiles and 32-row groups per wave");
 };
 
 // An e4m11 / e4m3 value as exact fixed point in units of 2^-17 (|y| < 2^9).
@@ -196,7 +200,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
 {
     using C = Cfg16<D, BQ, WR>;
     constexpr int NK = C::NK, BK = C::BK, KPT = C::KPT, NW = C::NW, CPW = C::CPW;
-    constexpr int CT = C::CT, QG = C::QG, YP = C::YP, H = C::H, NT = C::NT;
+    constexpr int CT = C::CT, QG = C::QG, YP = C::YP, H = C::H, NT = C::NT, NCW = C::NCW;
     constexpr int QPL = C::QPL;
     constexpr int HS = MODE == MODE_LAMP ? BQ / 64 : QPL;   // rows per lane whose running maximum a wave keeps
 
@@ -218,7 +222,8 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
 
     const int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // wave-uniform
-    const int w = wv & (NW - 1), hf = wv / NW;   // sub-block and channel slice, row part
+    const int w = wv & (NW - 1), hf = wv / NW;   // sub-block, row part
+    const int cw = w % NCW, r0 = w / NCW * C::RPV;   // output slice: channels, first row within the part
     LAMP_PH_INIT
     const int nqb = p.Nq / BQ;   // query blocks per head (the last may be partial)
     // Block order.  Workgroups are handed to the 8 XCDs round-robin (block i to
@@ -308,6 +313,8 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         muS[g] = NEG_INF;
     }
     auto own = [&](const float (&x)[HS], int s) { return HS == QPL || hf == 0 ? x[s] : x[HS - QPL + s]; };
+    // the slot of the rows of output group g
+    auto slot_of = [&](const auto &x, int g) { return x[QPL == 1 || r0 + g * 32 < 64 ? 0 : QPL - 1]; };
     float mu[QPL];
     double om[QPL];
 #pragma unroll
@@ -1292,7 +1299,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         auto load_v = [&](int c16, u32x4 (&a)[CT]) {
 #pragma unroll
             for (int tt = 0; tt < CT; ++tt)
-                a[tt] = *reinterpret_cast<const u32x4 *>(vtbase + (size_t)(w * CPW + tt * 32 + l32) * p.Nk + k0 +
+                a[tt] = *reinterpret_cast<const u32x4 *>(vtbase + (size_t)(cw * CPW + tt * 32 + l32) * p.Nk + k0 +
                                                          c16 * 16 + half * 8);
         };
         auto pv_chunk = [&](int c16, const u32x4 (&a)[CT]) {
@@ -1301,7 +1308,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
             const bool hi16 = p16 >> c16 & 1u;
 #pragma unroll
             for (int g = 0; g < QG; ++g) {
-                const int off = (hf * WR + g * 32 + l32) * YP + c16 * 16 + half * 8;
+                const int off = (hf * WR + r0 + g * 32 + l32) * YP + c16 * 16 + half * 8;
                 const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ycode + off));
 #pragma unroll
                 for (int tt = 0; tt < CT; ++tt)
@@ -1321,7 +1328,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         u32x4 va[CT], vb[CT];
         load_v(0, va);
         {
-            // lambda_hat of row 32g + l32 of the part lives in lane (32g + l32) % 64, slot g / 2
+            // lambda_hat of row r of the part lives in lane r % 64, slot r / 64
             // A row to which the tile added no mass (S = 0: every exponential
             // underflowed against a maximum that overshoots) keeps O and omega
             // in the same ratio, but lambda_hat can lie below fp32's range
@@ -1347,7 +1354,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
             if (wave_any(scale)) {
 #pragma unroll
                 for (int g = 0; g < QG; ++g) {
-                    const float lg = __shfl(lamf[g / 2], ((g & 1) << 5) + l32, 64);
+                    const float lg = __shfl(slot_of(lamf, g), ((r0 + g * 32) & 63) + l32, 64);
 #pragma unroll
                     for (int tt = 0; tt < CT; ++tt)
 #pragma unroll
@@ -1376,12 +1383,12 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
         for (int g = 0; g < QG; ++g) {
-            const double og = __shfl(om[g / 2], ((g & 1) << 5) + l32, 64);
-            const double pg = pend[w * BQ + hf * WR + g * 32 + l32];
+            const double og = __shfl(slot_of(om, g), ((r0 + g * 32) & 63) + l32, 64);
+            const double pg = pend[w * BQ + hf * WR + r0 + g * 32 + l32];
             const float inv = (float)(pg / og);   // pg = 1 unless the last tiles added no mass
-            const int jq = q0 + hf * WR + g * 32 + l32;
+            const int jq = q0 + hf * WR + r0 + g * 32 + l32;
             if (jq >= p.N) continue;   // beyond N in a partial last block
-            float *orow = p.o + (((size_t)b * p.Hq + h) * p.N + jq) * D + w * CPW;
+            float *orow = p.o + (((size_t)b * p.Hq + h) * p.N + jq) * D + cw * CPW;
 #pragma unroll
             for (int tt = 0; tt < CT; ++tt)
 #pragma unroll
@@ -1444,13 +1451,13 @@ static hipError_t launch_fwd16_mode(const FwdParams &p, hipStream_t s)
 {
     if constexpr (!SIMP)
         if (p.dbg_y8 || p.dbg_y16) {
-            if constexpr (MODE == MODE_LAMP && !SR && BQ == 128)
+            if constexpr (MODE == MODE_LAMP && !SR && BQ == 128 && D >= 128)
                 if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, false, true, true>(p, s);
             return launch_fwd16_wr<D, BQ, 64, MODE, false, true, false, SR>(p, s);
         }
     if constexpr (BQ == 128) {
-        // the compact schedule: threshold mode, hardware formats, 128-row blocks
-        if constexpr (MODE == MODE_LAMP && !SIMP && !SR)
+        // the compact schedule: threshold mode, hardware formats, 128-row blocks, d >= 128
+        if constexpr (MODE == MODE_LAMP && !SIMP && !SR && D >= 128)
             if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, false, true>(p, s);
         if (!fwd16_wide(p, BQ)) return launch_fwd16_wr<D, BQ, 128, MODE, SIMP, false, false, SR>(p, s);
     }
@@ -1466,12 +1473,13 @@ static hipError_t launch_fwd16(const FwdParams &p, hipStream_t s)
 }
 
 #ifndef LAMP_FWD16_PART
-// d = 128 with the formats of Sec. 3.3 here; d = 256 and the SIM profile in
-// lamp_fwd16_d256.hip and lamp_fwd16_sim.hip, which the library's build compiles
+// d = 128 with the formats of Sec. 3.3 here; d = 64, d = 256 and the SIM profile
+// in lamp_fwd16_d64.hip, lamp_fwd16_d256.hip and lamp_fwd16_sim.hip, which the library's build compiles
 // as units of their own (LAMP_SPLIT_UNITS), side by side.
 hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found)
 {
     if (p.flags & LAMP_SIM_PROFILE) return dispatch_fwd16_sim(D, BQ, p, s, found);
+    if (D == 64) return dispatch_fwd16_d64(BQ, p, s, found);
     if (D == 256) return dispatch_fwd16_d256(BQ, p, s, found);
     *found = true;
     if (D == 128 && BQ == 64) return launch_fwd16<128, 64, false>(p, s);
@@ -1485,6 +1493,7 @@ hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool
 
 #if !defined(LAMP_FWD16_PART) && !defined(LAMP_SPLIT_UNITS)
 #define LAMP_FWD16_ONE_UNIT
+#include "lamp_fwd16_d64.hip"
 #include "lamp_fwd16_d256.hip"
 #include "lamp_fwd16_sim.hip"
 #endif

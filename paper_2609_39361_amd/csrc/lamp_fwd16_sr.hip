@@ -15,6 +15,8 @@ static hipError_t launch_fwd16_sr(const FwdParams &p, hipStream_t s)
 hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found)
 {
     *found = true;
+    if (D == 64 && BQ == 64) return launch_fwd16_sr<64, 64>(p, s);
+    if (D == 64 && BQ == 128) return launch_fwd16_sr<64, 128>(p, s);
     if (D == 128 && BQ == 64) return launch_fwd16_sr<128, 64>(p, s);
     if (D == 128 && BQ == 128) return launch_fwd16_sr<128, 128>(p, s);
     if (D == 256 && BQ == 64) return launch_fwd16_sr<256, 64>(p, s);

@@ -61,6 +61,7 @@ hipError_t phase_read(unsigned long long *host, bool reset);
 hipError_t launch_prescale_q(const uint16_t *q, float *qt, int BH, int rows, int D, float scale, hipStream_t s);
 bool fwd_supported(int D, int BQ, int BK, int NK);
 hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
+hipError_t dispatch_fwd16_d64(int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_d256(int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sim(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);

@@ -27,6 +27,7 @@ def L():
 @pytest.mark.parametrize("tau", [math.inf, 0.5, 2.0 ** -5, 0.0])
 @pytest.mark.parametrize("d,N,causal,window,flags,seed", [
     (128, 1, 1, 0, 0, None), (128, 130, 1, 0, 0, None), (128, 333, 0, 0, 0, None), (128, 300, 1, 70, 0, None),
+    (64, 130, 1, 0, 0, None), (64, 200, 0, 0, 0, None), (64, 300, 1, 70, 0, None), (64, 140, 1, 0, 0, 11),
     (256, 200, 1, 0, 0, None), (256, 257, 1, 100, 0, None), (128, 200, 1, 0, SIM, None), (256, 140, 0, 0, SIM, None),
     (128, 200, 1, 0, 1, None), (128, 200, 1, 0, 2, None), (128, 140, 1, 0, 0, 11)])
 def test_large_grid_equals_its_parts(L, d, N, causal, window, flags, seed, tau):
