@@ -4,27 +4,33 @@
 //
 // One workgroup handles one (batch, query head, query block of BQ rows) and
 // walks its key tiles (KPT = BK*NK keys) in order.  Work split:
-//   * every lane holds QPL = BQ/64 query rows (rows lane and lane+64), and
-//     every wave keeps the running state (mu, omega) of all BQ rows -- the
-//     state is small and every wave derives it from the same shared data, so
-//     it stays identical across waves without extra traffic;
-//   * wave w owns SPW = NK/NW consecutive key sub-blocks of each tile: it
-//     computes their 8-bit logits and exponentials and publishes per-row
-//     partial results in LDS;
-//   * wave w owns the channel slice [w*CPW, (w+1)*CPW) of the output and
-//     accumulates O^T = V^T E for that slice on the bf16 matrix cores.
+//   * wave 4 hf + w of BQ/16 holds the 64 query rows of row part hf, one per
+//     lane, with their running state; the decisions concern all BQ rows: the
+//     running maxima of every row are small and kept by every wave, the sums
+//     stay with their row part, and the stage-2 test is put together from the
+//     parts' votes in LDS.  (The codes of a 128-row block leave room for one
+//     workgroup per compute unit: with 128 rows per wave each SIMD had a
+//     single wave to issue from.)
+//   * wave w of a part owns key sub-block w of each tile: it computes its 8-bit
+//     logits and exponentials and publishes per-row partial results in LDS;
+//   * and an output slice of the part's rows: the D/4 channels of index w, or,
+//     at d = 64, 32 channels of half the rows, accumulated as O^T = V^T E on the
+//     bf16 matrix cores.
 // Per tile (Alg. 1 inner loop):
-//   1. 8-bit logits of the own sub-blocks, column maxima m8 -> LDS;
-//   2. stage 1 (Sec. 3.1, Eq. (7)): threats, sort, sequential margin tests on
-//      the shared m8; a failing sub-block is recomputed in 16 bits by all
-//      waves (KPW keys each) and raises mu_hat;
-//   3. exponentials of the own sub-blocks against mu_hat (8-bit LUT in LDS,
-//      16-bit table in global memory), written in place of the logit codes,
-//      16-bit ones as exact bf16 high and low parts; partial row sums -> LDS;
-//      lambda_hat, omega_hat;
+//   1. 8-bit logits of the own sub-block, column maxima m8 -> LDS;
+//   2. stage 1 (Sec. 3.1, Eq. (7)): the sub-blocks that fail the margin test
+//      against the running maximum mu (the set F0; nearly always the ones
+//      stage 1 recomputes, since mu_hat only grows) are recomputed in 16 bits
+//      together, BK/4 keys of each per wave, before the sequential tests on the
+//      shared maxima; one outside F0 that fails against a larger mu_hat is
+//      recomputed on its own;
+//   3. exponentials of the own sub-block against mu_hat (8-bit LUT in LDS,
+//      16-bit table of exact bf16 high and low parts in global memory), written
+//      in place of the logit codes; partial row sums -> LDS; lambda_hat,
+//      omega_hat;
 //   4. stage 2 (Eq. (8)): per-sub-block costs -> LDS, feasibility of every
-//      candidate recompute set evaluated identically by every wave, 16-bit
-//      recompute of the chosen sub-blocks shared by all waves;
+//      candidate recompute set evaluated identically by every wave of a part,
+//      16-bit recompute of the chosen sub-blocks shared by all waves;
 //   5. omega, mu update; O^T <- O^T diag(lambda_hat) + V^T E.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -36,10 +42,6 @@
 #include "lamp_sr.h"
 #include "lamp_stats.h"
 
-#ifndef LAMP_MIN_WAVES
-#define LAMP_MIN_WAVES 2   // minimum waves per SIMD requested from the register allocator
-#endif
-
 namespace lamp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -50,31 +52,34 @@ enum { PREC_LOW = 0, PREC_S1 = 1, PREC_S2 = 2, PREC_INACTIVE = 3 };
 
 template <int D, int BQ, int BK, int NK>
 struct Cfg {
-    static constexpr int QPL = BQ / 64;                    // query rows per lane
+    static constexpr int H = BQ / 64;                      // row parts
     static constexpr int KPT = BK * NK;                    // keys per tile
     static constexpr int NCH = KPT / 16;                   // 16-key chunks per tile
-    static constexpr int NW = NK < D / 32 ? NK : D / 32;   // waves
-    static constexpr int SPW = NK / NW;                    // sub-blocks per wave
-    static constexpr int CPW = D / NW;                     // output channels per wave
+    static constexpr int NW = NK;                          // waves of a row part
+    static constexpr int NT = 64 * NW * H;                 // threads
+    static constexpr int CPW = D / NW >= 32 ? D / NW : 32; // output channels per wave
+    static constexpr int NCW = D / CPW;                    // channel slices
+    static constexpr int RPV = 64 * NCW / NW;              // rows of a wave's output slice
     static constexpr int CT = CPW / 32;                    // 32-channel MFMA tiles per wave
-    static constexpr int QG = BQ / 32;                     // 32-row MFMA groups
+    static constexpr int QG = RPV / 32;                    // 32-row MFMA groups of the slice
     static constexpr int KPW = BK / NW;                    // keys per wave in a shared 16-bit recompute
     static constexpr int YP = KPT + 8;                     // LDS pitch (u16) of the code rows
     static constexpr size_t OFF_Y = 0;
-    static constexpr size_t OFF_YL = OFF_Y + (size_t)BQ * YP * 2;        // low bf16 parts of E16
+    static constexpr size_t OFF_YL = OFF_Y + (size_t)BQ * YP * 2;        // 16-bit codes, then low bf16 parts of E16
     static constexpr size_t OFF_LUT = OFF_YL + (size_t)BQ * YP * 2;
     static constexpr size_t OFF_M8 = OFF_LUT + 512;                       // f32 [NK][BQ]
     static constexpr size_t OFF_CM = OFF_M8 + (size_t)NK * BQ * 4;       // f32 [NK][BQ] + [2][NW][BQ]
     static constexpr size_t OFF_SP = OFF_CM + (size_t)(NK + 2 * NW) * BQ * 4;   // f64 [2][NW][BQ]
     static constexpr size_t OFF_CO = OFF_SP + (size_t)2 * NW * BQ * 8;   // f64 [NK][BQ]
     static constexpr size_t OFF_ED = OFF_CO + (size_t)NK * BQ * 8;       // f64 [EXPDOC_NK]
-    static constexpr size_t OFF_ST = OFF_ED + (size_t)EXPDOC_NK * 8;     // u32 [ST_N] statistics
-    static constexpr size_t OFF_PD = OFF_ST + (size_t)ST_N * 4;          // f64 [NW][BQ] pending rescale factors
+    static constexpr size_t OFF_VT = OFF_ED + (size_t)EXPDOC_NK * 8;     // u32 [2][2] votes of the row parts
+    static constexpr size_t OFF_ST = OFF_VT + 16;                        // u32 [ST_N] statistics
+    static constexpr size_t OFF_PD = (OFF_ST + (size_t)ST_N * 4 + 7) / 8 * 8;   // f64 [NW][BQ] pending rescale factors
     static constexpr size_t LDS = OFF_PD + (size_t)NW * BQ * 8;
     static_assert(BQ == 64 || BQ == 128, "64 or 128 query rows per block");
-    static_assert(BK % 16 == 0 && NK <= 4 && NK % NW == 0, "sub-blocks of 16-key chunks, at most 4 per tile");
-    static_assert(CPW % 32 == 0, "whole 32-channel tiles per wave");
-    static_assert(KPW == 4 || KPW == 8 || KPW % 16 == 0, "recompute split in 4, 8 or multiples of 16 keys");
+    static_assert(BK % 16 == 0 && NK == 4, "sub-blocks of 16-key chunks, one per wave");
+    static_assert(CPW % 32 == 0 && RPV % 32 == 0, "whole 32-channel tiles and 32-row groups per wave");
+    static_assert(KPW % 16 == 0, "recompute split in multiples of 16 keys");
 };
 
 // SR: the 8-bit logits with stochastic rounding (lamp_sr.h) in place of
@@ -83,30 +88,35 @@ struct Cfg {
 // p.dbg_y16), kept apart so that the stores do not change the register
 // allocation of the others.
 template <int D, int BQ, int BK, int NK, bool SR, bool OBS>
-__global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) void lamp_fwd_kernel(FwdParams p)
+__global__ __launch_bounds__((Cfg<D, BQ, BK, NK>::NT), 2) void lamp_fwd_kernel(FwdParams p)
 {
     using C = Cfg<D, BQ, BK, NK>;
-    constexpr int QPL = C::QPL, KPT = C::KPT, NCH = C::NCH, NW = C::NW, SPW = C::SPW, CPW = C::CPW;
-    constexpr int CT = C::CT, QG = C::QG, YP = C::YP, KPW = C::KPW;
+    constexpr int KPT = C::KPT, NCH = C::NCH, NW = C::NW, CPW = C::CPW, NCW = C::NCW, NT = C::NT;
+    constexpr int CT = C::CT, QG = C::QG, YP = C::YP, KPW = C::KPW, H = C::H;
+    constexpr int QPL = 1;         // own query rows per lane
+    constexpr int HS = H;          // rows per lane whose running maximum a wave keeps
     constexpr int CPS = BK / 16;   // chunks per sub-block
 
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *ycode = reinterpret_cast<uint16_t *>(smem + C::OFF_Y);   // [BQ][YP] logit codes, then E (bf16 bits;
                                                                        // 16-bit sub-blocks: high part)
-    uint16_t *ylo = reinterpret_cast<uint16_t *>(smem + C::OFF_YL);    // [BQ][YP] low bf16 part of E16
+    uint16_t *ylo = reinterpret_cast<uint16_t *>(smem + C::OFF_YL);    // [BQ][YP] 16-bit logit codes, then low part of E16
     uint16_t *lut = reinterpret_cast<uint16_t *>(smem + C::OFF_LUT);   // [256] 8-bit exp (bf16 bits)
     float *m8s = reinterpret_cast<float *>(smem + C::OFF_M8);          // [NK][BQ] 8-bit column maxima
-    float *cms = reinterpret_cast<float *>(smem + C::OFF_CM);          // [NK][BQ] 16-bit column maxima (threshold 0)
+    float *cms = reinterpret_cast<float *>(smem + C::OFF_CM);          // [NK][BQ] 16-bit column maxima
     float *cmf = cms + NK * BQ;   // [2][NW][BQ] per-wave maxima of a shared recompute, by iteration parity
     double *sps = reinterpret_cast<double *>(smem + C::OFF_SP);        // [NW][BQ] partial row sums of E
     double *spf = sps + NW * BQ;                                       // [NW][BQ] the same over 8-bit sub-blocks
     double *cst_lds = reinterpret_cast<double *>(smem + C::OFF_CO);    // [NK][BQ] stage-2 costs
     double *edk = reinterpret_cast<double *>(smem + C::OFF_ED);        // exp_doc constants
+    uint32_t *votes = reinterpret_cast<uint32_t *>(smem + C::OFF_VT);  // [2][2] stage 2: needed, feasible sets
     uint32_t *stl = reinterpret_cast<uint32_t *>(smem + C::OFF_ST);    // [ST_N] statistics (p.stats)
     double *pend = reinterpret_cast<double *>(smem + C::OFF_PD);        // [NW][BQ] pending factors (step 5)
 
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // w is wave-uniform
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // wave-uniform
+    const int w = wv & (NW - 1), hf = wv / NW;   // sub-block, row part
+    const int cw = w % NCW, r0 = w / NCW * C::RPV;   // output slice: channels, first row within the part
     const int nqb = p.Nq / BQ;   // query blocks per head (the last may be partial)
     const int BH = p.B * p.Hq;
     const int qb = nqb - 1 - (int)(blockIdx.x / BH);   // longest blocks first under causality
@@ -119,10 +129,10 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
     // per-slot row, query index and visible key range [vlo, vhi]
     int row[QPL], vlo[QPL], vhi[QPL];
     QRows<QPL> qr;
-    qr.off = (uint32_t)lane * D * 4u;
+    qr.off = (uint32_t)lane * 16u;   // grouped layout: 64-row blocks stored [group][row][4]
 #pragma unroll
     for (int s = 0; s < QPL; ++s) {
-        row[s] = s * 64 + lane;
+        row[s] = hf * 64 + lane;
         const int j = q0 + row[s];
         vlo[s] = p.window > 0 ? (j - p.window + 1 > 0 ? j - p.window + 1 : 0) : 0;
         vhi[s] = p.causal ? j : p.N - 1;
@@ -130,21 +140,21 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             vlo[s] = p.N;
             vhi[s] = -1;
         }
-        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + 64 * s) * D;   // zero-padded rows, in bounds
+        qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + 64 * hf) * D;   // zero-padded rows, in bounds
     }
     // visible key range of the whole block
     const int bv_lo = p.window > 0 ? (q0 - p.window + 1 > 0 ? q0 - p.window + 1 : 0) : 0;
     const int bv_hi = p.causal ? (q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1) : p.N - 1;
     const int t_begin = bv_lo / KPT, t_end = bv_hi / KPT;
 
-    const float *kt32 = p.kt32 + ((size_t)b * p.Hkv + hk) * (size_t)p.Nk * D;   // fp32 keys [Nk][D]
+    const float *kt32 = p.kt32 + ((size_t)b * p.Hkv + hk) * (size_t)p.Nk * D;   // fp32 keys, grouped: 16-key blocks [group][key][4]
     const uint16_t *vtbase = p.vt + ((size_t)b * p.Hkv + hk) * (size_t)D * p.Nk;   // V^T [D][Nk]
     uint8_t *mrow = p.mask + (((size_t)b * p.Hq + h) * nqb + qb) * (size_t)(p.Nk / BK);
 
-    for (int i = tid; i < 256; i += 64 * NW) lut[i] = p.lut8e[i];
+    for (int i = tid; i < 256; i += NT) lut[i] = p.lut8e[i];
     if (tid < EXPDOC_NK) edk[tid] = EXPDOC_K[tid];
     if (tid < ST_N) stl[tid] = 0u;
-    for (int i = tid; i < NW * BQ; i += 64 * NW) pend[i] = 1.0;
+    for (int i = tid; i < NW * BQ; i += NT) pend[i] = 1.0;
     // logit observables (tests): this query block is observed (uniform)
     const bool dbg_blk = qb >= p.dbg_qb0 && qb < p.dbg_qb0 + p.dbg_nqb;
     const bool dbg8 = OBS && p.dbg_y8 != nullptr && dbg_blk, dbg16 = OBS && p.dbg_y16 != nullptr && dbg_blk;
@@ -152,6 +162,14 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
         return ((((size_t)b * p.Hq + h) * p.dbg_nqb + (qb - p.dbg_qb0)) * BQ + row[s]) * (size_t)p.Nk;
     };
 
+    // the running maxima of every row of the block, and the own row's
+    int rowS[HS];
+    float muS[HS];
+#pragma unroll
+    for (int g = 0; g < HS; ++g) {
+        rowS[g] = g * 64 + lane;
+        muS[g] = NEG_INF;
+    }
     float mu[QPL];     // running maxima (e4m11 or e4m3 values)
     double om[QPL];    // running sums omega
 #pragma unroll
@@ -168,90 +186,87 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             for (int r = 0; r < 16; ++r) acc[g][t][r] = 0.0f;
 
     auto visible = [&](int s, int key) { return key >= vlo[s] && key <= vhi[s]; };
+    // every key of [key0, key0 + n) visible to every row of this wave (uniform)
+    const int all_lo = p.window > 0 ? q0 + hf * 64 + 64 - p.window : 0;
+    const int all_hi = q0 + hf * 64 + 64 > p.N ? -1 : p.causal ? q0 + hf * 64 : p.N - 1;
+    auto all_visible = [&](int key0, int n) { return key0 >= all_lo && key0 + n - 1 <= all_hi; };
+    const int q_last = q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1;
+    // the margin test of one column against mu_hat (Eq. (7)): mu_hat = -inf
+    // enters as a finite number below every logit, so that a visible logit
+    // fails and a column without one (m8 = -inf) passes, as required
+    auto fails = [&](float m8v, float mhv) {
+        const double m = (double)__builtin_fmaxf(mhv, -0x1p100f);
+        return !(m > __builtin_fma(__builtin_fabs(m), p.delta, (double)m8v));
+    };
 
-    // Observables of the 16-bit logits of 2*NWD keys from kc of every slot
-    // (codes two per word): their codes for the tests, and the saturated ones
-    // among the visible keys whose code is the largest e4m11 magnitude (the
-    // FP32 chain rerun for those alone).
-    auto obs16 = [&](int kc, const auto &yc) {
-        constexpr int NWD = sizeof(yc[0]) / sizeof(uint32_t);   // words per slot
+    // Observables of the 16-bit logits of 16 keys from kc: their codes for the
+    // tests, and the saturated ones among the visible keys whose value is the
+    // largest e4m11 magnitude (the FP32 chain rerun for those alone).
+    auto obs16 = [&](int kc, const float (&y)[QPL][16]) {
         if (dbg16) {
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
-#pragma unroll
-                for (int x = 0; x < NWD; ++x) {
-                    const uint32_t lo = visible(s, kc + 2 * x) ? (yc[s][x] & 0xFFFFu) : 0xFFFFu;
-                    const uint32_t hi = visible(s, kc + 2 * x + 1) ? (yc[s][x] >> 16) : 0xFFFFu;
-                    *reinterpret_cast<uint32_t *>(p.dbg_y16 + dbg_off(s) + kc + 2 * x) = lo | (hi << 16);
-                }
+            for (int x = 0; x < 8; ++x) {
+                const uint32_t lo = visible(0, kc + 2 * x) ? e4m11_code(y[0][2 * x]) : 0xFFFFu;
+                const uint32_t hi = visible(0, kc + 2 * x + 1) ? e4m11_code(y[0][2 * x + 1]) : 0xFFFFu;
+                *reinterpret_cast<uint32_t *>(p.dbg_y16 + dbg_off(0) + kc + 2 * x) = lo | (hi << 16);
+            }
         }
         if (p.stats) {
-            static_assert(QPL * 2 * NWD <= 32, "one bit per slot and key");
-            uint32_t atmax = 0;   // bit s * 2NWD + i: slot s, key kc + i
+            uint32_t atmax = 0;   // bit i: key kc + i
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
-#pragma unroll
-                for (int i = 0; i < 2 * NWD; ++i) {
-                    const uint32_t code = (yc[s][i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-                    atmax |= ((code & 0x7FFFu) == 0x7FFFu && visible(s, kc + i) ? 1u : 0u) << (s * 2 * NWD + i);
-                }
+            for (int i = 0; i < 16; ++i)
+                atmax |= (__builtin_fabsf(y[0][i]) == 511.875f && visible(0, kc + i) ? 1u : 0u) << i;
             if (wave_any(atmax != 0u)) {
                 uint32_t n = 0;
-                for (uint32_t m = atmax; m; m &= m - 1) {
-                    const int bit = __builtin_ctz(m);
-                    const float *qrow = qr.row(0);
-#pragma unroll
-                    for (int s = 1; s < QPL; ++s) qrow = bit / (2 * NWD) == s ? qr.row(s) : qrow;
-                    n += y16_saturates<D, RowLay<D>>(qrow, kt32 + (size_t)(kc + bit % (2 * NWD)) * D) ? 1u : 0u;
-                }
+                for (uint32_t m = atmax; m; m &= m - 1)
+                    n += y16_saturates<D, GrpLay>(qr.row(0), kt32 + (size_t)kc * D + 4 * __builtin_ctz(m)) ? 1u : 0u;
                 if (n) atomicAdd(&stl[ST_SAT16], n);
             }
         }
     };
 
-    // 16-bit recompute of sub-block th shared by all waves: wave w takes keys
-    // [key0, key0 + KPW) with key0 = k0 + th*BK + w*KPW.  For every 16-key
-    // group (or the 4 / 8 keys) fn(key, nk, codes) receives the e4m11 codes.
+    // 16-bit recompute of sub-block th shared by all waves: wave w of a part
+    // takes keys [key0, key0 + KPW) with key0 = k0 + th*BK + w*KPW for its rows.
+    // For every 16-key group fn(key, logits) receives the values.
     auto shared16 = [&](int k0, int th, auto fn) {
         const int key0 = k0 + th * BK + w * KPW;
         if (key0 > bv_hi || key0 + KPW - 1 < bv_lo) return;   // nothing visible in the block
-        if constexpr (KPW >= 16) {
-            for (int ch = 0; ch < KPW / 16; ++ch) {
-                const int kc = key0 + ch * 16;
-                uint32_t yc[QPL][8];
-                rec16_keys<D, QPL, 16>(qr, keys16<RowLay<D>>(kt32 + (size_t)kc * D), yc);
-                fn(kc, yc);
-            }
-        } else {
-            uint32_t yc[QPL][KPW / 2];
-            rec16_keys<D, QPL, KPW>(qr, keys_at<RowLay<D>>(kt32 + (size_t)key0 * D, (uint32_t)((lane & 15) % KPW) * D), yc);
-            fn(key0, yc);
+        for (int ch = 0; ch < KPW / 16; ++ch) {
+            const int kc = key0 + ch * 16;
+            float y[QPL][16];
+            rec16_values<D, QPL, 16, false, GrpLay>(qr, keys16<GrpLay>(kt32 + (size_t)kc * D), y);
+            fn(kc, y);
         }
     };
-    // write n = 4, 8 or 16 u16 codes (packed two per word) at row r, key offset ko
-    auto put_codes = [&](uint16_t *arr, int r, int ko, const uint32_t *cw, int nw) {
-        uint16_t *dst = arr + r * YP + ko;
-        if (nw == 2) {
-            *reinterpret_cast<uint2 *>(dst) = make_uint2(cw[0], cw[1]);
-        } else {
-            for (int t = 0; t < nw; t += 4)
-                *reinterpret_cast<u32x4 *>(dst + 2 * t) = u32x4{cw[t], cw[t + 1], cw[t + 2], cw[t + 3]};
-        }
+    // codes of 16 logits from key kc of the tile at k0 into ylo, for the
+    // exponentials; returns the maximum over the visible ones
+    auto keep16 = [&](int k0, int kc, const float (&y)[QPL][16]) {
+        uint32_t c[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) c[x] = e4m11_code(y[0][2 * x]) | e4m11_code(y[0][2 * x + 1]) << 16;
+        u32x4 *dst = reinterpret_cast<u32x4 *>(ylo + row[0] * YP + (kc - k0));
+        dst[0] = u32x4{c[0], c[1], c[2], c[3]};
+        dst[1] = u32x4{c[4], c[5], c[6], c[7]};
+        const bool full = all_visible(kc, 16);
+        float m = NEG_INF;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = __builtin_fmaxf(m, full || visible(0, kc + i) ? y[0][i] : NEG_INF);
+        return m;
     };
 
     for (int tile = t_begin; tile <= t_end; ++tile) {
         const int k0 = tile * KPT;
         __syncthreads();   // readers of ycode / ylo / LDS partials of the previous tile are done
 
-        // ---- active sub-blocks (a visible pair anywhere in the block), uniform
+        // ---- active sub-blocks (a visible pair anywhere in the block): some row
+        // j of the block with k <= j <= z + window - 1, or, not causal, any key
         uint32_t active = 0;
 #pragma unroll
         for (int th = 0; th < NK; ++th) {
-            const int a = k0 + th * BK, z = a + BK - 1;
-            bool any = false;
-#pragma unroll
-            for (int s = 0; s < QPL; ++s) any |= (a <= vhi[s] && z >= vlo[s]);
-            if (wave_any(any)) active |= 1u << th;
+            const int k = k0 + th * BK, z = k + BK - 1;
+            const int j0 = p.causal && k > q0 ? k : q0;
+            const int j1 = p.window > 0 && z + p.window - 1 < q_last ? z + p.window - 1 : q_last;
+            if (k < p.N && j0 <= j1) active |= 1u << th;
         }
         if (active == 0) {   // no visible pair in the tile: no state change
             if (tid == 0)
@@ -259,11 +274,11 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             continue;
         }
 
-        // ---- 1. 8-bit logits of the own sub-blocks (unused at threshold 0)
+        // ---- 1. 8-bit logits of the own sub-block (unused at threshold 0)
+        for (int i = tid; i < NK * BQ; i += NT) cms[i] = NEG_INF;
         if (p.mode != MODE_ALL16) {
-#pragma unroll
-            for (int u = 0; u < SPW; ++u) {
-                const int th = w * SPW + u;
+            {
+                const int th = w;
                 float mx[QPL];
 #pragma unroll
                 for (int s = 0; s < QPL; ++s) mx[s] = NEG_INF;
@@ -274,12 +289,11 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                         if (ck0 > bv_hi || ck0 + 15 < bv_lo) continue;   // nothing visible in the block
                         uint32_t a8[QPL][4], sat[QPL];
                         if constexpr (SR) {
-                            int jq[QPL];
-#pragma unroll
-                            for (int s = 0; s < QPL; ++s) jq[s] = q0 + row[s];
-                            sr8_chunk<D, QPL>(qr, kt32 + (size_t)ck0 * D, p.seed, (uint64_t)bh, jq, ck0, a8, sat);
+                            const int jq[QPL] = {q0 + row[0]};
+                            sr8_chunk_bc<D, QPL, GrpLay>(qr, kt32 + (size_t)ck0 * D, jq, (uint32_t)ck0, (uint32_t)bh,
+                                                         p.seed, a8, sat);
                         } else {
-                            emu8_any<D, QPL, false>(qr, keys16<RowLay<D>>(kt32 + (size_t)ck0 * D), a8, sat);
+                            emu8_any<D, QPL, false, GrpLay>(qr, keys16<GrpLay>(kt32 + (size_t)ck0 * D), a8, sat);
                         }
                         auto vis16 = [&](int s) {
                             uint32_t m = 0;
@@ -320,7 +334,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                         }
 #pragma unroll
                         for (int s = 0; s < QPL; ++s) {
-                            const bool full = ck0 >= vlo[s] && ck0 + 15 <= vhi[s];
+                            const bool full = all_visible(ck0, 16);
                             uint32_t packed[8];
 #pragma unroll
                             for (int pp = 0; pp < 8; ++pp) {
@@ -329,8 +343,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                                 // invisible keys enter as -inf, by selection rather than branches
                                 const float x0 = (full || visible(s, i0)) ? yv.x : NEG_INF;
                                 const float x1 = (full || visible(s, i0 + 1)) ? yv.y : NEG_INF;
-                                mx[s] = x0 > mx[s] ? x0 : mx[s];
-                                mx[s] = x1 > mx[s] ? x1 : mx[s];
+                                mx[s] = __builtin_fmaxf(__builtin_fmaxf(x0, x1), mx[s]);
                                 packed[pp] = spread_codes(a8[s][pp / 2], pp & 1);
                             }
                             u32x4 *dst = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + c16 * 16);
@@ -346,71 +359,64 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
         __syncthreads();   // m8s complete
 
         // ---- 2. running maximum mu_hat and stage 1
-        float muh[QPL];
-        float m8[NK][QPL];
+        float muhS[HS], m8[NK][HS];
 #pragma unroll
-        for (int s = 0; s < QPL; ++s) {
-            muh[s] = mu[s];
+        for (int s = 0; s < HS; ++s) {
+            muhS[s] = muS[s];
 #pragma unroll
-            for (int th = 0; th < NK; ++th) m8[th][s] = (p.mode != MODE_ALL16) ? m8s[th * BQ + row[s]] : NEG_INF;
+            for (int th = 0; th < NK; ++th) m8[th][s] = (p.mode != MODE_ALL16) ? m8s[th * BQ + rowS[s]] : NEG_INF;
         }
         uint32_t prec16 = 0;   // stage-1 (or threshold-0) sub-blocks
+        uint32_t F0 = 0;       // sub-blocks whose 16-bit logits are computed ahead of the tests
         const bool stage1_off = (p.flags & LAMP_STAGE1_OFF) != 0u;   // flags are 0 outside the threshold mode
         if (p.mode == MODE_PURE8 || stage1_off) {   // running maximum over the 8-bit logits
 #pragma unroll
-            for (int s = 0; s < QPL; ++s)
+            for (int s = 0; s < HS; ++s)
 #pragma unroll
-                for (int th = 0; th < NK; ++th) muh[s] = m8[th][s] > muh[s] ? m8[th][s] : muh[s];
-        } else if (p.mode == MODE_ALL16) {
-            prec16 = active;
-#pragma unroll
-            for (int u = 0; u < SPW; ++u) {
-                const int th = w * SPW + u;
-                float cm[QPL];
-#pragma unroll
-                for (int s = 0; s < QPL; ++s) cm[s] = NEG_INF;
-                if (active >> th & 1u) {
-                    for (int ch = 0; ch < CPS; ++ch) {
-                        const int c16 = th * CPS + ch;
-                        const int ck0 = k0 + c16 * 16;
-                        if (ck0 > bv_hi || ck0 + 15 < bv_lo) continue;
-                        uint32_t yc[QPL][8];
-                        rec16_keys<D, QPL, 16>(qr, keys16<RowLay<D>>(kt32 + (size_t)ck0 * D), yc);
-                        obs16(ck0, yc);
-#pragma unroll
-                        for (int s = 0; s < QPL; ++s) {
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) {
-                                const float yv = e4m11_value((yc[s][i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-                                if (visible(s, ck0 + i)) cm[s] = yv > cm[s] ? yv : cm[s];
-                            }
-                            u32x4 *dst = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + c16 * 16);
-                            dst[0] = u32x4{yc[s][0], yc[s][1], yc[s][2], yc[s][3]};
-                            dst[1] = u32x4{yc[s][4], yc[s][5], yc[s][6], yc[s][7]};
-                        }
-                    }
-                }
-#pragma unroll
-                for (int s = 0; s < QPL; ++s) cms[th * BQ + row[s]] = cm[s];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int s = 0; s < QPL; ++s)
+                for (int th = 0; th < NK; ++th) muhS[s] = m8[th][s] > muhS[s] ? m8[th][s] : muhS[s];
+        } else {
+            // F0: every active sub-block at threshold 0, else the ones that fail
+            // against mu; recomputed together, their maxima merged in cms
+            if (p.mode == MODE_ALL16) {
+                F0 = active;
+            } else {
 #pragma unroll
                 for (int th = 0; th < NK; ++th) {
-                    const float c = cms[th * BQ + row[s]];
-                    muh[s] = c > muh[s] ? c : muh[s];
+                    bool bad = false;
+#pragma unroll
+                    for (int s = 0; s < HS; ++s) bad |= fails(m8[th][s], muhS[s]);
+                    if (wave_any(bad)) F0 |= 1u << th;
                 }
-        } else {
+            }
+            // codes and maxima of a recompute (its observables wait for the
+            // tests: a member of F0 may turn out not to be needed)
+            auto recompute = [&](int th) {
+                shared16(k0, th, [&](int kc, const float (&y)[QPL][16]) {
+                    lds_fmax(&cms[th * BQ + row[0]], keep16(k0, kc, y));
+                });
+            };
+            if (F0) {
+                for (uint32_t m = F0; m; m &= m - 1) recompute(__builtin_ctz(m));
+                __syncthreads();
+            }
+            auto raise = [&](int th) {
+#pragma unroll
+                for (int s = 0; s < HS; ++s) muhS[s] = __builtin_fmaxf(cms[th * BQ + rowS[s]], muhS[s]);
+            };
+            if (p.mode == MODE_ALL16) {
+                prec16 = active;
+#pragma unroll
+                for (int th = 0; th < NK; ++th) raise(th);
+            } else {
             // threats T_theta = max_j (m8 - mu_j), exact in fp64 (+inf when mu_j = -inf)
             double T[NK];
 #pragma unroll
             for (int th = 0; th < NK; ++th) {
                 double t = -__builtin_inf();
 #pragma unroll
-                for (int s = 0; s < QPL; ++s)
+                for (int s = 0; s < HS; ++s)
                     if (m8[th][s] > NEG_INF) {
-                        const double d = (double)m8[th][s] - (double)mu[s];
+                        const double d = (double)m8[th][s] - (double)muS[s];
                         t = d > t ? d : t;
                     }
                 T[th] = wave_max_f64(t);
@@ -436,67 +442,57 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                     taken |= 1u << best;
                 }
             }
-            // margin test of every sub-block against the current mu_hat:
-            // mu_hat_j > fma(|mu_hat_j|, delta, m8); columns without a visible
-            // entry are not tested; mu_hat = -inf fails
-            auto fails = [&]() {
-                uint32_t f = 0;
-#pragma unroll
-                for (int th = 0; th < NK; ++th) {
+            // the sub-blocks in that order, each tested against the mu_hat that
+            // the recomputes before it left (until the first one, mu, whose
+            // tests F0 holds)
+            bool raised = false;
+            for (int pos = 0; pos < na; ++pos) {
+                const int th = (int)((order >> (4 * pos)) & 15u);
+                if (raised) {
                     bool bad = false;
 #pragma unroll
-                    for (int s = 0; s < QPL; ++s)
-                        if (m8[th][s] > NEG_INF) {
-                            const double mh = (double)muh[s];
-                            bad |= !(mh > __builtin_fma(__builtin_fabs(mh), p.delta, (double)m8[th][s]));
-                        }
-                    if (wave_any(bad)) f |= 1u << th;
+                    for (int s = 0; s < HS; ++s) {
+                        float c8 = m8[0][s];
+#pragma unroll
+                        for (int t2 = 1; t2 < NK; ++t2) c8 = t2 == th ? m8[t2][s] : c8;
+                        bad |= fails(c8, muhS[s]);
+                    }
+                    if (!wave_any(bad)) continue;
+                } else if (!(F0 >> th & 1u)) {
+                    continue;
                 }
-                return f;
-            };
-            uint32_t fail = fails();
-            int pos = 0, par = 0;
-            while (true) {
-                while (pos < na && !(fail >> ((order >> (4 * pos)) & 15u) & 1u)) ++pos;
-                if (pos >= na) break;
-                const int th = (int)((order >> (4 * pos)) & 15u);
-                ++pos;
+                raised = true;
                 prec16 |= 1u << th;
-                {   // all waves recompute the sub-block in 16 bits, KPW keys each
-                    float cm[QPL];
-#pragma unroll
-                    for (int s = 0; s < QPL; ++s) cm[s] = NEG_INF;
-                    shared16(k0, th, [&](int kc, const auto &yc) {
-                        constexpr int NWD = sizeof(yc[0]) / sizeof(uint32_t);   // words per slot
-                        obs16(kc, yc);
-#pragma unroll
-                        for (int s = 0; s < QPL; ++s) {
-#pragma unroll
-                            for (int i = 0; i < 2 * NWD; ++i) {
-                                const float yv = e4m11_value((yc[s][i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-                                if (visible(s, kc + i)) cm[s] = yv > cm[s] ? yv : cm[s];
-                            }
-                            put_codes(ycode, row[s], kc - k0, yc[s], NWD);
-                        }
-                    });
-#pragma unroll
-                    for (int s = 0; s < QPL; ++s) cmf[(par * NW + w) * BQ + row[s]] = cm[s];
+                if (!(F0 >> th & 1u)) {
+                    recompute(th);
+                    __syncthreads();
                 }
-                __syncthreads();
+                raise(th);
+            }
+            }
+            if (dbg16 || p.stats) {
+                // observables of the sub-blocks that stage 1 settled on, from
+                // the codes kept in ylo by this wave
+                for (uint32_t m = prec16; m; m &= m - 1) {
+                    const int key0 = k0 + __builtin_ctz(m) * BK + w * KPW;
+                    if (key0 > bv_hi || key0 + KPW - 1 < bv_lo) continue;
+                    for (int kc = key0; kc < key0 + KPW; kc += 16) {
+                        const u32x4 *lp = reinterpret_cast<const u32x4 *>(ylo + row[0] * YP + (kc - k0));
+                        const u32x4 c0 = lp[0], c1 = lp[1];
+                        const uint32_t in[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
+                        float y[QPL][16];
 #pragma unroll
-                for (int s = 0; s < QPL; ++s) {
-#pragma unroll
-                    for (int ww = 0; ww < NW; ++ww) {
-                        const float c = cmf[(par * NW + ww) * BQ + row[s]];
-                        muh[s] = c > muh[s] ? c : muh[s];
+                        for (int i = 0; i < 16; ++i) y[0][i] = e4m11_value((in[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+                        obs16(kc, y);
                     }
                 }
-                par ^= 1;   // the next write goes to the other half: readers of this one may lag
-                if (pos < na) fail = fails();
+                __syncthreads();   // the exponentials overwrite the codes
             }
         }
+        float muh[QPL];
+        muh[0] = hf == 0 ? muhS[0] : muhS[HS - 1];
 
-        // ---- 3. exponentials of the own sub-blocks against mu_hat
+        // ---- 3. exponentials of the own sub-block against mu_hat
         {
             double sp[QPL], spF[QPL];   // all exponentials / those of 8-bit sub-blocks
             float mu8[QPL];             // the running maximum the 8-bit shifts use
@@ -505,26 +501,22 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                 sp[s] = spF[s] = 0.0;
                 mu8[s] = (p.flags & LAMP_MU_TRUNC) ? trunc_e4m3(muh[s]) : muh[s];
             }
+            const int th = w;
+            if (!(active >> th & 1u)) {
+                // inactive: zero exponentials so the P.V pass may read them
+                for (int ch = 0; ch < CPS; ++ch)
 #pragma unroll
-            for (int u = 0; u < SPW; ++u) {
-                const int th = w * SPW + u;
-                if (!(active >> th & 1u)) {
-                    // inactive: zero exponentials so the P.V pass may read them
-                    for (int ch = 0; ch < CPS; ++ch)
-#pragma unroll
-                        for (int s = 0; s < QPL; ++s) {
-                            u32x4 *d = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + (th * CPS + ch) * 16);
-                            d[0] = u32x4{0u, 0u, 0u, 0u};
-                            d[1] = u32x4{0u, 0u, 0u, 0u};
-                        }
-                    continue;
-                }
+                    for (int s = 0; s < QPL; ++s) {
+                        u32x4 *d = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + (th * CPS + ch) * 16);
+                        d[0] = u32x4{0u, 0u, 0u, 0u};
+                        d[1] = u32x4{0u, 0u, 0u, 0u};
+                    }
+            } else {
                 const bool hi16 = prec16 >> th & 1u;
-                // Straight-line per 16-key chunk and row: all codes read, all
-                // table indices formed (an invisible key reads the table's last
-                // entry, whose exponential is 0), all table reads issued, then
-                // the sums, which are exact in fp64 in any order (multiples of
-                // 2^-41 below 2^9).
+                // Straight-line per 16-key chunk and row: all codes read (16-bit
+                // ones from ylo), all table indices formed, all table reads
+                // issued, then the sums, which are exact in fp64 in any order
+                // (multiples of 2^-41 below 2^9).
                 auto run = [&](auto hi_c) {
                     constexpr bool HI = decltype(hi_c)::value;
                     for (int ch = 0; ch < CPS; ++ch) {
@@ -534,50 +526,45 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                         for (int s = 0; s < QPL; ++s) {
                             u32x4 *rp = reinterpret_cast<u32x4 *>(ycode + row[s] * YP + c16 * 16);
                             u32x4 *lp = reinterpret_cast<u32x4 *>(ylo + row[s] * YP + c16 * 16);
-                            const u32x4 c0 = rp[0], c1 = rp[1];
+                            const u32x4 c0 = HI ? lp[0] : rp[0], c1 = HI ? lp[1] : rp[1];
                             const uint32_t in[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
-                            uint32_t eb[16];
+                            uint32_t eb[16];   // HI: high | low << 16, else the bf16 bits
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
-                                const uint32_t yc = (in[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-                                const bool vis = visible(s, ck0 + i);
                                 if constexpr (HI) {
-                                    const uint32_t x = ue5m11_code(shift_of(muh[s], e4m11_value(yc)));
-                                    eb[i] = p.exp16[vis ? x : 65535u];
+                                    const uint32_t yc = (in[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+                                    eb[i] = p.exp16hl[ue5m11_code(shift_of(muh[s], e4m11_value(yc)))];
                                 } else {
                                     const float y = (i & 1) ? __builtin_amdgcn_cvt_f32_fp8((int)in[i >> 1], 2)
                                                             : __builtin_amdgcn_cvt_f32_fp8((int)in[i >> 1], 0);
-                                    const uint32_t x = ue5m3_code(shift_of(mu8[s], y));
-                                    eb[i] = lut[vis ? x : 255u];
+                                    eb[i] = lut[ue5m3_code(shift_of(mu8[s], y))];
                                 }
                             }
+                            if (!all_visible(ck0, 16)) {   // no mass from invisible keys
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) eb[i] = visible(s, ck0 + i) ? eb[i] : 0u;
+                            }
                             double a4[4] = {0.0, 0.0, 0.0, 0.0};
-                            uint32_t eh[16], el[16];
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
-                                float ev;
-                                if constexpr (HI) {
-                                    ev = ue5m11e_value(eb[i]);
-                                    split_bf16(ev, eh[i], el[i]);
-                                } else {
-                                    eh[i] = eb[i];
-                                    el[i] = 0u;
-                                    ev = bf16_value(eb[i]);
-                                }
+                                float ev = bf16_value(eb[i]);
+                                if constexpr (HI) ev += __builtin_bit_cast(float, eb[i] & 0xFFFF0000u);   // exact
                                 a4[i & 3] += (double)ev;
+                            }
+                            uint32_t eh[8], el[8];
+#pragma unroll
+                            for (int x = 0; x < 8; ++x) {
+                                eh[x] = __builtin_amdgcn_perm(eb[2 * x + 1], eb[2 * x], 0x05040100u);
+                                el[x] = __builtin_amdgcn_perm(eb[2 * x + 1], eb[2 * x], 0x07060302u);
                             }
                             const double ts = (a4[0] + a4[1]) + (a4[2] + a4[3]);
                             sp[s] += ts;
                             if constexpr (!HI) spF[s] += ts;
-                            rp[0] = u32x4{eh[0] | eh[1] << 16, eh[2] | eh[3] << 16, eh[4] | eh[5] << 16,
-                                          eh[6] | eh[7] << 16};
-                            rp[1] = u32x4{eh[8] | eh[9] << 16, eh[10] | eh[11] << 16, eh[12] | eh[13] << 16,
-                                          eh[14] | eh[15] << 16};
+                            rp[0] = u32x4{eh[0], eh[1], eh[2], eh[3]};
+                            rp[1] = u32x4{eh[4], eh[5], eh[6], eh[7]};
                             if constexpr (HI) {
-                                lp[0] = u32x4{el[0] | el[1] << 16, el[2] | el[3] << 16, el[4] | el[5] << 16,
-                                              el[6] | el[7] << 16};
-                                lp[1] = u32x4{el[8] | el[9] << 16, el[10] | el[11] << 16, el[12] | el[13] << 16,
-                                              el[14] | el[15] << 16};
+                                lp[0] = u32x4{el[0], el[1], el[2], el[3]};
+                                lp[1] = u32x4{el[4], el[5], el[6], el[7]};
                             }
                         }
                     }
@@ -630,13 +617,16 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                     need |= !(sf <= (p.tau * omh[s]) * (1.0 - 0x1p-38));
                 }
                 need = wave_any(need);
+                if constexpr (H > 1) {   // of any row part
+                    if (tid % (64 * NW) == 0) votes[hf] = need ? 1u : 0u;
+                    __syncthreads();
+                    need = __builtin_amdgcn_readfirstlane(votes[0] | votes[1]) != 0u;
+                }
             }
             if (need) {
                 // costs c_theta,j = sum_{i in theta, ascending} E (omega_hat - E)
-#pragma unroll
-                for (int u = 0; u < SPW; ++u) {
-                    const int th = w * SPW + u;
-                    if (!(F >> th & 1u)) continue;
+                if (F >> w & 1u) {
+                    const int th = w;
 #pragma unroll
                     for (int s = 0; s < QPL; ++s) {
                         double cth = 0.0;
@@ -679,6 +669,11 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                     }
                     if (!wave_any(bad)) feas |= 1u << R;
                 }
+                if constexpr (H > 1) {   // feasible for every row part
+                    if (tid % (64 * NW) == 0) votes[2 + hf] = feas;
+                    __syncthreads();
+                    feas = __builtin_amdgcn_readfirstlane(votes[2] & votes[3]);
+                }
                 // smallest recompute set first, then ascending bitmask
                 int chosen = (int)F;
                 bool found = false;
@@ -697,37 +692,35 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                     double ds[QPL];
 #pragma unroll
                     for (int s = 0; s < QPL; ++s) ds[s] = 0.0;
-                    auto s2fn = [&](int kc, const auto &yc) {
-                        constexpr int NWD = sizeof(yc[0]) / sizeof(uint32_t);
-                        obs16(kc, yc);
+                    auto s2fn = [&](int kc, const float (&y)[QPL][16]) {
+                        obs16(kc, y);
+                        u32x4 *rp = reinterpret_cast<u32x4 *>(ycode + row[0] * YP + (kc - k0));
+                        u32x4 *lp = reinterpret_cast<u32x4 *>(ylo + row[0] * YP + (kc - k0));
+                        const u32x4 c0 = rp[0], c1 = rp[1];
+                        const uint32_t in[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
+                        uint32_t hl[16];
 #pragma unroll
-                        for (int s = 0; s < QPL; ++s) {
-                            const uint16_t *src = ycode + row[s] * YP + (kc - k0);
-                            uint32_t outw[NWD], outl[NWD];
+                        for (int i = 0; i < 16; ++i) hl[i] = p.exp16hl[ue5m11_code(shift_of(muh[0], y[0][i]))];
+                        if (!all_visible(kc, 16)) {
 #pragma unroll
-                            for (int pp = 0; pp < NWD; ++pp) {
-                                uint32_t res = 0, rlo = 0;
-#pragma unroll
-                                for (int t = 0; t < 2; ++t) {
-                                    const int key = kc + 2 * pp + t;
-                                    uint32_t eh = 0, el = 0;
-                                    if (visible(s, key)) {
-                                        const float old = bf16_value(src[2 * pp + t]);
-                                        const float y = e4m11_value((yc[s][pp] >> (16 * t)) & 0xFFFFu);
-                                        const float ev = ue5m11e_value(p.exp16[ue5m11_code(shift_of(muh[s], y))]);
-                                        split_bf16(ev, eh, el);
-                                        ds[s] = ds[s] - (double)old;
-                                        ds[s] = ds[s] + (double)ev;
-                                    }
-                                    res |= eh << (16 * t);
-                                    rlo |= el << (16 * t);
-                                }
-                                outw[pp] = res;
-                                outl[pp] = rlo;
-                            }
-                            put_codes(ycode, row[s], kc - k0, outw, NWD);
-                            put_codes(ylo, row[s], kc - k0, outl, NWD);
+                            for (int i = 0; i < 16; ++i) hl[i] = visible(0, kc + i) ? hl[i] : 0u;
                         }
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {   // exact: multiples of 2^-41
+                            const float old = bf16_value((in[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+                            ds[0] = ds[0] - (double)old;
+                            ds[0] = ds[0] + (double)(bf16_value(hl[i]) + __builtin_bit_cast(float, hl[i] & 0xFFFF0000u));
+                        }
+                        uint32_t eh[8], el[8];
+#pragma unroll
+                        for (int x = 0; x < 8; ++x) {
+                            eh[x] = __builtin_amdgcn_perm(hl[2 * x + 1], hl[2 * x], 0x05040100u);
+                            el[x] = __builtin_amdgcn_perm(hl[2 * x + 1], hl[2 * x], 0x07060302u);
+                        }
+                        rp[0] = u32x4{eh[0], eh[1], eh[2], eh[3]};
+                        rp[1] = u32x4{eh[4], eh[5], eh[6], eh[7]};
+                        lp[0] = u32x4{el[0], el[1], el[2], el[3]};
+                        lp[1] = u32x4{el[4], el[5], el[6], el[7]};
                     };
                     for (int th = 0; th < NK; ++th) {
                         if (!(prec2 >> th & 1u)) continue;
@@ -753,6 +746,8 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             om[s] = __builtin_fma(lam[s], om[s], S[s]);
             mu[s] = muh[s];
         }
+#pragma unroll
+        for (int s = 0; s < HS; ++s) muS[s] = muhS[s];
         if (tid == 0) {
 #pragma unroll
             for (int th = 0; th < NK; ++th)
@@ -760,14 +755,13 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                                      : (prec16 >> th & 1u) ? PREC_S1
                                      : (prec2 >> th & 1u) ? PREC_S2 : PREC_LOW;
             if (p.stats) {
-                // every recompute of this kernel is one at a time (or after
-                // stage 2), except the all-16-bit mode's own sub-blocks
                 const uint32_t rec = prec16 | prec2;
                 stl[ST_TILES] += 1u;
                 stl[ST_S1] += __builtin_popcount(prec16);
                 stl[ST_S2] += __builtin_popcount(prec2);
                 stl[ST_ACT] += __builtin_popcount(active);
-                stl[ST_LATE] += p.mode == MODE_LAMP ? __builtin_popcount(rec) : 0;
+                stl[ST_UNUSED] += __builtin_popcount(F0 & ~rec);
+                stl[ST_LATE] += __builtin_popcount(rec & ~F0);
                 stl[ST_HIST + __builtin_popcount(rec)] += 1u;
             }
         }
@@ -779,7 +773,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
         auto load_v = [&](int c16, u32x4 (&a)[CT]) {
 #pragma unroll
             for (int t = 0; t < CT; ++t)
-                a[t] = *reinterpret_cast<const u32x4 *>(vtbase + (size_t)(w * CPW + t * 32 + l32) * p.Nk + k0 + c16 * 16 +
+                a[t] = *reinterpret_cast<const u32x4 *>(vtbase + (size_t)(cw * CPW + t * 32 + l32) * p.Nk + k0 + c16 * 16 +
                                                         half * 8);
         };
         auto pv_chunk = [&](int c16, const u32x4 (&a)[CT]) {
@@ -789,7 +783,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             const bool hi16 = p16 >> th & 1u;
 #pragma unroll
             for (int g = 0; g < QG; ++g) {
-                const int off = (g * 32 + l32) * YP + c16 * 16 + half * 8;
+                const int off = (hf * 64 + r0 + g * 32 + l32) * YP + c16 * 16 + half * 8;
                 const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ycode + off));
 #pragma unroll
                 for (int t = 0; t < CT; ++t)
@@ -807,7 +801,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
         u32x4 va[CT], vb[CT];
         load_v(0, va);
         {
-            // lambda_hat of row 32g + l32 lives in lane (32g + l32) % 64, slot (32g + l32) / 64
+            // lambda_hat of row r of the part lives in lane r
             // A row to which the tile added no mass (S = 0: every exponential
             // underflowed against a maximum that overshoots) keeps O and omega
             // in the same ratio, but lambda_hat can lie below fp32's range
@@ -833,7 +827,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
             if (wave_any(scale)) {
 #pragma unroll
                 for (int g = 0; g < QG; ++g) {
-                    const float lg = __shfl(lamf[g / 2 < QPL ? g / 2 : 0], ((g & 1) << 5) + l32, 64);
+                    const float lg = __shfl(lamf[0], r0 + g * 32 + l32, 64);
 #pragma unroll
                     for (int t = 0; t < CT; ++t)
 #pragma unroll
@@ -855,12 +849,12 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
         const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
         for (int g = 0; g < QG; ++g) {
-            const double og = __shfl(om[g / 2 < QPL ? g / 2 : 0], ((g & 1) << 5) + l32, 64);
-            const double pg = pend[w * BQ + g * 32 + l32];
+            const double og = __shfl(om[0], r0 + g * 32 + l32, 64);
+            const double pg = pend[w * BQ + hf * 64 + r0 + g * 32 + l32];
             const float inv = (float)(pg / og);   // pg = 1 unless the last tiles added no mass
-            const int jq = q0 + g * 32 + l32;
+            const int jq = q0 + hf * 64 + r0 + g * 32 + l32;
             if (jq >= p.N) continue;   // beyond N in a partial last block
-            float *orow = p.o + (((size_t)b * p.Hq + h) * p.N + jq) * D + w * CPW;
+            float *orow = p.o + (((size_t)b * p.Hq + h) * p.N + jq) * D + cw * CPW;
 #pragma unroll
             for (int t = 0; t < CT; ++t)
 #pragma unroll
@@ -877,7 +871,7 @@ __global__ __launch_bounds__(64 * (NK < D / 32 ? NK : D / 32), LAMP_MIN_WAVES) v
                 if (q0 + row[s] < p.N)
                     p.lse[((size_t)b * p.Hq + h) * p.N + q0 + row[s]] = (float)((double)mu[s] + ::log(om[s]));
         const int ntiles = p.Nk / KPT;
-        for (int t = tid; t < ntiles; t += 64 * NW)
+        for (int t = tid; t < ntiles; t += NT)
             if (t < t_begin || t > t_end)
                 for (int th = 0; th < NK; ++th) mrow[t * NK + th] = PREC_INACTIVE;
     }
@@ -894,7 +888,7 @@ static hipError_t launch_fwd_obs(const FwdParams &p, hipStream_t s)
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)(p.B * p.Hq * (p.Nq / BQ)));
-    hipLaunchKernelGGL(kern, grid, dim3(64 * C::NW), C::LDS, s, p);
+    hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS, s, p);
     return hipGetLastError();
 }
 
@@ -914,17 +908,10 @@ bool fwd_supported(int D, int BQ, int BK, int NK)
     return (D == 64 || D == 128 || D == 256) && (BQ == 64 || BQ == 128) && (BK == 16 || BK == 64) && NK == 4;
 }
 
-bool fwd_grouped(int D, int BQ, int BK, int NK)
-{
-    (void)BQ;
-    (void)D;
-    return BK == 16 && NK == 4;
-}
-
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found)
 {
     // 16-key sub-blocks: the kernel pipelined across key tiles
-    if (fwd_grouped(D, BQ, BK, NK)) return dispatch_fwd16(D, BQ, p, s, found);
+    if (BK == 16 && NK == 4) return dispatch_fwd16(D, BQ, p, s, found);
     *found = true;
 #define LAMP_FWD_D(D_) LAMP_FWD_CASE(D_, 64, 64, 4) LAMP_FWD_CASE(D_, 128, 64, 4)
     LAMP_FWD_D(64)
@@ -938,7 +925,7 @@ hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipSt
 hipError_t dispatch_fwd_sr(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found)
 {
     // 16-key sub-blocks: the pipelined kernel's SR instantiations
-    if (fwd_grouped(D, BQ, BK, NK)) return dispatch_fwd16_sr(D, BQ, p, s, found);
+    if (BK == 16 && NK == 4) return dispatch_fwd16_sr(D, BQ, p, s, found);
     *found = true;
 #define LAMP_FWD_SR(D_, BQ_, BK_)                                            \
     if (D == D_ && BQ == BQ_ && BK == BK_ && NK == 4) return launch_fwd<D_, BQ_, BK_, 4, true>(p, s);

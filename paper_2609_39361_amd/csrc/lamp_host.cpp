@@ -347,7 +347,6 @@ static int fwd_impl(const uint16_t *q, const uint16_t *k, const uint16_t *v, int
             rc = init_locked(dev);
             if (rc) return rc;
         }
-        p.exp16 = st->exp16;
         p.exp16hl = st->exp16hl;
         p.lut8e = st->lut8e;
         p.sim8 = st->sim8;
@@ -414,8 +413,7 @@ static int fwd_impl(const uint16_t *q, const uint16_t *k, const uint16_t *v, int
         bad = w.flag;
         HIP_TRY(hipMemsetAsync(bad, 0, sizeof(unsigned), s));
     }
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, Nq, Nk, d, scale_of(d), s,
-                                 lamp::fwd_grouped(d, bq, bk, nk), bad));
+    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, Nq, Nk, d, scale_of(d), s, true, bad));
     HIP_TRY(lamp::launch_transpose_v(v, w.vt, B, Hkv, N, Nk, d, s, bad));
     if (check) {
         unsigned h_bad = 0;

@@ -15,10 +15,9 @@ enum { MODE_LAMP = 0, MODE_PURE8 = 1, MODE_ALL16 = 2 };
 constexpr int SIM8_ENTRIES = 112, SIM8_TABLE = 256, SIM16_TABLE = 45056;
 
 struct FwdParams {
-    const float *qt;          // [B][Hq][Nq][D] pre-scaled queries, fp32 (row or grouped layout, see launch_prepass)
-    const float *kt32;        // [B][Hkv][Nk][D] keys, fp32 (row or grouped layout)
+    const float *qt;          // [B][Hq][Nq][D] pre-scaled queries, fp32 (grouped layout, see launch_prepass)
+    const float *kt32;        // [B][Hkv][Nk][D] keys, fp32 (grouped layout)
     const uint16_t *vt;       // [B][Hkv][D][Nk] bf16, V transposed
-    const uint16_t *exp16;    // ue5m11 shift code -> ue5m11 exp code
     const uint32_t *exp16hl;  // ue5m11 shift code -> bf16 high | low << 16 of the ue5m11 exp
     const uint16_t *lut8e;    // ue5m3 shift code -> bf16 bits of the ue5m3 exp
     const uint16_t *sim8;     // SIM profile: 8-bit exp table (bf16 bits), lamp_device.h layout
@@ -66,7 +65,7 @@ hipError_t dispatch_fwd16_d256(int BQ, const FwdParams &p, hipStream_t s, bool *
 hipError_t dispatch_fwd16_sim(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
-// the general kernel with stochastically rounded 8-bit logits (row layout)
+// the forward pass with stochastically rounded 8-bit logits
 hipError_t dispatch_fwd_sr(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
 // bad (may be null): bit 2 is or-ed into *bad if a V element is not finite.
 hipError_t launch_transpose_v(const uint16_t *v, uint16_t *vt, int B, int Hkv, int N, int Nk, int D, hipStream_t s,
@@ -76,15 +75,13 @@ hipError_t launch_transpose_v(const uint16_t *v, uint16_t *vt, int B, int Hkv, i
 // wave-instruction (per emulated step for RATE_STEP) per SIMD, into ns[RATE_N].
 enum { RATE_FMAC = 0, RATE_FMAC_DPP = 1, RATE_DECODE = 2, RATE_ENCODE = 3, RATE_STEP = 4, RATE_STEP_SIM = 5, RATE_N = 6 };
 hipError_t measure_issue_rates(double *ns, hipStream_t s);
-// grouped: the layout of the pipelined kernel (queries in 64-row and keys in
+// grouped: the layout of the forward kernels (queries in 64-row and keys in
 // 16-row blocks, each block stored [D/4][rows][4]); otherwise [rows][D].
 // bad (may be null): bit 0 (q) or bit 1 (k) is or-ed into *bad if an element
 // is not finite.
 hipError_t launch_prepass(const uint16_t *q, const uint16_t *k, float *qt, float *kt32, int B, int Hq, int Hkv,
                           int N, int Nq, int Nk, int D, float scale, hipStream_t s, bool grouped = false,
                           unsigned *bad = nullptr);
-// whether dispatch_fwd runs the pipelined kernel (which reads the grouped layout)
-bool fwd_grouped(int D, int BQ, int BK, int NK);
 hipError_t launch_logits8(const LogitsParams &p, int D, hipStream_t s, bool sr = false);
 hipError_t launch_logits16(const LogitsParams &p, int D, hipStream_t s);
 hipError_t launch_logits_sim(const LogitsParams &p, int D, int high, hipStream_t s);

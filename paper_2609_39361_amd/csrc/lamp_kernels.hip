@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64, 2) void logits8_kernel(LogitsParams p)
         uint32_t acc[1][4], sat[1];
         if constexpr (SR) {
             const int jq[1] = {j};
-            sr8_chunk<D, 1>(qr, kt, p.seed, (uint64_t)bh, jq, key0, acc, sat);
+            sr8_chunk_bc<D, 1, RowLay<D>>(qr, kt, jq, (uint32_t)key0, (uint32_t)bh, p.seed, acc, sat);
         } else {
             emu8_any<D, 1, false>(qr, keys16<RowLay<D>>(kt), acc, sat);
         }

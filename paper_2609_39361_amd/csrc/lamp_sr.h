@@ -58,104 +58,6 @@ __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uin
     }
 }
 
-// The random operand of channel u (0..7) of a group: its 16-bit field in the
-// top half of a word.
-template <int U>
-__device__ __forceinline__ uint32_t sr_operand(const uint32_t (&w)[4])
-{
-    return (U & 1) ? (w[U / 2] & 0xFFFF0000u) : (w[U / 2] << 16);
-}
-
-// One stochastically rounded step value (fp32, an e4m3 number); amax keeps
-// the largest |t| pattern seen, so that a chain whose steps were clamped
-// (|t| > 448) can be counted.
-__device__ __forceinline__ float sr_e4m3(float t, uint32_t rop, uint32_t &amax)
-{
-    const uint32_t a = __builtin_bit_cast(uint32_t, t) & 0x7FFFFFFFu;
-    amax = amax > a ? amax : a;
-    const float tc = __builtin_amdgcn_fmed3f(t, -448.0f, 448.0f);
-    return __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_sr_fp8_f32(tc, (int)rop, 0, 0), 0);
-}
-
-// The steps of one row over the channels U... of a group, in order.
-template <int NC, int... U>
-__device__ __forceinline__ float sr8_steps(const float (&qv)[NC], const float (&kv)[NC], const uint32_t (&w)[4],
-                                           float v, uint32_t &amax, std::integer_sequence<int, U...>)
-{
-    ((v = sr_e4m3(__builtin_fmaf(qv[U], kv[U], v), sr_operand<U>(w), amax)), ...);
-    return v;
-}
-
-// 8 channels from c0 of one key and QPL rows: the group's Philox call, then
-// the 8 steps of each row's recursion.
-template <int QPL>
-__device__ __forceinline__ void sr8_group(const float *const (&qrow)[QPL], const float *krow, int c0, uint64_t seed,
-                                          uint32_t bh, const int (&j)[QPL], uint32_t key, float (&y)[QPL],
-                                          uint32_t (&amax)[QPL])
-{
-    float kv[8];
-#pragma unroll
-    for (int u = 0; u < 8; u += 4) {
-        const float4 a = *reinterpret_cast<const float4 *>(krow + c0 + u);
-        kv[u] = a.x; kv[u + 1] = a.y; kv[u + 2] = a.z; kv[u + 3] = a.w;
-    }
-#pragma unroll
-    for (int s = 0; s < QPL; ++s) {
-        float qv[8];
-#pragma unroll
-        for (int u = 0; u < 8; u += 4) {
-            const float4 a = *reinterpret_cast<const float4 *>(qrow[s] + c0 + u);
-            qv[u] = a.x; qv[u + 1] = a.y; qv[u + 2] = a.z; qv[u + 3] = a.w;
-        }
-        uint32_t w[4] = {(uint32_t)j[s], key, bh, (uint32_t)(c0 / 8)};
-        philox4x32_10(w, (uint32_t)seed, (uint32_t)(seed >> 32));
-        y[s] = sr8_steps(qv, kv, w, y[s], amax[s], std::make_integer_sequence<int, 8>{});
-    }
-}
-
-// 8-bit logits with stochastic rounding for 16 keys and QPL query rows per
-// lane: the key rows k32 + kk*D (fp32, kk = 0..15, the same for every lane),
-// the query rows qrow[s] (fp32, pre-scaled) of query index j[s]; key index
-// i0 + kk; bh = b*Hq + h.  Codes out: acc[s][p] holds the
-// e4m3 codes of keys 4p .. 4p+3, one per byte; sat[s] bit kk is
-// set when a step of key kk's chain was clamped (|t| > 448).
-template <int D, int QPL>
-__device__ __forceinline__ void sr8_chunk(const QRows<QPL> &qr, const float *k32, uint64_t seed,
-                                          uint64_t bh, const int (&j)[QPL], int i0, uint32_t (&acc)[QPL][4],
-                                          uint32_t (&sat)[QPL])
-{
-    static_assert(D % 8 == 0, "channel groups of 8");
-    const float *qrow[QPL];
-#pragma unroll
-    for (int s = 0; s < QPL; ++s) {
-        qrow[s] = qr.row(s);
-        sat[s] = 0u;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) acc[s][p] = 0u;
-    }
-    for (int kk = 0; kk < 16; ++kk) {
-        const float *krow = k32 + (size_t)kk * D;
-        const uint32_t key = (uint32_t)(i0 + kk);
-        float y[QPL];
-        uint32_t amax[QPL];
-#pragma unroll
-        for (int s = 0; s < QPL; ++s) {
-            y[s] = 0.0f;
-            amax[s] = 0u;
-        }
-        for (int g = 0; g < D / 8; ++g) sr8_group<QPL>(qrow, krow, 8 * g, seed, (uint32_t)bh, j, key, y, amax);
-        // the code of key kk into its byte (exact: y is an e4m3 value)
-#pragma unroll
-        for (int s = 0; s < QPL; ++s) {
-            const uint32_t code = pk_e4m3_sat(y[s], 0.0f) & 0xFFu;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) acc[s][p] |= (p == (kk >> 2)) ? code << (8 * (kk & 3)) : 0u;
-            sat[s] |= (amax[s] > 0x43E00000u ? 1u : 0u) << kk;
-        }
-    }
-}
-
-// ---- the pipelined kernel's form: keys by DPP row broadcast --------------
 // Channels cb .. cb+7 of the two chains of keys 2P, 2P+1 of each of QPL query
 // rows, whose codes share word acc[s][P] (bits 7:0, 15:8): one Philox call per
 // chain, then 8 steps of both, each decoding the pair, running both FP32 FMAs
