@@ -273,6 +273,7 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         }
         qr.base[s] = p.qt + (((size_t)b * p.Hq + h) * p.Nq + q0 + WR * hf + 64 * s) * D;
     }
+    if constexpr (SIMP && MODE != MODE_ALL16) set_qmin<D, QPL, GrpLay>(qr);
     const int bv_lo = p.window > 0 ? (q0 - p.window + 1 > 0 ? q0 - p.window + 1 : 0) : 0;
     const int bv_hi = p.causal ? (q0 + BQ - 1 < p.N - 1 ? q0 + BQ - 1 : p.N - 1) : p.N - 1;
     const int t_begin = bv_lo / KPT, t_end = bv_hi / KPT;   // every tile in between has a visible pair

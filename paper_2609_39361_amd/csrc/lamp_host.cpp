@@ -413,8 +413,7 @@ static int fwd_impl(const uint16_t *q, const uint16_t *k, const uint16_t *v, int
         bad = w.flag;
         HIP_TRY(hipMemsetAsync(bad, 0, sizeof(unsigned), s));
     }
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, Nq, Nk, d, scale_of(d), s, true, bad));
-    HIP_TRY(lamp::launch_transpose_v(v, w.vt, B, Hkv, N, Nk, d, s, bad));
+    HIP_TRY(lamp::launch_prepass(q, k, v, w.qt, w.kt32, w.vt, B, Hq, Hkv, N, Nq, Nk, d, scale_of(d), s, true, bad));
     if (check) {
         unsigned h_bad = 0;
         HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof(unsigned), hipMemcpyDeviceToHost, s));
@@ -779,7 +778,7 @@ int lamp_attn_logits8(const uint16_t *q, const uint16_t *k, int B, int Hq, int H
     if (rc) return rc;
     p.y8 = y8;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
+    HIP_TRY(lamp::launch_prepass(q, k, nullptr, w.qt, w.kt32, nullptr, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
     HIP_TRY(lamp::launch_logits8(p, d, s));
     return LAMP_OK;
 }
@@ -794,7 +793,7 @@ int lamp_attn_logits8_sr(const uint16_t *q, const uint16_t *k, int B, int Hq, in
     p.y8 = y8;
     p.seed = seed;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
+    HIP_TRY(lamp::launch_prepass(q, k, nullptr, w.qt, w.kt32, nullptr, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
     HIP_TRY(lamp::launch_logits8(p, d, s, true));
     return LAMP_OK;
 }
@@ -808,7 +807,7 @@ int lamp_attn_logits16(const uint16_t *q, const uint16_t *k, int B, int Hq, int 
     if (rc) return rc;
     p.y16 = y16;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
+    HIP_TRY(lamp::launch_prepass(q, k, nullptr, w.qt, w.kt32, nullptr, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
     HIP_TRY(lamp::launch_logits16(p, d, s));
     return LAMP_OK;
 }
@@ -823,7 +822,7 @@ int lamp_attn_logits_sim(const uint16_t *q, const uint16_t *k, int B, int Hq, in
     if (rc) return rc;
     p.ysim = y;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIP_TRY(lamp::launch_prepass(q, k, w.qt, w.kt32, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
+    HIP_TRY(lamp::launch_prepass(q, k, nullptr, w.qt, w.kt32, nullptr, B, Hq, Hkv, N, N, N, d, scale_of(d), s));
     HIP_TRY(lamp::launch_logits_sim(p, d, high, s));
     return LAMP_OK;
 }

@@ -57,7 +57,6 @@ hipError_t noalloc_scratch_address(void **ptr);
 // cycle sums and the number of waves; hipErrorNotSupported otherwise.
 constexpr int PHASE_N = 10;
 hipError_t phase_read(unsigned long long *host, bool reset);
-hipError_t launch_prescale_q(const uint16_t *q, float *qt, int BH, int rows, int D, float scale, hipStream_t s);
 bool fwd_supported(int D, int BQ, int BK, int NK);
 hipError_t dispatch_fwd16(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_d64(int BQ, const FwdParams &p, hipStream_t s, bool *found);
@@ -67,21 +66,17 @@ hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, b
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
 // the forward pass with stochastically rounded 8-bit logits
 hipError_t dispatch_fwd_sr(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
-// bad (may be null): bit 2 is or-ed into *bad if a V element is not finite.
-hipError_t launch_transpose_v(const uint16_t *v, uint16_t *vt, int B, int Hkv, int N, int Nk, int D, hipStream_t s,
-                              unsigned *bad = nullptr);
-
 // Issue rates of the logit loops' instructions (lamp_rates.hip): ns per
 // wave-instruction (per emulated step for RATE_STEP) per SIMD, into ns[RATE_N].
 enum { RATE_FMAC = 0, RATE_FMAC_DPP = 1, RATE_DECODE = 2, RATE_ENCODE = 3, RATE_STEP = 4, RATE_STEP_SIM = 5, RATE_N = 6 };
 hipError_t measure_issue_rates(double *ns, hipStream_t s);
 // grouped: the layout of the forward kernels (queries in 64-row and keys in
 // 16-row blocks, each block stored [D/4][rows][4]); otherwise [rows][D].
-// bad (may be null): bit 0 (q) or bit 1 (k) is or-ed into *bad if an element
-// is not finite.
-hipError_t launch_prepass(const uint16_t *q, const uint16_t *k, float *qt, float *kt32, int B, int Hq, int Hkv,
-                          int N, int Nq, int Nk, int D, float scale, hipStream_t s, bool grouped = false,
-                          unsigned *bad = nullptr);
+// v null: no transposed V.  bad (may be null): bit 0 (q), 1 (k) or 2 (v) is
+// or-ed into *bad if an element is not finite.
+hipError_t launch_prepass(const uint16_t *q, const uint16_t *k, const uint16_t *v, float *qt, float *kt32, uint16_t *vt,
+                          int B, int Hq, int Hkv, int N, int Nq, int Nk, int D, float scale, hipStream_t s,
+                          bool grouped = false, unsigned *bad = nullptr);
 hipError_t launch_logits8(const LogitsParams &p, int D, hipStream_t s, bool sr = false);
 hipError_t launch_logits16(const LogitsParams &p, int D, hipStream_t s);
 hipError_t launch_logits_sim(const LogitsParams &p, int D, int high, hipStream_t s);

@@ -56,56 +56,38 @@ __device__ __forceinline__ void flag_nonfinite(unsigned *bad, bool seen, unsigne
     if (__ballot(seen) != 0ull && __lane_id() == (unsigned)__builtin_ctzll(__ballot(seen))) atomicOr(bad, bit);
 }
 
-// Pre-scaled queries q~ = RN32(q * s), rows padded with zeros from N to Nq:
-// qt [BH][Nq][D] from q [BH][N][D] (grouped layout: blk = 64).  Grid: x over
-// the float4 groups of a head, y over heads (both grid-stride).
-// With bad (may be null), bit `bit` is or-ed into *bad if an element of q is
-// not finite.
-__global__ void prescale_q_kernel(const uint16_t *__restrict__ q, float *__restrict__ qt, float s, int N, int Nq,
-                                  int D, int BH, int blk, unsigned *bad, unsigned bit)
+// Rows x [BH][N][D] as fp32 times scale (RN32; 1 converts exactly), padded with
+// zeros from N to Np rows: y [BH][Np][D] in the row or grouped layout (blk rows
+// a block).  Workgroup (bx, by) of (gx, gy): bx over the float4 groups of a
+// head, by over heads (both grid-stride).  Returns whether an element is not
+// finite.
+__device__ __forceinline__ bool rows_to_f32(const uint16_t *__restrict__ x, float *__restrict__ y, float scale, int N,
+                                            int Np, int D, int BH, int blk, unsigned bx, unsigned by, unsigned gx,
+                                            unsigned gy)
 {
-    const int G = D / 4, n4 = Nq * G;
+    const int G = D / 4, n4 = Np * G;
     bool seen = false;
-    for (int bh = blockIdx.y; bh < BH; bh += gridDim.y)
-        for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < n4; u += gridDim.x * blockDim.x) {
+    for (unsigned bh = by; bh < (unsigned)BH; bh += gy)
+        for (int u = bx * 256 + threadIdx.x; u < n4; u += gx * 256) {
             int j, g;
             rg_of(u, G, blk, j, g);
-            const uint2 w = j < N ? *reinterpret_cast<const uint2 *>(q + ((size_t)bh * N + j) * D + 4 * g)
+            const uint2 w = j < N ? *reinterpret_cast<const uint2 *>(x + ((size_t)bh * N + j) * D + 4 * g)
                                   : make_uint2(0u, 0u);
             seen |= (bf16_nonfinite(w.x) | bf16_nonfinite(w.y)) != 0u;
-            reinterpret_cast<float4 *>(qt + (size_t)bh * Nq * D)[u] = bf16x4_scaled(w, s);
+            reinterpret_cast<float4 *>(y + (size_t)bh * Np * D)[u] = bf16x4_scaled(w, scale);
         }
-    if (bad) flag_nonfinite(bad, seen, bit);
+    return seen;
 }
 
-// K in fp32 (bf16 -> fp32 is exact), rows padded with zeros from N to Nk:
-// k32 [BH][Nk][D] from k [BH][N][D] (grouped layout: blk = 16).
-__global__ void convert_k_kernel(const uint16_t *__restrict__ k, float *__restrict__ k32, int N, int Nk, int D,
-                                 int BH, int blk, unsigned *bad)
+// V^T [B*Hkv][D][Nk] from V [B*Hkv][N][D] (bf16), keys padded with zeros from N
+// to Nk: the 64 x 64 tile number t (key tiles innermost) through LDS.  Nk and D
+// are multiples of 64.
+__device__ __forceinline__ bool transpose_v_tile(const uint16_t *__restrict__ v, uint16_t *__restrict__ vt, int N,
+                                                 int Nk, int D, unsigned t, uint16_t (&tile)[64][66])
 {
-    const int G = D / 4, n4 = Nk * G;
-    bool seen = false;
-    for (int bh = blockIdx.y; bh < BH; bh += gridDim.y)
-        for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < n4; u += gridDim.x * blockDim.x) {
-            int j, g;
-            rg_of(u, G, blk, j, g);
-            const uint2 w = j < N ? *reinterpret_cast<const uint2 *>(k + ((size_t)bh * N + j) * D + 4 * g)
-                                  : make_uint2(0u, 0u);
-            seen |= (bf16_nonfinite(w.x) | bf16_nonfinite(w.y)) != 0u;
-            reinterpret_cast<float4 *>(k32 + (size_t)bh * Nk * D)[u] = bf16x4_scaled(w, 1.0f);
-        }
-    if (bad) flag_nonfinite(bad, seen, 2u);
-}
-
-// V^T [B*Hkv][D][Nk] from V [B*Hkv][N][D] (bf16), keys padded with zeros
-// from N to Nk: 64x64 tiles through LDS.  grid (Nk/64, D/64, B*Hkv); Nk and
-// D are multiples of 64.
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t *__restrict__ v, uint16_t *__restrict__ vt,
-                                                          int N, int Nk, int D, unsigned *bad)
-{
-    __shared__ uint16_t tile[64][66];
-    const size_t bh = blockIdx.z;
-    const int n0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    const unsigned nt = (unsigned)Nk / 64, ct = (unsigned)D / 64;
+    const size_t bh = t / (nt * ct);
+    const int n0 = (int)(t % nt) * 64, c0 = (int)(t / nt % ct) * 64;
     const uint16_t *src = v + bh * (size_t)N * D;
     uint16_t *dst = vt + bh * (size_t)D * Nk;
     bool seen = false;
@@ -115,12 +97,54 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t *__rest
         seen |= (x & 0x7F80u) == 0x7F80u;
         tile[r][c] = x;
     }
-    if (bad) flag_nonfinite(bad, seen, 4u);
     __syncthreads();
     for (int e = threadIdx.x; e < 64 * 64; e += 256) {
         const int c = e / 64, r = e % 64;
         dst[(size_t)(c0 + c) * Nk + n0 + r] = tile[r][c];
     }
+    return seen;
+}
+
+// The prepass in one launch: the pre-scaled queries q~ = RN32(q * s), the keys
+// in fp32 and (v not null) V transposed, each on its own range of workgroups.
+// Three launches cost a short call some 10 us of gaps and of devices nearly
+// empty (300 tokens, 32 heads: 17 us, one launch 7).
+// bad (may be null): bits 0, 1, 2 are or-ed into *bad if an element of q, k, v
+// is not finite.
+struct PrepassParams {
+    const uint16_t *q, *k, *v;
+    float *qt, *kt32;
+    uint16_t *vt;
+    int N, Nq, Nk, D, BHq, BHk, blkq, blkk;
+    float scale;
+    dim3 gq, gk;       // workgroups of the queries and keys
+    unsigned nv;       // workgroups of V
+    unsigned *bad;
+};
+
+__global__ __launch_bounds__(256) void prepass_kernel(PrepassParams a)
+{
+    __shared__ uint16_t tile[64][66];
+    const unsigned nq = a.gq.x * a.gq.y, nk = a.gk.x * a.gk.y;
+    unsigned i = blockIdx.x, bit;
+    bool seen;
+    if (i < nq) {
+        seen = rows_to_f32(a.q, a.qt, a.scale, a.N, a.Nq, a.D, a.BHq, a.blkq, i % a.gq.x, i / a.gq.x, a.gq.x, a.gq.y);
+        bit = 1u;
+    } else if (i < nq + nk) {
+        i -= nq;
+        seen = rows_to_f32(a.k, a.kt32, 1.0f, a.N, a.Nk, a.D, a.BHk, a.blkk, i % a.gk.x, i / a.gk.x, a.gk.x, a.gk.y);
+        bit = 2u;
+    } else {
+        const unsigned tiles = (unsigned)(a.Nk / 64) * (unsigned)(a.D / 64) * (unsigned)a.BHk;
+        seen = false;
+        for (unsigned t = i - nq - nk; t < tiles; t += a.nv) {
+            seen |= transpose_v_tile(a.v, a.vt, a.N, a.Nk, a.D, t, tile);
+            __syncthreads();   // the next tile's values replace this one's
+        }
+        bit = 4u;
+    }
+    if (a.bad) flag_nonfinite(a.bad, seen, bit);
 }
 
 // ------------------------------------------------------------------ tables
@@ -220,7 +244,7 @@ __global__ __launch_bounds__(64, 2) void logits8_kernel(LogitsParams p)
     const int r = rg * 64 + lane;
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
-    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
+    QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u, {0u}, false};
     for (int g = 0; g < NC; ++g) {
         const int key0 = (blockIdx.y * NC + g) * 16;
         const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
@@ -256,7 +280,7 @@ __global__ __launch_bounds__(64, 2) void logits16_kernel(LogitsParams p)
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
     const int key0 = blockIdx.y * 16;
-    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
+    QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u, {0u}, false};
     const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
     uint32_t codes[1][8];
     rec16_keys<D, 1, 16>(qr, keys16<RowLay<D>>(kt), codes);
@@ -284,7 +308,7 @@ __global__ __launch_bounds__(64, 2) void logits_sim_kernel(LogitsParams p)
     const int rr = r < p.nrows ? r : p.nrows - 1;
     const int j = p.row0 + rr;
     const int key0 = blockIdx.y * 16;
-    const QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u};
+    QRows<1> qr = {{p.qt + (((size_t)b * p.Hq + h) * p.N + p.row0) * D}, (uint32_t)rr * D * 4u, {0u}, false};
     const float *kt = p.kt32 + (((size_t)b * p.Hkv + hk) * p.N + key0) * (size_t)D;
     float val[16];
     if constexpr (HIGH) {
@@ -294,7 +318,16 @@ __global__ __launch_bounds__(64, 2) void logits_sim_kernel(LogitsParams p)
         for (int i = 0; i < 16; ++i) val[i] = y[0][i];
     } else {
         uint32_t w[1][8], sat[1];
+        set_qmin<D, 1, RowLay<D>>(qr);
         emu8_any<D, 1, true>(qr, keys16<RowLay<D>>(kt), w, sat);
+        // the fast rounding loses the sign of a zero, which this entry returns
+        bool zero = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zero |= (w[0][i >> 1] >> (16 * (i & 1)) & 0x7FFFu) == 0u;
+        if (wave_any(zero)) {
+            qr.exact = true;
+            emu8_any<D, 1, true>(qr, keys16<RowLay<D>>(kt), w, sat);
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) val[i] = bf16_value((w[0][i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
     }
@@ -335,37 +368,28 @@ __global__ void selftest_exp_doc_kernel(const double *__restrict__ x, double *__
 }
 
 // ------------------------------------------------------------------ launchers
-// Grid of the prepass kernels: 256-thread blocks over one head's float4
-// groups (x), heads (y); both capped, the kernels stride over the rest.
+// Workgroups of a part of the prepass: 256-thread ones over one head's float4
+// groups (x) and over the heads (y); capped (the kernel strides over the rest),
+// so that the launch stays below 2^32 threads.
+constexpr unsigned PREPASS_MAX = 1u << 21;
+
 static dim3 prepass_grid(int BH, int rows, int D)
 {
     const long n4 = (long)rows * (D / 4);
     const long gx = (n4 + 255) / 256;
-    return dim3((unsigned)(gx < 4096 ? (gx > 0 ? gx : 1) : 4096), (unsigned)(BH < 65535 ? (BH > 0 ? BH : 1) : 65535));
+    const unsigned x = (unsigned)(gx < 4096 ? (gx > 0 ? gx : 1) : 4096), my = PREPASS_MAX / x;
+    return dim3(x, (unsigned)BH < my ? (BH > 0 ? (unsigned)BH : 1u) : my);
 }
 
-hipError_t launch_prepass(const uint16_t *q, const uint16_t *k, float *qt, float *kt32, int B, int Hq, int Hkv,
-                          int N, int Nq, int Nk, int D, float scale, hipStream_t s, bool grouped, unsigned *bad)
+hipError_t launch_prepass(const uint16_t *q, const uint16_t *k, const uint16_t *v, float *qt, float *kt32, uint16_t *vt,
+                          int B, int Hq, int Hkv, int N, int Nq, int Nk, int D, float scale, hipStream_t s, bool grouped,
+                          unsigned *bad)
 {
-    hipLaunchKernelGGL(prescale_q_kernel, prepass_grid(B * Hq, Nq, D), dim3(256), 0, s, q, qt, scale, N, Nq, D, B * Hq,
-                       grouped ? 64 : 0, bad, 1u);
-    hipLaunchKernelGGL(convert_k_kernel, prepass_grid(B * Hkv, Nk, D), dim3(256), 0, s, k, kt32, N, Nk, D, B * Hkv,
-                       grouped ? 16 : 0, bad);
-    return hipGetLastError();
-}
-
-hipError_t launch_prescale_q(const uint16_t *q, float *qt, int BH, int rows, int D, float scale, hipStream_t s)
-{
-    hipLaunchKernelGGL(prescale_q_kernel, prepass_grid(BH, rows, D), dim3(256), 0, s, q, qt, scale, rows, rows, D, BH, 0,
-                       (unsigned *)nullptr, 0u);
-    return hipGetLastError();
-}
-
-hipError_t launch_transpose_v(const uint16_t *v, uint16_t *vt, int B, int Hkv, int N, int Nk, int D, hipStream_t s,
-                              unsigned *bad)
-{
-    hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)(Nk / 64), (unsigned)(D / 64), (unsigned)(B * Hkv)),
-                       dim3(256), 0, s, v, vt, N, Nk, D, bad);
+    const uint64_t tiles = v ? (uint64_t)(Nk / 64) * (uint64_t)(D / 64) * (uint64_t)B * Hkv : 0;
+    PrepassParams a{q, k, v, qt, kt32, vt, N, Nq, Nk, D, B * Hq, B * Hkv, grouped ? 64 : 0, grouped ? 16 : 0, scale,
+                    prepass_grid(B * Hq, Nq, D), prepass_grid(B * Hkv, Nk, D),
+                    (unsigned)(tiles < PREPASS_MAX ? tiles : PREPASS_MAX), bad};
+    hipLaunchKernelGGL(prepass_kernel, dim3(a.gq.x * a.gq.y + a.gk.x * a.gk.y + a.nv), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -45,6 +45,11 @@ __device__ __forceinline__ f32x4_t rank1(float kv, float q, f32x4_t c)
     return __builtin_amdgcn_mfma_f32_4x4x1f32(kv, q, c, 4, ABID, 0);
 }
 
+// A key that orders the nonzero magnitudes (zero last): the pattern without its
+// sign, doubled, minus one; bits [31:24] are at most the biased exponent.
+__device__ __forceinline__ uint32_t min_bits(float x) { return (__builtin_bit_cast(uint32_t, x) << 1) - 1u; }
+__device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
 // Where the loops find the fp32 queries and keys.  Row layout ([row][D]): the
 // 4-channel group g of a row is at offset 4g and consecutive keys are D apart.
 // Grouped layout (the pipelined kernel): queries in blocks of 64 rows and keys
@@ -61,10 +66,14 @@ using GrpLay = Lay<256, 64, 4>;
 
 // The query rows of a wave: slot s of a lane at base[s] (uniform) + off bytes
 // (the lane's own), so that the loads keep one offset register.
+// SIM profile only: qmin, min_bits over each row (set_qmin), and whether the
+// 8-bit loop has left the range of its fast rounding (uniform).
 template <int QPL>
 struct QRows {
     const float *base[QPL];
     uint32_t off;
+    uint32_t qmin[QPL];
+    bool exact;
     __device__ __forceinline__ const float *row(int s) const
     {
         return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base[s]) + off);
@@ -162,16 +171,32 @@ __device__ __forceinline__ void emu8_row(float ke, float kr, float q, uint32_t (
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The 8-bit SIM rounding of a value that is 0 or has 2^-126 <= |t| < 2^107, in
+// two FMA-class operations instead of three integer ones (2.3 against 4.8 ns per
+// 64 values and SIMD).  With t = m 2^(e-23) and q = 2^(e-3) the quantum to round
+// to, t (2^20 - 1) = (m - m 2^-20) q rounded to FP32 is m - RN(m 2^-20) quanta,
+// ties to even since m is even there, and t 2^20 = m q minus it is t rounded
+// (Dekker's splitting).  Below 2^23 quanta, m < 2^23 + 8, the product's ulp is
+// q/2, but m 2^-20 then lies within 2^-17 of 8 and rounds to it all the same; a
+// factor 2^20 + 1 would not do: above 2^24 quanta its ulp is 2q, and an odd m
+// rounds to 15 instead of 16.  c1 = -(2^20 - 1), c2 = 2^20.
+__device__ __forceinline__ float rn_sim3_normal(float t, float c1, float c2)
+{
+    const float s = t * c1;
+    return __builtin_fmaf(t, c2, s);
+}
+
 // The loop over the channels: the 8-bit accumulation of the 16 keys of ke
 // (EMU; in the SIM profile on FP32 values in e8, otherwise on the codes w8;
-// SAT: saturating) and the FMA chains of NM groups of 4 keys of kr, sharing
+// EXACT: saturating, or in the SIM profile the rounding that holds for every
+// FP32 value) and the FMA chains of NM groups of 4 keys of kr, sharing
 // the query loads.  The queries come PD 4-channel groups ahead, the keys a
 // 16-channel block ahead (the last block's loads wrap to the first channels
 // and are not used).
-template <int D, int QPL, int NM, bool EMU, bool SIMP, bool SAT, int PD, class LY>
+template <int D, int QPL, int NM, bool EMU, bool SIMP, bool EXACT, int PD, class LY>
 __device__ __forceinline__ void logit_loop(const QRows<QPL> &qr, const KRows &ke, const KRows &kr,
                                            uint32_t (&w8)[QPL][4], f32x4_t (&e8)[QPL][SIMP && EMU ? 4 : 1],
-                                           f32x4_t (&acc)[QPL][NM > 0 ? NM : 1])
+                                           f32x4_t (&acc)[QPL][NM > 0 ? NM : 1], uint32_t &kmin)
 {
     static_assert(D % 16 == 0 && (PD == 2 || PD == 4), "16-channel blocks");
     f32x4_t q4[PD][QPL], kea, keb, kra, krb;
@@ -184,6 +209,8 @@ __device__ __forceinline__ void logit_loop(const QRows<QPL> &qr, const KRows &ke
 #pragma unroll
         for (int s = 0; s < QPL; ++s) q[s] = load4v(qr.base[s] + g * LY::QS, qoff);
     };
+    float c1 = -1048575.0f, c2 = 1048576.0f;   // kept in vector registers (a scalar operand issues slower)
+    if constexpr (EMU && SIMP && !EXACT) asm volatile("" : "+v"(c1), "+v"(c2));
     ldk(0, kea, kra);
 #pragma unroll
     for (int r = 0; r < PD; ++r) ldq(r, q4[r]);
@@ -195,15 +222,18 @@ __device__ __forceinline__ void logit_loop(const QRows<QPL> &qr, const KRows &ke
             for (int s = 0; s < QPL; ++s) {
                 const float q = q4[R % PD][s][cc];
                 if constexpr (EMU && !SIMP) {
-                    emu8_row<R, SAT, NM>(e[cc], NM > 0 ? k[cc] : 0.0f, q, w8[s], acc[s]);
+                    emu8_row<R, EXACT, NM>(e[cc], NM > 0 ? k[cc] : 0.0f, q, w8[s], acc[s]);
                 } else {
                     if constexpr (EMU) fma_groups<R>(e[cc], q, e8[s], std::make_integer_sequence<int, 4>());
                     if constexpr (NM > 0) fma_groups<R>(k[cc], q, acc[s], std::make_integer_sequence<int, NM>());
                     if constexpr (EMU) {
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int g = 0; g < 4; ++g)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) e8[s][g][i] = rn_sim<3>(e8[s][g][i]);
+                            for (int i = 0; i < 4; ++i)
+                                e8[s][g][i] = EXACT ? rn_sim<3>(e8[s][g][i]) : rn_sim3_normal(e8[s][g][i], c1, c2);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
@@ -216,6 +246,10 @@ __device__ __forceinline__ void logit_loop(const QRows<QPL> &qr, const KRows &ke
         // base plus a 32-bit lane offset
         asm volatile("" : "+v"(qoff), "+v"(eoff), "+v"(roff));
         ldk(c + 16 < D ? c + 16 : 0, keb, krb);
+        if constexpr (EMU && SIMP && !EXACT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kmin = min_u32(kmin, min_bits(kea[i]));
+        }
         group(std::integral_constant<int, 0>(), c, kea, kra);
         group(std::integral_constant<int, 1>(), c, kea, kra);
         group(std::integral_constant<int, 2>(), c, kea, kra);
@@ -235,7 +269,8 @@ __device__ __forceinline__ void emu8_pass(const QRows<QPL> &qr, const KRows &ke,
     for (int s = 0; s < QPL; ++s)
 #pragma unroll
         for (int g = 0; g < 4; ++g) w[s][g] = 0u;
-    logit_loop<D, QPL, 0, true, false, SAT, 2, LY>(qr, ke, ke, w, none, none);
+    uint32_t kmin;
+    logit_loop<D, QPL, 0, true, false, SAT, 2, LY>(qr, ke, ke, w, none, none, kmin);
 }
 
 // Nonzero iff one of the four codes of a word is a NaN code (bits 7, 15, 23, 31).
@@ -283,6 +318,46 @@ __device__ __forceinline__ void emu8_check(const QRows<QPL> &qr, const KRows &ke
 }
 
 // ---- the SIM profile (Sec. 4.1): FP32 range, 3 / 11 mantissa bits, no saturation
+// Smallest nonzero magnitudes of a lane's query rows.
+template <int D, int QPL, class LY>
+__device__ __forceinline__ void set_qmin(QRows<QPL> &qr)
+{
+#pragma unroll
+    for (int s = 0; s < QPL; ++s) {
+        uint32_t m = 0xFFFFFFFFu;
+        for (int g = 0; g < D / 4; ++g) {
+            const f32x4_t v = load4v(qr.base[s] + g * LY::QS, qr.off);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m = min_u32(m, min_bits(v[i]));
+        }
+        qr.qmin[s] = m;
+    }
+    qr.exact = false;
+}
+
+// Whether a pass with rn_sim3_normal rounded some step outside its range (then
+// the chunk is recomputed with rn_sim).  Above: an overflow gives an infinity or
+// a NaN, which stays to the end of the chain.  Below: every sum and every
+// rounded value is a multiple of the product of the smallest quanta of the row
+// and the keys, 2^(eq-23) and 2^(ek-7) (bf16 keys), so with eq + ek >= -96 a
+// nonzero one is at least 2^-126.
+template <int QPL>
+__device__ __forceinline__ bool sim8_out_of_range(const QRows<QPL> &qr, uint32_t kmin, const f32x4_t (&e8)[QPL][4])
+{
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) kmin = min_u32(kmin, (uint32_t)__shfl_xor((int)kmin, m, 64));
+    bool bad = false;
+#pragma unroll
+    for (int s = 0; s < QPL; ++s) {
+        bad |= (qr.qmin[s] >> 24) + (kmin >> 24) < 2 * 127 - 96;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bad |= !(__builtin_fabsf(e8[s][g][i]) < __builtin_inff());
+    }
+    return wave_any(bad);
+}
+
 // Two SIM 8-bit logits as their bf16 patterns (exact: 3 mantissa bits).
 __device__ __forceinline__ uint32_t pack_sim8(float a, float b)
 {
@@ -308,7 +383,7 @@ __device__ __forceinline__ void round16(const f32x4_t (&acc)[QPL][NM], float (&y
 // 8-bit logits (Y8_WORDS), y16 the 16-bit ones as FP32 values, sat the saturated keys of the
 // 8-bit chunk (0 in the SIM profile, which does not saturate).
 template <int D, int QPL, int NKEY, bool EMU, bool SIMP, class LY = RowLay<D>>
-__device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke, const KRows &kr,
+__device__ __forceinline__ void fused_pass(QRows<QPL> &qr, const KRows &ke, const KRows &kr,
                                            uint32_t (&a8)[QPL][Y8_WORDS<SIMP>], float (&y16)[QPL][NKEY > 0 ? NKEY : 1],
                                            uint32_t (&sat)[QPL])
 {
@@ -327,8 +402,24 @@ __device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke
 #pragma unroll
         for (int g = 0; g < NE; ++g) e8[s][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    logit_loop<D, QPL, NM, EMU, SIMP, false, EMU ? 2 : 4, LY>(qr, ke, kr, w8, e8, acc);
+    uint32_t kmin = 0xFFFFFFFFu;
+    if (!(EMU && SIMP) || !qr.exact)
+        logit_loop<D, QPL, NM, EMU, SIMP, false, EMU ? 2 : 4, LY>(qr, ke, kr, w8, e8, acc, kmin);
     if constexpr (EMU && SIMP) {
+        // out of range once: the rest of the workgroup's tiles at once exactly
+        f32x4_t none[QPL][1];
+        if (qr.exact) {
+            if constexpr (NM > 0) logit_loop<D, QPL, NM, false, true, false, 4, LY>(qr, kr, kr, w8, none, acc, kmin);
+        } else {
+            qr.exact = sim8_out_of_range<QPL>(qr, kmin, e8);
+        }
+        if (qr.exact) {
+#pragma unroll
+            for (int s = 0; s < QPL; ++s)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) e8[s][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            logit_loop<D, QPL, 0, true, true, true, 2, LY>(qr, ke, ke, w8, e8, none, kmin);
+        }
 #pragma unroll
         for (int s = 0; s < QPL; ++s)
 #pragma unroll
@@ -345,7 +436,7 @@ __device__ __forceinline__ void fused_pass(const QRows<QPL> &qr, const KRows &ke
 
 // Y8 of a 16-key chunk in either profile (sat as in emu8_check).
 template <int D, int QPL, bool SIMP, class LY = RowLay<D>>
-__device__ __forceinline__ void emu8_any(const QRows<QPL> &qr, const KRows &ke, uint32_t (&a8)[QPL][Y8_WORDS<SIMP>],
+__device__ __forceinline__ void emu8_any(QRows<QPL> &qr, const KRows &ke, uint32_t (&a8)[QPL][Y8_WORDS<SIMP>],
                                          uint32_t (&sat)[QPL])
 {
     float none[QPL][1];
@@ -357,7 +448,7 @@ __device__ __forceinline__ void emu8_any(const QRows<QPL> &qr, const KRows &ke, 
 // (saturating), as FP32 values.  Lane l of every 16-lane row of kr supplies key
 // (l mod 16) and must hold key (l mod NKEY) (lanes past NKEY are not read).
 template <int D, int QPL, int NKEY, bool SIMP = false, class LY = RowLay<D>>
-__device__ __forceinline__ void rec16_values(const QRows<QPL> &qr, const KRows &kr, float (&y)[QPL][NKEY])
+__device__ __forceinline__ void rec16_values(QRows<QPL> &qr, const KRows &kr, float (&y)[QPL][NKEY])
 {
     uint32_t none[QPL][Y8_WORDS<SIMP>], sat[QPL];
     fused_pass<D, QPL, NKEY, false, SIMP, LY>(qr, kr, kr, none, y, sat);
@@ -365,7 +456,7 @@ __device__ __forceinline__ void rec16_values(const QRows<QPL> &qr, const KRows &
 
 // The same as e4m11 codes: codes[s][p] holds keys 2p (bits [15:0]) and 2p+1.
 template <int D, int QPL, int NKEY, class LY = RowLay<D>>
-__device__ __forceinline__ void rec16_keys(const QRows<QPL> &qr, const KRows &kr, uint32_t (&codes)[QPL][NKEY / 2])
+__device__ __forceinline__ void rec16_keys(QRows<QPL> &qr, const KRows &kr, uint32_t (&codes)[QPL][NKEY / 2])
 {
     float y[QPL][NKEY];
     rec16_values<D, QPL, NKEY, false, LY>(qr, kr, y);
