@@ -587,19 +587,39 @@ struct RowDecider {
         const bool in = jl < nt;
         const uint64_t cw = in ? words(jl, sub) : 0ull;
         const int key0 = tj * TK + CH * sub;
-        float mxl = NEG_INF, sf = 0.0f;
-        double sl = 0.0;
+        // a wave's decisions are one dependent chain, so what counts here is
+        // the number of instructions: codes decoded in pairs, all table reads
+        // issued before the first sum, and no per-key visibility test where
+        // every key of the run is visible (a uniform branch)
+        float y[CH], e[CH];
+#pragma unroll
+        for (int k = 0; k < CH; k += 2) {
+            const float2 v = unpk_e4m3x4((uint32_t)(cw >> (32 * (k / 4))), (k / 2) & 1);
+            y[k] = v.x;
+            y[k + 1] = v.y;
+        }
+        const bool full = nt == CH && t * TK >= vlo && (t + CH) * TK - 1 <= vhi;
+        if (!full) {
+#pragma unroll
+            for (int k = 0; k < CH; ++k) y[k] = in && key0 + k >= vlo && key0 + k <= vhi ? y[k] : NEG_INF;
+        }
+        uint32_t lb[CH];   // a shift of +inf (an invisible key) reads the table's last entry, 0
+#pragma unroll
+        for (int k = 0; k < CH; ++k) lb[k] = lut[ue5m3_code(shift_of(mu, y[k]))];
+        float mxl = y[0];
+#pragma unroll
+        for (int k = 1; k < CH; ++k) mxl = __builtin_fmaxf(mxl, y[k]);
+#pragma unroll
+        for (int k = 0; k < CH; ++k) e[k] = bf16_value(lb[k]);
+        // (the fp64 sum is exact in any order)
+        double sd[2] = {0.0, 0.0};
+        float sf = 0.0f;
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
-            const int key = key0 + k;
-            const bool vis = in && key >= vlo && key <= vhi;
-            const uint8_t code = (uint8_t)(cw >> (8 * k));
-            const float y = vis ? e4m3_value(code) : NEG_INF;
-            mxl = y > mxl ? y : mxl;
-            const float e = vis ? bf16_value(lut[ue5m3_code(shift_of(mu, y))]) : 0.0f;
-            sl += (double)e;
-            sf += e;
+            sd[k & 1] += (double)e[k];
+            sf += e[k];
         }
+        double sl = sd[0] + sd[1];
         // reductions over the lanes of each tile (quad neighbours, quad
         // pairs, half-row mirror, and for 16 lanes the row mirror)
         {
@@ -619,27 +639,27 @@ struct RowDecider {
                 if (LPT == 16) sf += dpp_f32<0x140>(sf);
             }
         }
-        // the look-ahead test of every tile at once (lane LPT j holds tile j's
-        // maximum), then the omega chain and the quick acceptance tile by tile
-        // up to the first failure, without branches
+        // the look-ahead test of every tile at once (lane LPT j holds tile j's maximum)
         const double m = (double)mu;
         const bool passl = MODE == MODE_PURE8 ? !(mxl > mu) : m > __builtin_fma(__builtin_fabs(m), p->delta, (double)mxl);
         constexpr uint64_t heads = LPT == 8 ? 0x0101010101010101ull : 0x0001000100010001ull;
         const uint64_t fails = ~__ballot(passl) & heads & (nt < CH ? (1ull << (LPT * nt)) - 1ull : ~0ull);
         int jc = fails ? __builtin_ctzll(fails) / LPT : nt;   // tiles committed
-        double omv = om;
+        // the omega chain over all tiles, then every tile's acceptance at once:
+        // the values before the first failure are those of the committed tiles
+        double ch[CH];
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const double omh = __builtin_fma(1.0, omv, readlane_f64(sl, LPT * j));
-            bool ok = true;
-            if (MODE == MODE_LAMP) {
+        for (int j = 0; j < CH; ++j) ch[j] = (j > 0 ? ch[j - 1] : om) + readlane_f64(sl, LPT * j);
+        if (MODE == MODE_LAMP) {
+#pragma unroll
+            for (int j = CH - 1; j >= 0; --j) {
                 const double SF = (double)readlane_f32(sf, LPT * j) * (1.0 + 0x1p-17);
-                ok = SF <= (p->tau * omh) * (1.0 - 0x1p-38);
+                const bool ok = SF <= (p->tau * ch[j]) * (1.0 - 0x1p-38);
+                jc = !ok && j < jc ? j : jc;
             }
-            jc = (j < jc && !ok) ? j : jc;
-            omv = j < jc ? omh : omv;
         }
-        om = omv;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) om = j == jc - 1 ? ch[j] : om;
 #pragma unroll
         for (int j = 0; j < CH; ++j)
             if (j < jc) record_tile(t + j, mu, 1.0);
