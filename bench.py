@@ -420,11 +420,13 @@ def run_fwd(args, w, tau, flags, host_inputs, dev_inputs, out, dev):
     sim = bool(flags & SIM_FLAG)
     # the multiply-adds alone at the issue rates measured on this device: one
     # emulated 8-bit step is two multiply-adds per lane (128 per wave), one
-    # SIM step one (64 per wave), one 16-bit FMA with its broadcast key one
+    # SIM step one (64 per wave)
     rates = lamp.issue_rates()
     simds = 4 * torch.cuda.get_device_properties(dev).multi_processor_count
     step8 = rates["emulated_step_sim"] / 64.0 if sim else rates["emulated_step"] / 128.0
-    floor_ms = (mac8 * step8 + mac16 / 64.0 * rates["fmac_f32_dpp"]) / simds * 1e-6
+    # a 16-bit multiply-add: what an 8-bit step takes beside its conversions
+    mac16_ns = rates["emulated_step"] / 2.0 - (rates["cvt_pk_f32_fp8"] + rates["cvt_pk_fp8_f32"]) / 2.0
+    floor_ms = (mac8 * step8 + mac16 / 64.0 * max(mac16_ns, 0.0)) / simds * 1e-6
     issue_floor = None if sr else {
         "ms": floor_ms, "frac": floor_ms / kernel_ms,
         "ns_per_wave_instruction_per_simd": rates,

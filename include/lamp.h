@@ -254,11 +254,11 @@ enum {
      * graph (LAMP_ERR_INVALID_ARG).  Applies in every mode. */
     LAMP_CHECK_FINITE = 8,
     /* The compact register layout of Sec. 3.3 ("Register layout") as the
-     * kernel's schedule: 8-bit accumulators four per 32-bit register, room
-     * for one 16-bit sub-block in the fused 8-bit pass, and a sequential
-     * 16-bit pass for "disruptive" tiles where two or more sub-blocks are
-     * flagged.  Results are bit-identical to the default (safe) layout.
-     * Applies to the pipelined kernel (b_k = 16, N_k = 4, d >= 128) at
+     * kernel's schedule: 8-bit accumulators four per 32-bit register (as by
+     * default), room for one 16-bit sub-block in the fused 8-bit pass, and a
+     * sequential 16-bit pass for "disruptive" tiles where two or more
+     * sub-blocks are flagged.  Results are bit-identical to the default
+     * schedule.  Applies to the pipelined kernel (b_k = 16, N_k = 4, d >= 128) at
      * b_q = 128 in the threshold mode with the formats of Sec. 3.3; the flag
      * has no effect elsewhere. */
     LAMP_COMPACT = 16
@@ -405,9 +405,9 @@ int lamp_timing_read(int *launches, double *fwd_ms, double *prepass_ms);
  * of: [0] an fp32 FMA on VGPR operands, [1] an fp32 FMA reading its first
  * operand through a DPP row broadcast, [2] a packed e4m3 -> fp32 decode,
  * [3] a packed fp32 -> e4m3 rounding, [4] per emulated step of the 8-bit
- * loop (decode, two broadcast FMAs, rounding: two multiply-adds per lane),
- * and [5] per emulated step of the SIM profile's 8-bit loop (a broadcast FMA
- * and the 3-instruction rounding of the FP32 pattern: one multiply-add).
+ * loop (decode, matrix instructions, rounding: two multiply-adds per lane),
+ * and [5] per emulated step of the SIM profile's 8-bit loop (one multiply-add
+ * and its rounding).
  * Each kind runs 16 independent chains per lane at 8 waves per SIMD.  The
  * call allocates a small device buffer, runs on `stream` and waits for it;
  * it takes a few milliseconds.

@@ -18,7 +18,7 @@
 // tile t-1 (the set F0; the test is monotone in mu_hat and mu_hat only grows,
 // so every sub-block stage 1 recomputes is in F0; one that is not takes the
 // one-at-a-time path).  So one fused pass over the channels computes the
-// 16-bit logits of F0(t) (4 keys of each member per wave, codes kept in
+// 16-bit logits of F0(t) (4 keys of each member per wave, kept in
 // registers) together with the 8-bit logits of this wave's sub-block of tile
 // t+1 (codes to the other half of a double-buffered LDS array).  Per tile:
 //   A. fused pass: 16-bit logits of F0(t), 8-bit logits of tile t+1;
@@ -1425,8 +1425,8 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
 // longest, fill the compute units once: a causal pass of 512 blocks (half as
 // long on average as the longest) takes 1.05 against 1.20 ms, of 640 blocks
 // 1.64 against 1.56; blocks of equal length 0.93 against 1.01 ms at 256 and
-// 1.82 against 1.67 at 512 (d = 128; the same side at d = 256, in the
-// simulation profile and with stochastic rounding).
+// 1.82 against 1.67 at 512 (d = 128; the same side, within 2 %, at d = 64 and
+// 256, in the simulation profile and with stochastic rounding).
 inline bool fwd16_wide(const FwdParams &p, int BQ)
 {
     const int64_t blocks = (int64_t)p.B * p.Hq * (p.Nq / BQ);

@@ -3,18 +3,19 @@
 //
 // The forward kernel is bound by VALU issue, and not every instruction it
 // issues takes one issue slot: on gfx950 a plain fp32 FMA on VGPR operands
-// issues faster than one that reads its key through a DPP broadcast, and the
-// packed fp32 -> e4m3 conversion takes about two slots.  The published VALU
-// peak therefore overstates what the emulated 8-bit accumulation can reach.
-// These kernels time each instruction kind (16 independent chains per lane,
-// 8 waves per SIMD, so that issue and not latency binds) and the complete
-// emulated step of the 8-bit loop (decode a code pair, two broadcast FMAs,
-// round the pair back), giving the instruction-mix floor the benchmark sets
-// beside the measured kernel time.
+// issues faster than one that reads its key through a DPP broadcast (the
+// stochastic-rounding loop), and the packed fp32 -> e4m3 conversion takes about
+// two slots.  The published VALU peak therefore overstates what the emulated
+// 8-bit accumulation can reach.  These kernels time each instruction kind (16
+// independent chains per lane, 8 waves per SIMD, so that issue and not latency
+// binds) and the complete steps of the 8-bit loops as the kernels run them
+// (lamp_loops.h), giving the instruction-mix floor the benchmark sets beside
+// the measured kernel time.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "lamp_kernels.h"
+#include "lamp_loops.h"
 
 namespace lamp {
 
@@ -99,58 +100,53 @@ __global__ __launch_bounds__(256) void rate_encode_kernel(float *out, int iters,
     out[blockIdx.x * blockDim.x + threadIdx.x] = (float)s;
 }
 
-// the emulated step of the 8-bit loop: two multiply-adds (decode, two
-// broadcast FMAs, round back), on two fixed temporaries
-__global__ __launch_bounds__(256) void rate_step_kernel(float *out, int iters, float q)
+// the step of the 8-bit loop: one channel of two query rows and 16 keys (decode,
+// rank-1 matrix instructions, round back), 32 multiply-adds per lane, counted
+// as 16 steps of two
+__global__ __launch_bounds__(256, 8) void rate_step_kernel(float *out, int iters, float q)
 {
-    uint32_t a[16];
+    uint32_t w[2][4];
+    f32x4_t none[1] = {f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}};
     const float k = (float)threadIdx.x * 1e-3f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) a[i] = (uint32_t)i * 0x0101u;
-    asm volatile("s_nop 4");
-    for (int it = 0; it < iters; ++it) {
-#define LAMP_F(i)                                                                        \
-    asm volatile("v_cvt_pk_f32_fp8 v[40:41], %0\n\t"                                     \
-                 "v_fmac_f32_dpp v40, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t" \
-                 "v_fmac_f32_dpp v41, %1, %2 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t" \
-                 "v_cvt_pk_fp8_f32 %0, v40, v41"                                         \
-                 : "+v"(a[i])                                                            \
-                 : "v"(k), "v"(q)                                                        \
-                 : "v40", "v41");
-        LAMP_REP16(LAMP_F)
-#undef LAMP_F
-    }
-    uint32_t s = 0;
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s += a[i];
-    out[blockIdx.x * blockDim.x + threadIdx.x] = (float)s;
+        for (int g = 0; g < 4; ++g) w[s][g] = (uint32_t)(4 * s + g) * 0x01010101u;
+    for (int it = 0; it < iters; ++it) {
+        emu8_row<0, false, 0>(k, 0.0f, q, w[0], none);
+        emu8_row<0, false, 0>(k, 0.0f, q, w[1], none);
+    }
+    uint32_t sum = 0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) sum += w[s][g];
+    out[blockIdx.x * blockDim.x + threadIdx.x] = (float)sum;
 }
 
-// the emulated step of the SIM profile's 8-bit loop: one broadcast FMA and
-// the round-to-nearest-even of the FP32 pattern to 3 mantissa bits (last kept
-// bit extracted, one 3-input add, one mask), per multiply-add
-__global__ __launch_bounds__(256) void rate_step_sim_kernel(float *out, int iters, float q)
+// the step of the SIM profile's 8-bit loop: one channel of 16 keys (rank-1
+// matrix instructions, rounding to 3 mantissa bits), counted as 16 steps of one
+// multiply-add
+__global__ __launch_bounds__(256, 8) void rate_step_sim_kernel(float *out, int iters, float q)
 {
-    float a[16];
+    f32x4_t e[4];
     const float k = (float)threadIdx.x * 1e-3f;
+    float c1 = -1048575.0f, c2 = 1048576.0f;
+    asm volatile("" : "+v"(c1), "+v"(c2));
 #pragma unroll
-    for (int i = 0; i < 16; ++i) a[i] = (float)i * 1e-3f;
-    asm volatile("s_nop 4");
+    for (int g = 0; g < 4; ++g) e[g] = f32x4_t{q, k, q + k, (float)g};
     for (int it = 0; it < iters; ++it) {
-#define LAMP_F(i)                                                                                     \
-    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n\t"           \
-                 "v_bfe_u32 v40, %0, 20, 1\n\t"                                                      \
-                 "v_add3_u32 %0, %0, v40, %4\n\t"                                                    \
-                 "v_and_b32 %0, %5, %0"                                                              \
-                 : "+v"(a[i])                                                                        \
-                 : "v"(k), "v"(q), "n"(i), "v"(0x7FFFFu), "v"(0xFFF00000u)                           \
-                 : "v40");
-        LAMP_REP16(LAMP_F)
-#undef LAMP_F
+        fma_groups<0>(k, q, e, std::make_integer_sequence<int, 4>());
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[g][i] = rn_sim3_normal(e[g][i], c1, c2);
+        __builtin_amdgcn_sched_barrier(0);
     }
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s += a[i];
+    for (int g = 0; g < 4; ++g) s += (e[g][0] + e[g][1]) + (e[g][2] + e[g][3]);
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
