@@ -389,7 +389,7 @@ static int fwd_impl(const uint16_t *q, const uint16_t *k, const uint16_t *v, int
     p.Nq = Nq;
     p.Nk = Nk;
     p.causal = causal;
-    p.window = window;
+    p.window = window < N ? window : N;   // a longer one hides nothing; key + window stays in int range
     p.delta = delta;
     p.tau = tau;
     p.mode = std::isinf(tau) ? lamp::MODE_PURE8 : (tau == 0.0 ? lamp::MODE_ALL16 : lamp::MODE_LAMP);

@@ -27,7 +27,7 @@ struct FwdParams {
     uint8_t *mask;            // [B][Hq][N/BQ][N/BK]
     int B, Hq, Hkv, N;        // N: sequence length (visibility, O / lse rows)
     int Nq, Nk;               // padded lengths: rows of qt, keys of kt32 / vt (whole blocks / tiles)
-    int causal, window, mode;
+    int causal, window, mode; // window: 0 (none) to N
     unsigned flags;           // LAMP_SIM_PROFILE; LAMP_STAGE1_OFF | LAMP_MU_TRUNC in the threshold mode
     double delta, tau;
     uint64_t seed;            // key of the stochastic-rounding generator (dispatch_fwd_sr)
