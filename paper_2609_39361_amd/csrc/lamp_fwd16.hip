@@ -440,9 +440,10 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
     // mu_hat_j > fma(|mu_hat_j|, delta, m8); columns without a visible entry
     // are not tested; mu_hat = -inf fails.  m8 from LDS, identical in every wave.
     auto fails = [&](float m8v, float mhv) {
-        // mu_hat = -inf as a finite number below every logit: a visible logit
-        // then fails and a column without one (m8 = -inf) passes, as required
-        const double m = (double)__builtin_fmaxf(mhv, -0x1p100f);
+        // mu_hat = -inf as FP32's lowest number, at or below every logit (those
+        // of the SIM profile span FP32): a visible logit then fails and a
+        // column without one (m8 = -inf) passes, as required
+        const double m = (double)__builtin_fmaxf(mhv, -0x1.fffffep127f);
         return !(m > __builtin_fma(__builtin_fabs(m), p.delta, (double)m8v));
     };
     auto fails_of = [&](const float (&m8)[NK][HS], const float (&mh)[HS]) {
