@@ -1448,22 +1448,25 @@ static hipError_t launch_fwd16_wr(const FwdParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
+// The form of a call, the same with and without the observables.
+template <int D, int BQ, int MODE, bool SIMP, bool OBS, bool SR>
+static hipError_t launch_fwd16_form(const FwdParams &p, hipStream_t s)
+{
+    if constexpr (BQ == 128) {
+        // the compact schedule: threshold mode, hardware formats, 128-row blocks, d >= 128
+        if constexpr (MODE == MODE_LAMP && !SIMP && !SR && D >= 128)
+            if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, true>(p, s);
+        if (!fwd16_wide(p, BQ)) return launch_fwd16_wr<D, BQ, 128, MODE, SIMP, OBS, false, SR>(p, s);
+    }
+    return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, false, SR>(p, s);
+}
+
 template <int D, int BQ, int MODE, bool SIMP, bool SR = false>
 static hipError_t launch_fwd16_mode(const FwdParams &p, hipStream_t s)
 {
     if constexpr (!SIMP)
-        if (p.dbg_y8 || p.dbg_y16) {
-            if constexpr (MODE == MODE_LAMP && !SR && BQ == 128 && D >= 128)
-                if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, false, true, true>(p, s);
-            return launch_fwd16_wr<D, BQ, 64, MODE, false, true, false, SR>(p, s);
-        }
-    if constexpr (BQ == 128) {
-        // the compact schedule: threshold mode, hardware formats, 128-row blocks, d >= 128
-        if constexpr (MODE == MODE_LAMP && !SIMP && !SR && D >= 128)
-            if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, false, true>(p, s);
-        if (!fwd16_wide(p, BQ)) return launch_fwd16_wr<D, BQ, 128, MODE, SIMP, false, false, SR>(p, s);
-    }
-    return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, false, false, SR>(p, s);
+        if (p.dbg_y8 || p.dbg_y16) return launch_fwd16_form<D, BQ, MODE, SIMP, true, SR>(p, s);
+    return launch_fwd16_form<D, BQ, MODE, SIMP, false, SR>(p, s);
 }
 
 template <int D, int BQ, bool SIMP>

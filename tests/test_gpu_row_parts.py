@@ -4,13 +4,17 @@ grids are compared with the oracle elsewhere: here a large grid (640 blocks of
 ragged, windowed or grouped sequences) is compared with its first and last
 sequence alone, which take the 64-row form.  Every value has to be equal: the
 masks are decisions, lse and O come from the same operations in the same
-order."""
+order.  The large grid's own logits and statistics are compared with the
+oracle."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2609_39361_amd import workloads as W
+import test_gpu_observe as OBS
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +47,30 @@ def test_large_grid_equals_its_parts(L, d, N, causal, window, flags, seed, tau):
         assert torch.equal(mask[b], pm[0])
         assert torch.equal(lse[b], pl[0])
         assert torch.equal(o[b], po[0]), float((o[b] - po[0]).abs().max())
+
+
+@pytest.mark.parametrize("d,N,flags,seed,gain,tau", [
+    (128, 140, 0, None, 8.0, math.inf), (128, 140, 0, None, 8.0, 0.5), (128, 140, 0, None, 1.0, 2.0 ** -5),
+    (128, 140, 0, None, 8.0, 0.0), (64, 130, 0, None, 8.0, math.inf), (64, 130, 0, None, 8.0, 0.5),
+    (256, 130, 0, None, 1.0, 0.5), (256, 130, 0, None, 1.0, 2.0 ** -5), (128, 140, 16, None, 8.0, 0.5),
+    (256, 130, 16, None, 1.0, 2.0 ** -5), (128, 130, 0, 11, 1.0, 0.5), (64, 130, 0, 11, 1.0, math.inf)])
+def test_large_grid_observables_and_statistics(L, d, N, flags, seed, gain, tau):
+    """The 128-row form's 8-bit and used 16-bit codes on sampled heads and its
+    statistics words (saturations of both formats among them), against the
+    oracle; observed and timed instantiations give the same results."""
+    w = W.small(B=4, Hq=72, Hkv=8, N=N, d=d, bq=128, bk=16, nk=4, seed=N + d, extra={"gain": gain})
+    q, k, v = W.make_inputs(w)
+    dev = tuple(t.cuda() for t in (q, k, v))
+    st = torch.zeros(L.stats_words(w.nk), dtype=torch.int64, device="cuda")
+    timed = L.attn_fwd(*dev, tau=tau, flags=flags, sr_seed=seed, stats=st)
+    seen = OBS._check_observables(L, w, tau, 0, 2, heads=[(0, 0), (1, 41), (3, 71)], flags=flags, sr_seed=seed,
+                                  q=(q, k, v) + dev)
+    assert all(torch.equal(a, b) for a, b in zip(timed, seen))
+    _, _, rmask, rst = O.fwd(O.bf16_bits(q), O.bf16_bits(k), O.bf16_bits(v), 1, 0, 128, 16, 4, w.delta, tau,
+                             flags=O.SR8 if seed is not None else 0, seed=seed or 0, stats=True)
+    assert np.array_equal(timed[2].cpu().numpy(), rmask)
+    got = st.cpu().numpy().astype(np.uint64)
+    sel = [0, 1, 2, 3, 4, 5] + list(range(8, 8 + w.nk + 1))
+    assert got[sel].tolist() == rst[sel].tolist()
+    if gain > 1.0:
+        assert got[4] > 0 or tau == 0.0
