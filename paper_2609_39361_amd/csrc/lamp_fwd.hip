@@ -85,8 +85,8 @@ struct Cfg {
 // SR: the 8-bit logits with stochastic rounding (lamp_sr.h) in place of
 // round-to-nearest.
 // OBS: the instantiation that also writes the logit observables (p.dbg_y8,
-// p.dbg_y16), kept apart so that the stores do not change the register
-// allocation of the others.
+// p.dbg_y16) and, with SR, counts saturations, kept apart so that these do not
+// change the register allocation of the others.
 template <int D, int BQ, int BK, int NK, bool SR, bool OBS>
 __global__ __launch_bounds__((Cfg<D, BQ, BK, NK>::NT), 2) void lamp_fwd_kernel(FwdParams p)
 {
@@ -290,8 +290,8 @@ __global__ __launch_bounds__((Cfg<D, BQ, BK, NK>::NT), 2) void lamp_fwd_kernel(F
                         uint32_t a8[QPL][4], sat[QPL];
                         if constexpr (SR) {
                             const int jq[QPL] = {q0 + row[0]};
-                            sr8_chunk_bc<D, QPL, GrpLay>(qr, kt32 + (size_t)ck0 * D, jq, (uint32_t)ck0, (uint32_t)bh,
-                                                         p.seed, a8, sat);
+                            sr8_chunk_bc<D, QPL, GrpLay, OBS>(qr, kt32 + (size_t)ck0 * D, jq, (uint32_t)ck0,
+                                                              (uint32_t)bh, p.seed, a8, sat, p.stats != nullptr);
                         } else {
                             emu8_any<D, QPL, false, GrpLay>(qr, keys16<GrpLay>(kt32 + (size_t)ck0 * D), a8, sat);
                         }
@@ -895,7 +895,7 @@ static hipError_t launch_fwd_obs(const FwdParams &p, hipStream_t s)
 template <int D, int BQ, int BK, int NK, bool SR = false>
 static hipError_t launch_fwd(const FwdParams &p, hipStream_t s)
 {
-    if (p.dbg_y8 || p.dbg_y16) return launch_fwd_obs<D, BQ, BK, NK, SR, true>(p, s);
+    if (p.dbg_y8 || p.dbg_y16 || (SR && p.stats)) return launch_fwd_obs<D, BQ, BK, NK, SR, true>(p, s);
     return launch_fwd_obs<D, BQ, BK, NK, SR, false>(p, s);
 }
 

@@ -181,8 +181,8 @@ __device__ __forceinline__ int wave_max_i32(int v)
 } // namespace
 
 // OBS: the instantiation that also writes the logit observables (p.dbg_y8,
-// p.dbg_y16); the same code otherwise, kept apart so that the stores do not
-// change the register allocation of the instantiations that do not.
+// p.dbg_y16) and, with SR, counts saturations (p.stats); the same code otherwise,
+// kept apart so that these do not change the register allocation of the others.
 // CMP: the schedule of the compact register layout (Sec. 3.3, "Register
 // layout"): the fused pass computes the 16-bit logits of at most one
 // speculative sub-block; when two or more are flagged (a
@@ -593,8 +593,9 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
         uint32_t a8[QPL][Y8_WORDS<SIMP>], sat[QPL];
         if (done) {
             if constexpr (SR)
-                sr8_chunk_bc<D, QPL, GrpLay>(qr, kt32 + (size_t)(t * KPT + w * BK) * D, jq, (uint32_t)(t * KPT + w * BK),
-                                             (uint32_t)(b * p.Hq + h), p.seed, a8, sat);
+                sr8_chunk_bc<D, QPL, GrpLay, OBS>(qr, kt32 + (size_t)(t * KPT + w * BK) * D, jq,
+                                                  (uint32_t)(t * KPT + w * BK), (uint32_t)(b * p.Hq + h), p.seed, a8, sat,
+                                                  p.stats != nullptr);
             else emu8_any<D, QPL, SIMP, GrpLay>(qr, keys16<GrpLay>(kt32 + (size_t)(t * KPT + w * BK) * D), a8, sat);
         }
         emit8(t, a8, done, sat);
@@ -652,8 +653,8 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
             }
             if constexpr (SR)
                 if (emu)
-                    sr8_chunk_bc<D, QPL, GrpLay>(qr, k32e, jq, (uint32_t)(k0 + KPT + w * BK), (uint32_t)(b * p.Hq + h),
-                                                 p.seed, a8, sat8);
+                    sr8_chunk_bc<D, QPL, GrpLay, OBS>(qr, k32e, jq, (uint32_t)(k0 + KPT + w * BK),
+                                                      (uint32_t)(b * p.Hq + h), p.seed, a8, sat8, p.stats != nullptr);
             LAMP_PH(0);
             if (has_next && mode != MODE_ALL16) emit8(t + 1, a8, emu, sat8);
             if constexpr (CMP) {
@@ -1465,7 +1466,7 @@ template <int D, int BQ, int MODE, bool SIMP, bool SR = false>
 static hipError_t launch_fwd16_mode(const FwdParams &p, hipStream_t s)
 {
     if constexpr (!SIMP)
-        if (p.dbg_y8 || p.dbg_y16) return launch_fwd16_form<D, BQ, MODE, SIMP, true, SR>(p, s);
+        if (p.dbg_y8 || p.dbg_y16 || (SR && p.stats)) return launch_fwd16_form<D, BQ, MODE, SIMP, true, SR>(p, s);
     return launch_fwd16_form<D, BQ, MODE, SIMP, false, SR>(p, s);
 }
 

@@ -62,13 +62,15 @@ __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uin
 // rows, whose codes share word acc[s][P] (bits 7:0, 15:8): one Philox call per
 // chain, then 8 steps of both, each decoding the pair, running both FP32 FMAs
 // (the keys by row broadcast) and rounding each value stochastically into its
-// byte.  Without CLAMP a |t| above 448 gives a NaN code, which the NaN carries
-// to the end of the chain (the caller then re-runs with CLAMP, which is the
-// saturating recursion: the two agree up to that step).
-template <int P, int QPL, bool CLAMP>
+// byte.  Without CLAMP a |t| above 448 gives +-448 as well or, rounded up, a
+// NaN code, which the NaN carries to the end of the chain (the caller then
+// re-runs with CLAMP, which is the saturating recursion: the two agree up to
+// that step).  COUNT: bit i of sat[s] is set when a step of key i had |t| > 448.
+template <int P, int QPL, bool CLAMP, bool COUNT>
 __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, const float4 (&q0)[QPL],
                                           const float4 (&q1)[QPL], const int (&j)[QPL], uint32_t key0,
-                                          uint32_t bh, uint32_t g, uint32_t s0, uint32_t s1, uint32_t (&acc)[QPL][8])
+                                          uint32_t bh, uint32_t g, uint32_t s0, uint32_t s1, uint32_t (&acc)[QPL][8],
+                                          uint32_t (&sat)[QPL])
 {
     const float kv[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
 #pragma unroll
@@ -84,6 +86,7 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
         philox4x32_10(wb, s0, s1);
         const float qv[8] = {q0[s].x, q0[s].y, q0[s].z, q0[s].w, q1[s].x, q1[s].y, q1[s].z, q1[s].w};
         uint32_t word = acc[s][P];
+        float ma = 0.0f, mb = 0.0f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const uint32_t ra = (c & 1) ? (wa[c / 2] & 0xFFFF0000u) : (wa[c / 2] << 16);
@@ -91,6 +94,10 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
             const float2 f = unpk_e4m3(word);
             float ta = fmac_bc<2 * P>(f.x, kv[c], qv[c]);
             float tb = fmac_bc<2 * P + 1>(f.y, kv[c], qv[c]);
+            if constexpr (COUNT) {
+                ma = __builtin_fmaxf(ma, __builtin_fabsf(ta));
+                mb = __builtin_fmaxf(mb, __builtin_fabsf(tb));
+            }
             if (CLAMP) {
                 ta = __builtin_amdgcn_fmed3f(ta, -448.0f, 448.0f);
                 tb = __builtin_amdgcn_fmed3f(tb, -448.0f, 448.0f);
@@ -99,6 +106,7 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
             word = (uint32_t)__builtin_amdgcn_cvt_sr_fp8_f32(tb, (int)rb, (int)word, 1);
         }
         acc[s][P] = word;
+        if constexpr (COUNT) sat[s] |= (ma > 448.0f ? 1u << (2 * P) : 0u) | (mb > 448.0f ? 2u << (2 * P) : 0u);
     }
 }
 
@@ -111,16 +119,18 @@ __device__ __forceinline__ void sr8_pair8(const float4 &k0, const float4 &k1, co
 // broadcast lane is an immediate, and one pair's chains at a time keep the
 // registers of the surrounding kernel free); the loads run 8 channels ahead in
 // two buffers written only by loads.  acc[s][p] receives the codes of keys
-// 2p (bits 7:0) and 2p+1 (bits 15:8).
-template <int D, int QPL, bool CLAMP, class LY>
+// 2p (bits 7:0) and 2p+1 (bits 15:8), sat[s] (COUNT) the saturated keys.
+template <int D, int QPL, bool CLAMP, bool COUNT, class LY>
 __device__ __forceinline__ void sr8_pass(const QRows<QPL> &qr, const float *k32, const int (&j)[QPL], uint32_t key0,
-                                         uint32_t bh, uint64_t seed, uint32_t (&acc)[QPL][8])
+                                         uint32_t bh, uint64_t seed, uint32_t (&acc)[QPL][8], uint32_t (&sat)[QPL])
 {
     static_assert(D % 16 == 0, "pairs of 8-channel blocks");
 #pragma unroll
-    for (int s = 0; s < QPL; ++s)
+    for (int s = 0; s < QPL; ++s) {
+        sat[s] = 0u;
 #pragma unroll
         for (int p = 0; p < 8; ++p) acc[s][p] = 0u;
+    }
     const uint32_t s0 = (uint32_t)seed, s1 = (uint32_t)(seed >> 32);
     const float *krow = k32 + (size_t)(__lane_id() & 15) * LY::KR;
     float4 ka0, ka1, kb0, kb1, qa0[QPL], qa1[QPL], qb0[QPL], qb1[QPL];
@@ -138,14 +148,14 @@ __device__ __forceinline__ void sr8_pass(const QRows<QPL> &qr, const float *k32,
 #pragma nounroll
         for (int p = 0; p < 8; ++p) {
             switch (p) {
-            case 0: sr8_pair8<0, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 1: sr8_pair8<1, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 2: sr8_pair8<2, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 3: sr8_pair8<3, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 4: sr8_pair8<4, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 5: sr8_pair8<5, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            case 6: sr8_pair8<6, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
-            default: sr8_pair8<7, QPL, CLAMP>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc); break;
+            case 0: sr8_pair8<0, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 1: sr8_pair8<1, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 2: sr8_pair8<2, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 3: sr8_pair8<3, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 4: sr8_pair8<4, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 5: sr8_pair8<5, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            case 6: sr8_pair8<6, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
+            default: sr8_pair8<7, QPL, CLAMP, COUNT>(k0, k1, q0, q1, j, key0, bh, g, s0, s1, acc, sat); break;
             }
         }
     };
@@ -165,12 +175,15 @@ __device__ __forceinline__ void sr8_pass(const QRows<QPL> &qr, const float *k32,
 
 // sr8_pass without saturation first; if any lane of the wave overflowed (a
 // NaN code at the end of a chain), the chunk again with the clamp.  w[s][p]
-// receives the codes of keys 4p .. 4p+3, one per byte, sat[s] the keys of slot
-// s whose accumulation saturated (as emu8_check).
-template <int D, int QPL, class LY>
+// receives the codes of keys 4p .. 4p+3, one per byte.  COUNT and count
+// (uniform): the pass with the clamp alone, and sat[s] the keys of slot s with a
+// |t| > 448 (one in (448, 480) may round to 448 and leave no NaN); else sat is 0.
+// Kept to the kernels' observing instantiations: in the others the third pass
+// changes the register allocation (8K prefill 38.96 to 39.45 ms).
+template <int D, int QPL, class LY, bool COUNT = false>
 __device__ __forceinline__ void sr8_chunk_bc(const QRows<QPL> &qr, const float *k32, const int (&j)[QPL],
                                              uint32_t key0, uint32_t bh, uint64_t seed, uint32_t (&w)[QPL][4],
-                                             uint32_t (&sat)[QPL])
+                                             uint32_t (&sat)[QPL], bool count = false)
 {
     uint32_t acc[QPL][8];
     auto pack = [&] {
@@ -179,18 +192,21 @@ __device__ __forceinline__ void sr8_chunk_bc(const QRows<QPL> &qr, const float *
 #pragma unroll
             for (int p = 0; p < 4; ++p) w[s][p] = (acc[s][2 * p] & 0xFFFFu) | (acc[s][2 * p + 1] << 16);
     };
-    sr8_pass<D, QPL, false, LY>(qr, k32, j, key0, bh, seed, acc);
+    if constexpr (COUNT)
+        if (count) {
+            sr8_pass<D, QPL, true, true, LY>(qr, k32, j, key0, bh, seed, acc, sat);
+            pack();
+            return;
+        }
+    sr8_pass<D, QPL, false, false, LY>(qr, k32, j, key0, bh, seed, acc, sat);
     pack();
     uint32_t nan = 0;
 #pragma unroll
-    for (int s = 0; s < QPL; ++s) {
-        sat[s] = 0u;
+    for (int s = 0; s < QPL; ++s)
 #pragma unroll
         for (int p = 0; p < 4; ++p) nan |= e4m3x4_nan_bits(w[s][p]);
-    }
     if (wave_any(nan != 0)) {
-        nan_keys<QPL>(w, sat);
-        sr8_pass<D, QPL, true, LY>(qr, k32, j, key0, bh, seed, acc);
+        sr8_pass<D, QPL, true, false, LY>(qr, k32, j, key0, bh, seed, acc, sat);
         pack();
     }
 }

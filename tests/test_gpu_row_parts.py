@@ -53,7 +53,7 @@ def test_large_grid_equals_its_parts(L, d, N, causal, window, flags, seed, tau):
     (128, 140, 0, None, 8.0, math.inf), (128, 140, 0, None, 8.0, 0.5), (128, 140, 0, None, 1.0, 2.0 ** -5),
     (128, 140, 0, None, 8.0, 0.0), (64, 130, 0, None, 8.0, math.inf), (64, 130, 0, None, 8.0, 0.5),
     (256, 130, 0, None, 1.0, 0.5), (256, 130, 0, None, 1.0, 2.0 ** -5), (128, 140, 16, None, 8.0, 0.5),
-    (256, 130, 16, None, 1.0, 2.0 ** -5), (128, 130, 0, 11, 1.0, 0.5), (64, 130, 0, 11, 1.0, math.inf)])
+    (256, 130, 16, None, 1.0, 2.0 ** -5), (128, 130, 0, 11, 8.0, 0.5), (64, 130, 0, 11, 8.0, math.inf)])
 def test_large_grid_observables_and_statistics(L, d, N, flags, seed, gain, tau):
     """The 128-row form's 8-bit and used 16-bit codes on sampled heads and its
     statistics words (saturations of both formats among them), against the

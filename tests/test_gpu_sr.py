@@ -119,6 +119,27 @@ def test_fwd_sr_variants(L, w, flags):
     _compare(L, w, 0.5, flags=flags, seed=SEEDS[1])
 
 
+@pytest.mark.parametrize("tau", [math.inf, 0.5])
+@pytest.mark.parametrize("d,bq,bk,N,gain", [(64, 64, 16, 150, 8.0), (64, 64, 64, 150, 8.0), (128, 128, 16, 300, 8.0),
+                                            (128, 128, 64, 150, 8.0), (256, 128, 16, 140, 6.0), (128, 64, 16, 140, 1.0)])
+def test_fwd_sr_statistics(L, d, bq, bk, N, gain, tau):
+    """The statistics words equal the oracle's: a logit counts as saturated when
+    a step exceeds 448, whichever way that step rounds."""
+    w = W.small("sr_st", N=N, d=d, Hq=2, Hkv=1, bq=bq, bk=bk, nk=4, causal=1, seed=430 + d + bk, extra={"gain": gain})
+    qd, kd, vd, qb, kb, vb = _inputs(w)
+    st = torch.zeros(L.stats_words(4), dtype=torch.int64, device="cuda")
+    got = L.attn_fwd(qd, kd, vd, 1, 0, bq, bk, 4, w.delta, tau, sr_seed=SEEDS[1], stats=st)
+    plain = L.attn_fwd(qd, kd, vd, 1, 0, bq, bk, 4, w.delta, tau, sr_seed=SEEDS[1])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, plain))
+    _, _, rmask, rst = O.fwd(qb, kb, vb, 1, 0, bq, bk, 4, w.delta, tau, flags=O.SR8, seed=SEEDS[1], stats=True)
+    assert np.array_equal(got[2].cpu().numpy(), rmask)
+    s = st.cpu().numpy().astype(np.uint64)
+    sel = [0, 1, 2, 3, 4, 5] + list(range(8, 13))
+    assert s[sel].tolist() == rst[sel].tolist()
+    assert (s[4] > 0) == (gain > 1.0)
+
+
 def test_fwd_sr_row_with_every_exponential_underflowing(L):
     """With the first stage off, mu_hat is the largest 8-bit logit; here
     (seed 3, query row 123) a stochastically rounded 8-bit logit overshoots its
