@@ -1453,13 +1453,15 @@ static hipError_t launch_fwd16_wr(const FwdParams &p, hipStream_t s)
 template <int D, int BQ, int MODE, bool SIMP, bool OBS, bool SR>
 static hipError_t launch_fwd16_form(const FwdParams &p, hipStream_t s)
 {
-    if constexpr (BQ == 128) {
-        // the compact schedule: threshold mode, hardware formats, 128-row blocks, d >= 128
-        if constexpr (MODE == MODE_LAMP && !SIMP && !SR && D >= 128)
-            if (p.flags & LAMP_COMPACT) return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, true>(p, s);
-        if (!fwd16_wide(p, BQ)) return launch_fwd16_wr<D, BQ, 128, MODE, SIMP, OBS, false, SR>(p, s);
-    }
-    return launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, false, SR>(p, s);
+    // the compact schedule: threshold mode, hardware formats, 128-row blocks, d >= 128
+    constexpr bool HAS_CMP = MODE == MODE_LAMP && !SIMP && !SR && BQ == 128 && D >= 128;
+    const bool cmp = HAS_CMP && (p.flags & LAMP_COMPACT) != 0u;
+    if constexpr (BQ == 128)
+        if (!fwd16_wide(p, BQ))
+            return cmp ? launch_fwd16_wr<D, BQ, 128, MODE, SIMP, OBS, HAS_CMP, SR>(p, s)
+                       : launch_fwd16_wr<D, BQ, 128, MODE, SIMP, OBS, false, SR>(p, s);
+    return cmp ? launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, HAS_CMP, SR>(p, s)
+               : launch_fwd16_wr<D, BQ, 64, MODE, SIMP, OBS, false, SR>(p, s);
 }
 
 template <int D, int BQ, int MODE, bool SIMP, bool SR = false>
