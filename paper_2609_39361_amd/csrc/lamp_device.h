@@ -50,11 +50,6 @@ __device__ __forceinline__ uint32_t pk_e4m3_sat_hi(float a, float b, uint32_t ol
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, true);
 }
 
-// Pointers into read-only memory that every lane of a wave reads at the same
-// address: the constant address space makes the compiler use scalar loads.
-typedef const float __attribute__((address_space(4))) *kptr32_t;
-typedef const double __attribute__((address_space(4))) *kptr64_t;
-
 // Nonzero iff one of the two codes in bits [15:0] is a NaN code.
 __device__ __forceinline__ uint32_t e4m3_nan_bits(uint32_t r)
 {
@@ -155,14 +150,7 @@ __device__ __forceinline__ uint32_t ue5m11_code(float x)
     return c < 65535u ? c : 65535u;
 }
 
-// --- exponential codes -------------------------------------------------------
-// Value of a ue5m11 (bias 31) exponential code, exact in fp32.
-__device__ __forceinline__ float ue5m11e_value(uint32_t c)
-{
-    uint32_t ex = c >> 11, m = c & 0x7FFu;
-    return ex ? __builtin_bit_cast(float, ((ex + 96u) << 23) | (m << 12)) : (float)m * 0x1p-41f;
-}
-
+// --- bf16 parts of exponentials ----------------------------------------------
 // bf16 bit pattern of a bf16-exact fp32 value.
 __device__ __forceinline__ uint32_t bf16_bits(float v)
 {
@@ -232,20 +220,6 @@ __device__ __forceinline__ uint32_t sim_shift_index(float mu, float y)
     int e = (int)(r >> 23) - 127;
     e = e < EMIN ? EMIN : (e > EMAX ? EMAX : e);
     return ((uint32_t)(e - EMIN) << P) | ((r >> DROP) & ((1u << P) - 1u));
-}
-
-// Column maxima of SIM logits merge through an integer atomic max: the FP32
-// pattern mapped to an int that orders like the value (negative patterns
-// have their magnitude bits flipped); the map is its own inverse.
-__device__ __forceinline__ int ord_of(float y)
-{
-    const int b = __builtin_bit_cast(int, y);
-    return b ^ ((b >> 31) & 0x7FFFFFFF);
-}
-
-__device__ __forceinline__ float ord_value(int k)
-{
-    return __builtin_bit_cast(float, k ^ ((k >> 31) & 0x7FFFFFFF));
 }
 
 // --- exp_doc ----------------------------------------------------------------

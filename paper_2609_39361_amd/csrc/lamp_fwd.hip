@@ -68,8 +68,8 @@ struct Cfg {
     static constexpr size_t OFF_YL = OFF_Y + (size_t)BQ * YP * 2;        // 16-bit codes, then low bf16 parts of E16
     static constexpr size_t OFF_LUT = OFF_YL + (size_t)BQ * YP * 2;
     static constexpr size_t OFF_M8 = OFF_LUT + 512;                       // f32 [NK][BQ]
-    static constexpr size_t OFF_CM = OFF_M8 + (size_t)NK * BQ * 4;       // f32 [NK][BQ] + [2][NW][BQ]
-    static constexpr size_t OFF_SP = OFF_CM + (size_t)(NK + 2 * NW) * BQ * 4;   // f64 [2][NW][BQ]
+    static constexpr size_t OFF_CM = OFF_M8 + (size_t)NK * BQ * 4;       // f32 [NK][BQ]
+    static constexpr size_t OFF_SP = OFF_CM + (size_t)NK * BQ * 4;       // f64 [2][NW][BQ]
     static constexpr size_t OFF_CO = OFF_SP + (size_t)2 * NW * BQ * 8;   // f64 [NK][BQ]
     static constexpr size_t OFF_ED = OFF_CO + (size_t)NK * BQ * 8;       // f64 [EXPDOC_NK]
     static constexpr size_t OFF_VT = OFF_ED + (size_t)EXPDOC_NK * 8;     // u32 [2][2] votes of the row parts
@@ -104,7 +104,6 @@ __global__ __launch_bounds__((Cfg<D, BQ, BK, NK>::NT), 2) void lamp_fwd_kernel(F
     uint16_t *lut = reinterpret_cast<uint16_t *>(smem + C::OFF_LUT);   // [256] 8-bit exp (bf16 bits)
     float *m8s = reinterpret_cast<float *>(smem + C::OFF_M8);          // [NK][BQ] 8-bit column maxima
     float *cms = reinterpret_cast<float *>(smem + C::OFF_CM);          // [NK][BQ] 16-bit column maxima
-    float *cmf = cms + NK * BQ;   // [2][NW][BQ] per-wave maxima of a shared recompute, by iteration parity
     double *sps = reinterpret_cast<double *>(smem + C::OFF_SP);        // [NW][BQ] partial row sums of E
     double *spf = sps + NW * BQ;                                       // [NW][BQ] the same over 8-bit sub-blocks
     double *cst_lds = reinterpret_cast<double *>(smem + C::OFF_CO);    // [NK][BQ] stage-2 costs
