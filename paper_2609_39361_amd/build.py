@@ -30,9 +30,10 @@ ARCH = "gfx950"
 
 SOURCES = ["lamp_kernels.hip", "lamp_fwd.hip", "lamp_fwd16.hip", "lamp_fwd16_sr.hip", "lamp_decode.hip", "lamp_rates.hip",
            "lamp_noalloc.hip", "lamp_host.cpp"]
-# parts of lamp_fwd16.hip that this build compiles as units of their own, side
-# by side (-DLAMP_SPLIT_UNITS; without it lamp_fwd16.hip includes them)
-SPLIT_UNITS = ["lamp_fwd16_d64.hip", "lamp_fwd16_d256.hip", "lamp_fwd16_sim.hip"]
+# parts of lamp_fwd16.hip and lamp_fwd16_sr.hip that this build compiles as units
+# of their own, side by side (-DLAMP_SPLIT_UNITS; without it those include them)
+SPLIT_UNITS = ["lamp_fwd16_d64.hip", "lamp_fwd16_d256.hip", "lamp_fwd16_sim.hip", "lamp_fwd16_sr_d64.hip",
+               "lamp_fwd16_sr_d256.hip"]
 
 DPP_VGPR_WAITS = 2
 DPP_EXEC_WAITS = 5
@@ -168,7 +169,7 @@ def build(verbose=False, extra=(), out=LIB):
              "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-DLAMP_SPLIT_UNITS",
              "-I", os.path.join(ROOT, "include"), "-I", CSRC,
              "-Wno-unused-command-line-argument", "-save-temps"] + list(extra)
-    units = SOURCES + SPLIT_UNITS
+    units = SPLIT_UNITS + SOURCES   # (the longest among the first)
     jobs = max(1, min(len(units), int(os.environ.get("MAX_JOBS", "0")) or (os.cpu_count() or 1)))
     with tempfile.TemporaryDirectory(prefix="lamp_build_") as work:
         with ThreadPoolExecutor(max_workers=jobs) as ex:

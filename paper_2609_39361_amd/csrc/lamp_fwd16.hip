@@ -1480,6 +1480,14 @@ static hipError_t launch_fwd16(const FwdParams &p, hipStream_t s)
     return launch_fwd16_mode<D, BQ, MODE_LAMP, SIMP>(p, s);
 }
 
+// Stochastic rounding (the all-16-bit mode computes no 8-bit logit).
+template <int D, int BQ>
+static hipError_t launch_fwd16_sr(const FwdParams &p, hipStream_t s)
+{
+    if (p.mode == MODE_PURE8) return launch_fwd16_mode<D, BQ, MODE_PURE8, false, true>(p, s);
+    return launch_fwd16_mode<D, BQ, MODE_LAMP, false, true>(p, s);
+}
+
 #ifndef LAMP_FWD16_PART
 // d = 128 with the formats of Sec. 3.3 here; d = 64, d = 256 and the SIM profile
 // in lamp_fwd16_d64.hip, lamp_fwd16_d256.hip and lamp_fwd16_sim.hip, which the library's build compiles

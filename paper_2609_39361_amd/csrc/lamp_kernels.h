@@ -63,6 +63,8 @@ hipError_t dispatch_fwd16_d64(int BQ, const FwdParams &p, hipStream_t s, bool *f
 hipError_t dispatch_fwd16_d256(int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sim(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd16_sr(int D, int BQ, const FwdParams &p, hipStream_t s, bool *found);
+hipError_t dispatch_fwd16_sr_d64(int BQ, const FwdParams &p, hipStream_t s, bool *found);
+hipError_t dispatch_fwd16_sr_d256(int BQ, const FwdParams &p, hipStream_t s, bool *found);
 hipError_t dispatch_fwd(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
 // the forward pass with stochastically rounded 8-bit logits
 hipError_t dispatch_fwd_sr(int D, int BQ, int BK, int NK, const FwdParams &p, hipStream_t s, bool *found);
