@@ -28,15 +28,14 @@ sys.path.insert(0, ROOT)
 # peak, 157.3 TFLOP/s (packed FMAs: 2 flops on 2 values per lane and cycle).
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9          # 39.3e12 lane-instructions / s
 FP32_PEAK_FLOPS = 157.3e12
-# Fewest VALU lane-instructions per emulated 8-bit multiply-add on gfx950: one
-# fp32 FMA, half a packed round-to-e4m3 and half a packed decode.
+# Lane-operations counted per emulated 8-bit multiply-add: one fp32 FMA (in a
+# rank-1 matrix instruction), half a packed round-to-e4m3 and half a packed decode.
 OPS_PER_MAC8 = 2.0
 # 16-bit recompute: one fp32 FMA per multiply-add.
 OPS_PER_MAC16 = 1.0
-# SIM precision profile (flag 4): the 8-bit step is one fp32 FMA and a
-# round-to-nearest-even of the FP32 encoding to 3 mantissa bits (bit-field
-# extract of the last kept bit, one 3-input add, one mask): 4 per MAC.
-OPS_PER_MAC8_SIM = 4.0
+# SIM precision profile (flag 4): the 8-bit step is one fp32 FMA and a rounding
+# to 3 mantissa bits in two operations: 3 per MAC.
+OPS_PER_MAC8_SIM = 3.0
 SIM_FLAG = 4
 
 
@@ -424,7 +423,8 @@ def run_fwd(args, w, tau, flags, host_inputs, dev_inputs, out, dev):
     rates = lamp.issue_rates()
     simds = 4 * torch.cuda.get_device_properties(dev).multi_processor_count
     step8 = rates["emulated_step_sim"] / 64.0 if sim else rates["emulated_step"] / 128.0
-    # a 16-bit multiply-add: what an 8-bit step takes beside its conversions
+    # a 16-bit multiply-add, by subtraction (the rate library times no matrix
+    # instruction by itself): what an 8-bit step takes beside its conversions
     mac16_ns = rates["emulated_step"] / 2.0 - (rates["cvt_pk_f32_fp8"] + rates["cvt_pk_fp8_f32"]) / 2.0
     floor_ms = (mac8 * step8 + mac16 / 64.0 * max(mac16_ns, 0.0)) / simds * 1e-6
     issue_floor = None if sr else {
@@ -474,15 +474,17 @@ def run_fwd(args, w, tau, flags, host_inputs, dev_inputs, out, dev):
             "frac_vs_measured_fmac_rate": macs_per_s / fmac_rate,
             "measured_fmac_lane_ops_per_s": fmac_rate,
             "traffic": None if sr else measured_traffic(w.name, tau, flags),
-            "kernel": ("lamp_fwd16_kernel<%d,%d,%d,%s%s>" % (w.d, w.bq, _mode_of(tau), "true" if sim else "false",
-                                                             ",SR" if sr and _mode_of(tau) != 2 else ""))
-                      if (w.bk == 16 and w.d >= 128)
+            # WR: 64 or 128 query rows per wave, by the grid
+            "kernel": ("lamp_fwd16_kernel<%d,%d,WR,%d,%s%s>" % (w.d, w.bq, _mode_of(tau), "true" if sim else "false",
+                                                                ",SR" if sr and _mode_of(tau) != 2 else ""))
+                      if w.bk == 16
                       else ("lamp_fwd_kernel<%d,%d,%d,%d%s>" % (w.d, w.bq, w.bk, w.nk, ",SR" if sr else "")),
             "kernel_ms": kernel_ms,
             "prepass_ms": pre_ms_sum / launches,
             "macs_per_launch": {"mac8": mac8, "mac16": mac16},
-            "ops_per_unit": ("1 per MAC for frac; frac_2op_per_mac8 charges %d per emulated 8-bit MAC "
-                             "(this emulation's cost) and 1 per 16-bit MAC" % (OPS_PER_MAC8_SIM if sim else OPS_PER_MAC8)),
+            "ops_per_unit": ("1 per MAC for frac; frac_2op_per_mac8 charges %d lane-operations per emulated 8-bit "
+                             "MAC (its FMA, decode and rounding; the FMAs run as matrix instructions) and 1 per 16-bit "
+                             "MAC" % (OPS_PER_MAC8_SIM if sim else OPS_PER_MAC8)),
             "valu_issue_frac_counters": None if sr else measured_valu_issue(w.name, tau, flags),
             "issue_floor": issue_floor,
         },

@@ -1424,11 +1424,18 @@ __global__ __launch_bounds__((Cfg16<D, BQ, WR>::NT), 2) void lamp_fwd16_kernel(F
 // two side by side need 48 us for a tile of each, so that a loaded device is
 // 1.2x faster with 128 rows, whose blocks are out of step with each other.
 // The line is where the blocks' key tiles, counted in blocks as long as the
-// longest, fill the compute units once: a causal pass of 512 blocks (half as
-// long on average as the longest) takes 1.05 against 1.20 ms, of 640 blocks
-// 1.64 against 1.56; blocks of equal length 0.93 against 1.01 ms at 256 and
-// 1.82 against 1.67 at 512 (d = 128; the same side, within 2 %, at d = 64 and
-// 256, in the simulation profile and with stochastic rounding).
+// longest, fill the compute units once.  Both sides of it, ms with 64 / 128 rows
+// (2048 tokens, d = 128; causal blocks are half as long on average as the longest):
+//                     causal, 512   causal, 640   equal, 256   equal, 512 blocks
+//   threshold 1/2     0.98 / 1.15   1.35 / 1.28   0.91 / 0.99  1.79 / 1.64
+//   pure 8-bit        0.69 / 0.86   0.96 / 0.95   0.64 / 0.67  1.26 / 1.19
+//   all 16-bit        0.40 / 0.48   0.55 / 0.51   0.37 / 0.45  0.71 / 0.63
+//   stochastic, 1/2   3.02 / 3.58   4.23 / 4.03   2.83 / 3.52  5.65 / 5.35
+//   SIM, 1/2          1.06 / 1.55   1.46 / 1.59   1.00 / 1.45  1.93 / 2.00
+// At d = 64 and 256 the line chooses the faster side or one within 2 % of it as
+// well, but for d = 256 with 640 causal blocks in the all-16-bit mode (0.91 /
+// 0.96).  The SIM profile would have its line later, at d = 256 beyond these grids
+// (its 128-row form spills most: 640 causal blocks 2.40 / 3.33).
 inline bool fwd16_wide(const FwdParams &p, int BQ)
 {
     const int64_t blocks = (int64_t)p.B * p.Hq * (p.Nq / BQ);

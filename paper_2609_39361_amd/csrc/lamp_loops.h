@@ -14,12 +14,16 @@
 //
 // What bounds it: VALU issue.  The fp32 matrix instructions do not overlap the
 // VALU's conversions (neither of their own wave nor of another), but feed the
-// keys for free: 0.89 ns per 64 multiply-adds and SIMD, against 1.99 ns for an
-// FMA that reads its key through a DPP broadcast and 1.19 ns for one on plain
-// registers.  The 8-bit step (decode a code pair 2.09 ns, round a value pair
-// to e4m3 3.70 ns) takes 3.65 ns per 64 multiply-adds instead of 4.54 with
-// broadcast FMAs; the 16-bit accumulation 0.9 instead of 1.99.  (Decoding on
-// the fp8 matrix instructions instead was no faster: 3.4 to 3.7 ns.)
+// keys for free.  Measured in one run, ns per wave and SIMD (they move together
+// by some 4 % from run to run): the matrix instruction 3.60, 0.90 per 64
+// multiply-adds, against 1.78 for an FMA that reads its key through a DPP
+// broadcast and 1.09 for one on plain registers; decoding a code pair 1.96,
+// rounding a value pair to e4m3 3.39.  Per 64 multiply-adds the parts of the
+// 8-bit step come to 0.90 + (1.96 + 3.39) / 2 = 3.58, and the step takes 3.72:
+// nothing overlaps, and the changes between the two kinds cost the rest.  With
+// broadcast FMAs the parts come to 4.45.  The 16-bit accumulation takes 0.90.
+// (Decoding on the fp8 matrix instructions instead was no faster: 0.93 to 1.01
+// of the step's time.)
 #pragma once
 #include <utility>
 
@@ -142,9 +146,8 @@ __device__ __forceinline__ void fma_groups(float kv, float q, f32x4_t (&c)[NG], 
 // keys of kr.  In three batches that nothing is scheduled across -- decode the
 // four code words, the matrix instructions back to back, round back -- because
 // every change between the VALU and the matrix instructions costs some 8
-// cycles: alternating them one by one took 4.32 ns per 64 multiply-adds, the
-// batches 3.65 (all eight words of two rows in one batch: the same, with 16
-// more registers).
+// cycles: alternating them one by one took 1.18 times as long as the batches (all
+// eight words of two rows in one batch: the same time, with 16 more registers).
 template <int R, bool SAT, int NM>
 __device__ __forceinline__ void emu8_row(float ke, float kr, float q, uint32_t (&w)[4], f32x4_t (&acc)[NM > 0 ? NM : 1])
 {
@@ -172,9 +175,10 @@ __device__ __forceinline__ void emu8_row(float ke, float kr, float q, uint32_t (
 }
 
 // The 8-bit SIM rounding of a value that is 0 or has 2^-126 <= |t| < 2^107, in
-// two FMA-class operations instead of three integer ones (2.3 against 4.8 ns per
-// 64 values and SIMD).  With t = m 2^(e-23) and q = 2^(e-3) the quantum to round
-// to, t (2^20 - 1) = (m - m 2^-20) q rounded to FP32 is m - RN(m 2^-20) quanta,
+// two FMA-class operations instead of three integer ones (the step of one
+// multiply-add takes 2.95 ns per 64 and SIMD, 0.90 of it the matrix
+// instruction; the integer operations alone took 4.8).  With t = m 2^(e-23) and
+// q = 2^(e-3) the quantum to round to, t (2^20 - 1) = (m - m 2^-20) q rounded to FP32 is m - RN(m 2^-20) quanta,
 // ties to even since m is even there, and t 2^20 = m q minus it is t rounded
 // (Dekker's splitting).  Below 2^23 quanta, m < 2^23 + 8, the product's ulp is
 // q/2, but m 2^-20 then lies within 2^-17 of 8 and rounds to it all the same; a
@@ -406,7 +410,7 @@ __device__ __forceinline__ void fused_pass(QRows<QPL> &qr, const KRows &ke, cons
     if (!(EMU && SIMP) || !qr.exact)
         logit_loop<D, QPL, NM, EMU, SIMP, false, EMU ? 2 : 4, LY>(qr, ke, kr, w8, e8, acc, kmin);
     if constexpr (EMU && SIMP) {
-        // out of range once: the rest of the workgroup's tiles at once exactly
+        // out of range once: the rest of this wave's tiles at once exactly
         f32x4_t none[QPL][1];
         if (qr.exact) {
             if constexpr (NM > 0) logit_loop<D, QPL, NM, false, true, false, 4, LY>(qr, kr, kr, w8, none, acc, kmin);

@@ -42,8 +42,8 @@ __global__ __launch_bounds__(256) void rate_fmac_kernel(float *out, int iters, f
 }
 
 // fp32 FMA reading its first operand through a DPP row broadcast (the key feed
-// of the logit loops); the wait states keep the broadcast source away from
-// the VALU write that produced it
+// of the stochastic-rounding loop); the wait states keep the broadcast source
+// away from the VALU write that produced it
 __global__ __launch_bounds__(256) void rate_fmac_dpp_kernel(float *out, int iters, float q)
 {
     float a[16];

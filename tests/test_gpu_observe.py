@@ -112,8 +112,8 @@ SMALL = [
 @pytest.mark.parametrize("w", SMALL, ids=[w.name for w in SMALL])
 def test_observables_small(L, w, tau):
     """Every query block observed: all 8-bit codes and all used 16-bit codes
-    of both kernels (pipelined: 16-key sub-blocks with d >= 128; general:
-    d = 64 or 64-key sub-blocks), ragged lengths, saturating inputs."""
+    of both kernels (pipelined: 16-key sub-blocks; the other: 64-key
+    sub-blocks), ragged lengths, saturating inputs."""
     nqb = -(-w.N // w.bq)
     _check_observables(L, w, tau, 0, nqb)
 
@@ -138,7 +138,7 @@ def test_observed_instantiation_equals_timed_one(L, w, tau):
 
 def test_observables_subrange_and_sr(L):
     """A sub-range of query blocks (the others are not written), and the
-    stochastically rounded 8-bit logits of the general kernel."""
+    stochastically rounded 8-bit logits."""
     w = W.small("o_sr", N=320, d=128, Hq=2, Hkv=1, bq=64, bk=16, nk=4, causal=1, seed=507)
     _check_observables(L, w, 0.5, 2, 2)
     _check_observables(L, w, 0.5, 1, 3, sr_seed=9)
